@@ -6,13 +6,13 @@
 // from those of the single operators (Eqs. ci) by the product rule of App. A;
 // terms with equal (m, l, x, s) are merged by adding their prefactors.
 //
-// The product is taken in gather form from the bra side (Eq. Talpha2), one
-// lane per output row, so no atomics are needed:
+// The product is taken in gather form from the bra side (Eq. Talpha2), each
+// output row summed by one wave or workgroup, so no atomics are needed:
 //   y_alpha = sum_T v [alpha AND m == l] (-1)^popcount(alpha AND s) x[rank(alpha XOR x_T)]
-// with alpha = states[row] and the rank from the operator's ranker: a staggered
+// with alpha = states[row].  Ranks come from two small tables where the sector
+// allows it (op_sum_tables), else from the operator's ranker: a staggered
 // table (sector C^M_N; table staged in LDS when it fits) or a packed trie (any
-// sector; walk plus membership check).  Tuples are uniform across the lanes
-// and are read through the scalar path.
+// sector; walk plus membership check).
 #include <algorithm>
 #include <memory>
 #include <tuple>
@@ -104,69 +104,360 @@ std::vector<Tup> merge_terms(std::vector<Tup> ts) {
 }
 
 // ---------------------------------------------------------------- device apply
+// A wave takes kOpRows consecutive rows: lane = (tuple slot, row), four tuple
+// slots of sixteen rows, so one step evaluates four tuples on sixteen rows.
+// Consecutive members share their high bits, and a tuple whose requirement
+// fails on a bit that is the same in all of the wave's rows is dead for every
+// one of them.  The wave therefore first sieves the tuples, a tuple per lane
+// (64 per step, against the AND and the OR of its rows), and compacts the
+// survivors into its own LDS queue; only those are evaluated row by row.  On
+// the 14-site ring with total momentum 0 (841,332 rows, 2,772 tuples) about
+// one tuple in four survives.
+//
+// Few rows leave the chip idle when every wave runs through all tuples, so a
+// row group's tuples are then split over up to the 16 waves of a workgroup and
+// the partial sums added in wave order (see op_split).
+//
+// The tuples are kept in three ranges: diagonal ones (x = 0), which need no
+// rank; ones that keep every member inside the sector; and the rest, whose
+// targets are checked.  Inside a range they are ordered by the high bits they
+// flip, so that consecutive tuples gather from the same stretch of x, which
+// then sits in L1.
+//
+// What bounds it: issue of the evaluation steps (19 vector instructions per
+// four tuples and sixteen rows, a third of the lanes live), the SIMDs being
+// about 70% busy; the gathers of x hit L1 and L2 (1.1 lines looked up per
+// term).  One row per lane running through every tuple took 2,937 us on the
+// ring (sum tables below, 594 us with the sieve) and 3,180 us on 15 orbitals
+// half filled (6,435 rows, 11,250 tuples; 52 us).
 constexpr unsigned kBlock = 256;
 constexpr size_t kLdsTable = 64 * 1024;
 
-enum RankKind { kStagLds = 0, kStagGlobal = 1, kTrie = 2 };
+constexpr int kOpRows = 16;                 // rows per wave
+constexpr int kOpSlots = 64 / kOpRows;      // tuples evaluated side by side
+constexpr int kOpUnroll = 4;                // steps issued together
+constexpr int kOpWaves = 16;                // waves per workgroup
+constexpr unsigned kOpBlock = 64 * kOpWaves;
+constexpr unsigned kOpQueue = 128;          // survivors a wave can hold (fewer than 64 wait when a sieve step adds up to 64)
+
+// How a target pattern is ranked.  kSum*: rank = base[high bits] + off[low
+// bits], see op_sum_tables; the others are the operator's ranker.
+enum RankKind { kSumLds = 0, kSumGlobal = 1, kStagLds = 2, kStagGlobal = 3, kTrie = 4 };
+
+template <class P>
+struct alignas(2 * sizeof(P)) Two {
+    P a, b;
+};
 
 template <class P>
 struct OpArgs {
     const P *states;
     uint64_t ns;
-    int64_t nt;
+    int64_t n_diag, n_keep, n_all;  // ends of the three tuple ranges
+    const Two<P> *ml, *xs;          // (m, l) and (x, s) of every tuple
     const double *v;
-    const P *m, *l, *x, *s;
-    const uint32_t *keep;  // per tuple: every member's target is a member
     const double *xin;
     double *out;
+    uint32_t split;                 // waves that share a row group's tuples (divides kOpWaves)
+    uint32_t units;                 // workgroup-sized pieces of the rows
     StagArgs stag;
     const void *stab;
     TrieWalk trie;
+    const uint32_t *base;           // sum tables
+    const uint16_t *off;
+    uint32_t n_base, n_off;
+    int32_t low_bits;
 };
 
+template <class P>
+__device__ __forceinline__ int popc(P v) {
+    return sizeof(P) == 8 ? __popcll((uint64_t)v) : __popc((uint32_t)v);
+}
+
+// at(): rank of a pattern known to be a member.  find(): rank of any pattern,
+// or a value >= ns outside the sector.
 template <class P, class E, int RK>
-__global__ void __launch_bounds__(kBlock) op_apply_kernel(OpArgs<P> a) {
+struct OpRank {
+    const OpArgs<P> &a;
+    const E *tab;          // staggered table
+    const uint32_t *base;  // sum tables
+    const uint16_t *off;
+    __device__ __forceinline__ uint64_t at(P be) const {
+        if constexpr (RK == kSumLds || RK == kSumGlobal) {
+            return base[be >> a.low_bits] + (uint32_t)off[be & (P)(a.n_off - 1)];
+        } else if constexpr (RK == kTrie) {
+            uint32_t node = 0;
+            for (int lv = 0; lv < a.trie.H; ++lv)
+                node = a.trie.tab[a.trie.off[lv] + node + ((uint32_t)(be >> a.trie.shift[lv]) & a.trie.wmask[lv])];
+            return node;
+        } else {
+            return stag_rank<P, E>(be, tab, a.stag);
+        }
+    }
+    __device__ __forceinline__ uint64_t find(P be) const {
+        if constexpr (RK == kSumLds || RK == kSumGlobal) {
+            const uint64_t r = (uint64_t)base[be >> a.low_bits] + off[be & (P)(a.n_off - 1)];
+            return r < a.ns && a.states[r] == be ? r : ~0ull;
+        } else if constexpr (RK == kTrie) {
+            const uint32_t q = trie_rank_one<P>(be, a.trie);
+            return q == MBR_NOT_FOUND ? ~0ull : q;
+        } else {
+            if (popc(be) != a.stag.N || !below_width(be, a.stag.M)) return ~0ull;
+            return stag_rank<P, E>(be, tab, a.stag);
+        }
+    }
+};
+
+// A wave's queue of surviving tuples.
+template <class P>
+struct OpQueue {
+    Two<P> ml[kOpQueue], xs[kOpQueue];
+    double v[kOpQueue];
+};
+
+// The queue is written and read by one wave; the hardware keeps a wave's LDS
+// accesses in order, the fences keep the compiler's.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+enum TupleRange { kDiagonal = 0, kKeeping = 1, kLeaving = 2 };
+
+// One range of tuples on the wave's rows: sieve, queue, evaluate.  `al` is the
+// pattern of the lane's row, `ref` that of any row and `same` the bits
+// that agree in all rows.  kDiagonal leaves the sum of signed prefactors in acc
+// and sets `any` when a tuple acted; the others add their terms to acc.
+template <class P, class R, int RANGE>
+__device__ __forceinline__ void op_range(const OpArgs<P> &a, const R &rk, OpQueue<P> &qu, int64_t begin, int64_t end,
+                                         uint32_t part, P al, P ref, P same, double &acc, bool &any) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t slot = (uint32_t)lane / kOpRows;
+    uint32_t cnt = 0;
+    auto eval = [&](uint32_t n) {  // the first n queued tuples, n a multiple of kOpSlots * kOpUnroll
+        const OpQueue<P> *p = &qu;
+        for (uint32_t i = slot; i < n; i += kOpSlots * kOpUnroll) {
+            Two<P> xs[kOpUnroll];
+            double v[kOpUnroll], xv[kOpUnroll];
+            bool ok[kOpUnroll];
+            uint64_t r[kOpUnroll];
+#pragma unroll
+            for (int u = 0; u < kOpUnroll; ++u) {
+                const Two<P> ml = p->ml[i + u * kOpSlots];
+                xs[u] = p->xs[i + u * kOpSlots];
+                v[u] = p->v[i + u * kOpSlots];
+                ok[u] = (al & ml.a) == ml.b;
+            }
+            // ranks, then gathers, then sums: each in flight for all the tuples of the step.  A tuple that does not
+            // act on this row still gets a rank (any pattern is safe to look up) but reads no x.
+            if constexpr (RANGE != kDiagonal) {
+#pragma unroll
+                for (int u = 0; u < kOpUnroll; ++u) {
+                    if constexpr (RANGE == kKeeping) {
+                        r[u] = rk.at(ok[u] ? al ^ xs[u].a : al);
+                    } else {
+                        r[u] = ok[u] ? rk.find(al ^ xs[u].a) : ~0ull;
+                        ok[u] = r[u] < a.ns;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kOpUnroll; ++u) {
+                    xv[u] = 0.0;
+                    if (ok[u]) xv[u] = a.xin[r[u]];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kOpUnroll; ++u) {
+                // signed prefactor, zero when the tuple does not act
+                const uint64_t bits = __builtin_bit_cast(uint64_t, v[u]);
+                uint32_t hi = (uint32_t)(bits >> 32) ^ ((uint32_t)popc((P)(al & xs[u].b)) << 31), lo = (uint32_t)bits;
+                hi = ok[u] ? hi : 0u;
+                lo = ok[u] ? lo : 0u;
+                const double c = __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+                if constexpr (RANGE == kDiagonal) {
+                    acc += c;
+                    any = any || ok[u];
+                } else {
+                    acc = __builtin_fma(c, xv[u], acc);
+                }
+            }
+        }
+    };
+    const int64_t step = (int64_t)64 * a.split;
+    int64_t t = begin + (int64_t)part * 64 + lane;
+    const int64_t tend = end + lane;  // t < tend holds for all lanes alike
+    Two<P> nx{};
+    if (t < end) nx = a.ml[t];
+    for (; t < tend; t += step) {
+        const Two<P> ml = nx;
+        const bool in = t < end;
+        if (t + step < end) nx = a.ml[t + step];
+        const bool live = in && (((ref ^ ml.b) & ml.a & same) == 0);
+        const uint64_t b = __ballot(live);
+        if (b == 0) continue;
+        if (live) {
+            const uint32_t q = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0));
+            qu.ml[q] = ml;
+            qu.xs[q] = a.xs[t];
+            qu.v[q] = a.v[t];
+        }
+        cnt += (uint32_t)__popcll(b);
+        if (cnt >= 64) {
+            wave_lds_fence();
+            eval(64);
+            cnt -= 64;
+            // the rest moves to the front
+            Two<P> m2{}, x2{};
+            double v2 = 0.0;
+            if (lane < (int)cnt) {
+                m2 = qu.ml[64 + lane];
+                x2 = qu.xs[64 + lane];
+                v2 = qu.v[64 + lane];
+            }
+            wave_lds_fence();
+            if (lane < (int)cnt) {
+                qu.ml[lane] = m2;
+                qu.xs[lane] = x2;
+                qu.v[lane] = v2;
+            }
+            wave_lds_fence();
+        }
+    }
+    if (cnt) {
+        // fill the last step with tuples that no pattern satisfies
+        const uint32_t n = (cnt + kOpSlots * kOpUnroll - 1) / (kOpSlots * kOpUnroll) * (kOpSlots * kOpUnroll);
+        if (cnt + lane < n) {
+            qu.ml[cnt + lane] = Two<P>{0, 1};
+            qu.xs[cnt + lane] = Two<P>{0, 0};
+            qu.v[cnt + lane] = 0.0;
+        }
+        wave_lds_fence();
+        eval(n);
+        wave_lds_fence();
+    }
+}
+
+template <class P>
+size_t op_lds_bytes(size_t table_bytes) {
+    return (table_bytes + 15) / 16 * 16 + kOpWaves * sizeof(OpQueue<P>) + kOpWaves * kOpRows * sizeof(double);
+}
+
+template <class P, class E, int RK>
+__global__ void __launch_bounds__(kOpBlock) op_apply_kernel(OpArgs<P> a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const E *tab = static_cast<const E *>(a.stab);
+    // LDS: rank tables | a queue per wave | partial sums of the split
+    size_t tb = 0;
+    OpRank<P, E, RK> rk{a, static_cast<const E *>(a.stab), a.base, a.off};
     if constexpr (RK == kStagLds) {
         E *t = reinterpret_cast<E *>(lds_raw);
-        for (uint64_t i = threadIdx.x; i < a.stag.nentries; i += blockDim.x) t[i] = tab[i];
-        __syncthreads();
-        tab = t;
-    }
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t row = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; row < a.ns; row += stride) {
-        const P al = a.states[row];
-        double acc = 0.0;
-        for (int64_t t = 0; t < a.nt; ++t) {
-            if ((al & a.m[t]) != a.l[t]) continue;
-            const P be = al ^ a.x[t];
-            uint64_t rr;
-            if (a.x[t] == 0) {
-                rr = row;
-            } else if constexpr (RK == kTrie) {
-                if (a.keep[t]) {
-                    // the target is a member, so the walk alone gives its rank
-                    uint32_t node = 0;
-                    for (int lv = 0; lv < a.trie.H; ++lv)
-                        node = a.trie.tab[a.trie.off[lv] + node + ((uint32_t)(be >> a.trie.shift[lv]) & a.trie.wmask[lv])];
-                    rr = node;
-                } else {
-                    const uint32_t q = trie_rank_one<P>(be, a.trie);
-                    if (q == MBR_NOT_FOUND) continue;  // the term leaves the sector
-                    rr = q;
-                }
-            } else {
-                const int h = (sizeof(P) == 8) ? __popcll((uint64_t)be) : __popc((uint32_t)be);
-                if (h != a.stag.N || !below_width(be, a.stag.M)) continue;  // leaves C^M_N
-                rr = stag_rank<P, E>(be, tab, a.stag);
-            }
-            const bool odd = ((sizeof(P) == 8) ? __popcll((uint64_t)(al & a.s[t])) : __popc((uint32_t)(al & a.s[t]))) & 1;
-            const double c = odd ? -a.v[t] : a.v[t];
-            acc = __builtin_fma(c, a.xin[rr], acc);
+        for (uint64_t i = threadIdx.x; i < a.stag.nentries; i += blockDim.x) t[i] = rk.tab[i];
+        tb = a.stag.nentries * sizeof(E);
+        rk.tab = t;
+    } else if constexpr (RK == kSumLds || RK == kSumGlobal) {
+        if constexpr (RK == kSumLds) {
+            uint32_t *b = reinterpret_cast<uint32_t *>(lds_raw);
+            for (uint32_t i = threadIdx.x; i < a.n_base; i += blockDim.x) b[i] = a.base[i];
+            rk.base = b;
+            tb = (size_t)a.n_base * 4;
         }
-        a.out[row] = acc;
+        uint16_t *o = reinterpret_cast<uint16_t *>(lds_raw + tb);
+        for (uint32_t i = threadIdx.x; i < a.n_off; i += blockDim.x) o[i] = a.off[i];
+        rk.off = o;
+        tb += (size_t)a.n_off * 2;
     }
+    tb = (tb + 15) / 16 * 16;
+    const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    OpQueue<P> &qu = reinterpret_cast<OpQueue<P> *>(lds_raw + tb)[w];
+    double *red = reinterpret_cast<double *>(lds_raw + tb + kOpWaves * sizeof(OpQueue<P>));
+    __syncthreads();
+    const uint32_t groups = kOpWaves / a.split;  // row groups of a workgroup
+    const uint32_t part = w % a.split;
+    // workgroup b runs on XCD b mod 8: each XCD takes one contiguous stretch of
+    // the rows (the grid is a multiple of 8)
+    const uint32_t xcd = blockIdx.x & 7;
+    const uint32_t u1 = (uint32_t)((uint64_t)a.units * (xcd + 1) / 8);
+    for (uint32_t u = (uint32_t)((uint64_t)a.units * xcd / 8) + (blockIdx.x >> 3); u < u1; u += gridDim.x >> 3) {
+        const uint64_t row0 = ((uint64_t)u * groups + w / a.split) * kOpRows;
+        const uint64_t row = row0 + (lane & (kOpRows - 1));
+        double acc = 0.0;
+        if (row0 < a.ns) {
+            const uint64_t own = row < a.ns ? row : a.ns - 1;  // past the end: the last row again, not stored
+            const P al = a.states[own];
+            P all = al, one = al;
+#pragma unroll
+            for (int o = 1; o < kOpRows; o <<= 1) {
+                all &= (P)__shfl_xor(all, o, 64);
+                one |= (P)__shfl_xor(one, o, 64);
+            }
+            const P same = ~(all ^ one);
+            bool any = false;
+            op_range<P, OpRank<P, E, RK>, kDiagonal>(a, rk, qu, 0, a.n_diag, part, al, all, same, acc, any);
+            // a row no diagonal tuple acts on does not read its own x
+            acc = any ? acc * a.xin[own] : 0.0;
+            op_range<P, OpRank<P, E, RK>, kKeeping>(a, rk, qu, a.n_diag, a.n_keep, part, al, all, same, acc, any);
+            op_range<P, OpRank<P, E, RK>, kLeaving>(a, rk, qu, a.n_keep, a.n_all, part, al, all, same, acc, any);
+            // the four tuple slots of a row
+#pragma unroll
+            for (int o = kOpRows; o < 64; o <<= 1) acc += __shfl_xor(acc, o, 64);
+        }
+        if (a.split == 1) {
+            if (lane < kOpRows && row < a.ns) a.out[row] = acc;
+        } else {
+            if (lane < kOpRows) red[w * kOpRows + lane] = acc;
+            __syncthreads();
+            if (part == 0 && lane < kOpRows && row < a.ns) {
+                double s = acc;
+                for (uint32_t k = 1; k < a.split; ++k) s += red[(w + k) * kOpRows + lane];
+                a.out[row] = s;
+            }
+            __syncthreads();  // red is free again
+        }
+    }
+}
+
+// Sum tables.  When the members under two different high parts are either the
+// same set of low parts or share none (exact particle-number windows, and
+// with them a modular weight, make it so: the high part fixes what the low
+// part has to hold), the position of a low part among its siblings depends on
+// the low part alone, and rank = base[high] + off[low]: two reads, both from
+// LDS for up to 28 orbitals, instead of a walk through a trie or a chunk loop.
+// Neighbouring rows' targets then also read neighbouring entries.  Whether a
+// sector is of that kind is not guessed from its windows but checked here on
+// its list: base[high] is the first position of the high part, and every
+// member's position minus that has to agree for equal low parts.
+constexpr uint32_t kNoEntry = 0xFFFFFFFFu;
+
+template <class P>
+__global__ void __launch_bounds__(kBlock) op_sum_base(const P *__restrict__ st, uint64_t n, int low_bits, uint32_t *base) {
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+        const P hi = st[i] >> low_bits;
+        if (i == 0 || (st[i - 1] >> low_bits) != hi) base[hi] = (uint32_t)i;
+    }
+}
+
+template <class P>
+__global__ void __launch_bounds__(kBlock) op_sum_off(const P *__restrict__ st, uint64_t n, int low_bits,
+                                                     const uint32_t *__restrict__ base, uint32_t *off, uint32_t *bad) {
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t o = (uint32_t)i - base[st[i] >> low_bits];
+        uint32_t *e = off + (st[i] & (P)(((P)1 << low_bits) - 1));
+        uint32_t cur = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (cur == kNoEntry) cur = atomicCAS(e, kNoEntry, o);
+        if (cur != kNoEntry && cur != o) *bad = 1u;
+    }
+}
+
+__global__ void op_fill_kernel(uint32_t *p, uint32_t n, uint32_t v) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = v;
+}
+
+// 16-bit copy (a low part has fewer than 2^14 smaller siblings; low parts that
+// no member has keep all ones).
+__global__ void op_sum_narrow(const uint32_t *__restrict__ off, uint32_t n, uint16_t *__restrict__ o16) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) o16[i] = (uint16_t)off[i];
 }
 
 // ---------------------------------------------------------------- Lanczos
@@ -271,23 +562,102 @@ __global__ void __launch_bounds__(kBlock) op_next_kernel(double *__restrict__ w,
 struct mbr_operator {
     const mbr_sector *sec = nullptr;
     const mbr_ranker *rk = nullptr;
-    int64_t nt = 0;
+    int64_t nt = 0, n_diag = 0, n_keep = 0;  // tuples: diagonal | sector-keeping | the rest
     int32_t M = 0, width_bits = 32;
-    mbr::DevBuf v, m, l, x, s, keep;
+    mbr::DevBuf v, ml, xs;
+    mbr::DevBuf base, off;                   // sum tables (low_bits > 0)
+    int32_t low_bits = 0;
+    uint32_t split = 1, units = 1, grid = 8;
+    size_t lds = 0;
     int device = 0;
 };
 
 namespace {
 
-template <class P, class E, int RK>
-mbr_status launch_op(const mbr_operator *op, OpArgs<P> a, size_t lds, hipStream_t st) {
-    auto kern = op_apply_kernel<P, E, RK>;
-    if (lds > 64 * 1024)
-        MBR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    const unsigned grid = mbr::grid_for(op->sec->n, kBlock, mbr::device_cu_count() * 8);
-    kern<<<grid, kBlock, lds, st>>>(a);
+constexpr size_t kOpLdsMax = 160 * 1024;
+constexpr size_t kOpTables = 100 * 1024;  // sum tables up to this size are staged whole
+
+// Waves that share a row group's tuples: as few as fill the chip (about 16
+// waves per CU), and none that would not get 64 tuples to sieve.  15 orbitals
+// half filled (6,435 rows, 11,026 tuples): 16 waves, 52 us a
+// product; unsplit 329 us.
+uint32_t op_split(uint64_t ns, int64_t nt) {
+    const uint64_t groups = (ns + kOpRows - 1) / kOpRows;
+    const uint64_t want = (uint64_t)mbr::device_cu_count() * 16;
+    uint32_t s = 1;
+    while (s < (uint32_t)kOpWaves && groups * s < want && (int64_t)s * 64 < nt) s *= 2;
+    return s;
+}
+
+// Run f with the kernel instance of the operator's rank path and pattern type.
+template <class P, class F>
+mbr_status with_kernel(const mbr_operator *op, F f) {
+    const mbr_ranker *r = op->rk;
+    if constexpr (sizeof(P) == 4) {
+        if (op->low_bits) {
+            const size_t nb = op->base.bytes, no = op->off.bytes;
+            if (nb + no <= kOpTables) return f(op_apply_kernel<P, uint16_t, kSumLds>, nb + no);
+            return f(op_apply_kernel<P, uint16_t, kSumGlobal>, no);
+        }
+    }
+    if (r->kind == MBR_RANKER_TRIE) return f(op_apply_kernel<P, uint32_t, kTrie>, (size_t)0);
+    const StagTable &tb = r->stag;
+    const size_t lds = ((size_t)tb.nrows << tb.k) * tb.entry_bytes;
+    const bool in_lds = lds <= kLdsTable;
+    switch (tb.entry_bytes) {
+        case 2: return in_lds ? f(op_apply_kernel<P, uint16_t, kStagLds>, lds) : f(op_apply_kernel<P, uint16_t, kStagGlobal>, (size_t)0);
+        case 4: return in_lds ? f(op_apply_kernel<P, uint32_t, kStagLds>, lds) : f(op_apply_kernel<P, uint32_t, kStagGlobal>, (size_t)0);
+        default: return in_lds ? f(op_apply_kernel<P, uint64_t, kStagLds>, lds) : f(op_apply_kernel<P, uint64_t, kStagGlobal>, (size_t)0);
+    }
+}
+
+// Launch shape of the operator's products, fixed when it is created.
+template <class P>
+mbr_status plan_launch(mbr_operator *op) {
+    return with_kernel<P>(op, [&](auto kern, size_t tables) -> mbr_status {
+        op->lds = op_lds_bytes<P>(tables);
+        MBR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOpLdsMax));
+        op->split = op_split(op->sec->n, op->nt);
+        const uint64_t rows = (uint64_t)kOpRows * kOpWaves / op->split;
+        op->units = (uint32_t)((op->sec->n + rows - 1) / rows);
+        int per_cu = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kOpBlock, op->lds) != hipSuccess || per_cu < 1) per_cu = 1;
+        const uint64_t most = (uint64_t)mbr::device_cu_count() * per_cu;
+        op->grid = (uint32_t)std::min<uint64_t>(most, op->units) + 7;
+        op->grid -= op->grid % 8;
+        return MBR_OK;
+    });
+}
+
+// Sum tables of the sector, when it has them; op->low_bits stays 0 otherwise.
+mbr_status op_sum_tables(mbr_operator *op, hipStream_t st) {
+    using namespace mbr;
+    const mbr_sector *sec = op->sec;
+    const int low = std::min((sec->M + 1) / 2, 14), high = sec->M - low;
+    const uint32_t nb = 1u << high, no = 1u << low;
+    DevBuf wide, flag;
+    MBR_TRY(op->base.alloc((size_t)nb * 4));
+    MBR_TRY(op->off.alloc((size_t)no * 2));
+    MBR_TRY(wide.alloc((size_t)no * 4));
+    MBR_TRY(flag.alloc(4));
+    const unsigned grid = grid_for(sec->n, kBlock, device_cu_count() * 8);
+    const uint32_t *states = sec->states.as<uint32_t>();
+    op_fill_kernel<<<(nb + 255) / 256, 256, 0, st>>>(op->base.as<uint32_t>(), nb, kNoEntry);
+    op_fill_kernel<<<(no + 255) / 256, 256, 0, st>>>(wide.as<uint32_t>(), no, kNoEntry);
+    op_fill_kernel<<<1, 64, 0, st>>>(flag.as<uint32_t>(), 1, 0u);
+    op_sum_base<uint32_t><<<grid, kBlock, 0, st>>>(states, sec->n, low, op->base.as<uint32_t>());
+    op_sum_off<uint32_t><<<grid, kBlock, 0, st>>>(states, sec->n, low, op->base.as<uint32_t>(), wide.as<uint32_t>(), flag.as<uint32_t>());
+    op_sum_narrow<<<(no + 255) / 256, 256, 0, st>>>(wide.as<uint32_t>(), no, op->off.as<uint16_t>());
     MBR_HIP(hipGetLastError());
+    uint32_t bad = 1;
+    MBR_HIP(hipMemcpyAsync(&bad, flag.p, 4, hipMemcpyDeviceToHost, st));
+    MBR_HIP(hipStreamSynchronize(st));
+    if (bad) {
+        op->base.release();
+        op->off.release();
+    } else {
+        op->low_bits = low;
+    }
     return MBR_OK;
 }
 
@@ -296,17 +666,24 @@ mbr_status apply_t(const mbr_operator *op, const double *x, double *y, hipStream
     OpArgs<P> a{};
     a.states = op->sec->states.as<P>();
     a.ns = op->sec->n;
-    a.nt = op->nt;
+    a.n_diag = op->n_diag;
+    a.n_keep = op->n_keep;
+    a.n_all = op->nt;
+    a.ml = op->ml.as<Two<P>>();
+    a.xs = op->xs.as<Two<P>>();
     a.v = op->v.as<double>();
-    a.m = op->m.as<P>();
-    a.l = op->l.as<P>();
-    a.x = op->x.as<P>();
-    a.s = op->s.as<P>();
-    a.keep = op->keep.as<uint32_t>();
     a.xin = x;
     a.out = y;
+    a.split = op->split;
+    a.units = op->units;
     const mbr_ranker *r = op->rk;
-    if (r->kind == MBR_RANKER_TRIE) {
+    if (op->low_bits) {
+        a.base = op->base.as<uint32_t>();
+        a.off = op->off.as<uint16_t>();
+        a.low_bits = op->low_bits;
+        a.n_off = 1u << op->low_bits;
+        a.n_base = 1u << (op->M - op->low_bits);
+    } else if (r->kind == MBR_RANKER_TRIE) {
         const TrieLevels &t = *r->trie;
         a.trie.tab = t.table.as<uint32_t>();
         a.trie.states = op->sec->states.p;
@@ -319,23 +696,21 @@ mbr_status apply_t(const mbr_operator *op, const double *x, double *y, hipStream
             a.trie.off[lv] = t.off[lv];
         }
         a.trie.off[t.H] = t.off[t.H];
-        return launch_op<P, uint32_t, kTrie>(op, a, 0, st);
+    } else {
+        const StagTable &tb = r->stag;
+        a.stag.M = tb.M;
+        a.stag.k = tb.k;
+        a.stag.nch = tb.nch;
+        a.stag.N = r->N;
+        for (int c = 0; c < tb.nch && c < 16; ++c) a.stag.rowoff[c] = tb.rowoff[c];
+        a.stag.nentries = (uint64_t)tb.nrows << tb.k;
+        a.stab = tb.table.p;
     }
-    const StagTable &tb = r->stag;
-    a.stag.M = tb.M;
-    a.stag.k = tb.k;
-    a.stag.nch = tb.nch;
-    a.stag.N = r->N;
-    for (int c = 0; c < tb.nch && c < 16; ++c) a.stag.rowoff[c] = tb.rowoff[c];
-    a.stag.nentries = (uint64_t)tb.nrows << tb.k;
-    a.stab = tb.table.p;
-    const size_t lds = a.stag.nentries * tb.entry_bytes;
-    const bool in_lds = lds <= kLdsTable;
-    switch (tb.entry_bytes) {
-        case 2: return in_lds ? launch_op<P, uint16_t, kStagLds>(op, a, lds, st) : launch_op<P, uint16_t, kStagGlobal>(op, a, 0, st);
-        case 4: return in_lds ? launch_op<P, uint32_t, kStagLds>(op, a, lds, st) : launch_op<P, uint32_t, kStagGlobal>(op, a, 0, st);
-        default: return in_lds ? launch_op<P, uint64_t, kStagLds>(op, a, lds, st) : launch_op<P, uint64_t, kStagGlobal>(op, a, 0, st);
-    }
+    return with_kernel<P>(op, [&](auto kern, size_t) -> mbr_status {
+        kern<<<op->grid, kOpBlock, op->lds, st>>>(a);
+        MBR_HIP(hipGetLastError());
+        return MBR_OK;
+    });
 }
 
 }  // namespace
@@ -403,22 +778,11 @@ mbr_status mbr_operator_create(const mbr_sector *sec, const mbr_ranker *rk, cons
     op->M = sec->M;
     op->width_bits = sec->width_bits;
     (void)hipGetDevice(&op->device);
-    const size_t n = (size_t)std::max<int64_t>(n_terms, 1);
-    std::vector<double> v(n, 0.0);
-    std::vector<uint64_t> f[4];
-    for (auto &a : f) a.assign(n, 0);
-    for (int64_t i = 0; i < n_terms; ++i) {
-        v[i] = terms[i].v;
-        f[0][i] = terms[i].m;
-        f[1][i] = terms[i].l;
-        f[2][i] = terms[i].x;
-        f[3][i] = terms[i].s;
-    }
     // A tuple keeps the sector when it moves no particle into or out of any
     // constraint's orbitals and leaves the modular weight unchanged: the
     // target of every member is then a member (bits outside m are untouched,
     // and inside m the row holds l and the target l ^ x).
-    std::vector<uint32_t> keep(n, 0u);
+    std::vector<uint8_t> range(n_terms);
     for (int64_t i = 0; i < n_terms; ++i) {
         const uint64_t lo = terms[i].l, hi = terms[i].l ^ terms[i].x;
         // a caller's list has no constraints to check a tuple against
@@ -430,19 +794,41 @@ mbr_status mbr_operator_create(const mbr_sector *sec, const mbr_ranker *rk, cons
             for (int b = 0; b < sec->M; ++b) dw += (int64_t)(((hi >> b) & 1) - ((lo >> b) & 1)) * sec->weights[b];
             k = k && dw % sec->modulus == 0;
         }
-        keep[i] = k ? 1u : 0u;
+        range[i] = terms[i].x == 0 ? kDiagonal : k ? kKeeping : kLeaving;
+    }
+    // the three ranges, each by the high bits its tuples flip, then as given
+    std::vector<int64_t> order(n_terms);
+    for (int64_t i = 0; i < n_terms; ++i) order[i] = i;
+    const int half = (sec->M + 1) / 2;
+    std::stable_sort(order.begin(), order.end(), [&](int64_t i, int64_t j) {
+        const uint64_t xi = terms[i].x >> half, xj = terms[j].x >> half;
+        return std::tie(range[i], xi) < std::tie(range[j], xj);
+    });
+    op->n_diag = std::count(range.begin(), range.end(), (uint8_t)kDiagonal);
+    op->n_keep = op->n_diag + std::count(range.begin(), range.end(), (uint8_t)kKeeping);
+    const size_t n = (size_t)std::max<int64_t>(n_terms, 1);
+    std::vector<double> v(n, 0.0);
+    std::vector<uint64_t> ml(2 * n, 0), xs(2 * n, 0);
+    for (int64_t i = 0; i < n_terms; ++i) {
+        const mbr_term &t = terms[order[i]];
+        v[i] = t.v;
+        ml[2 * i] = t.m;
+        ml[2 * i + 1] = t.l;
+        xs[2 * i] = t.x;
+        xs[2 * i + 1] = t.s;
     }
     hipStream_t st = as_stream(stream);
-    MBR_TRY(upload(op->keep, keep.data(), n * 4, st));
     MBR_TRY(upload(op->v, v.data(), n * 8, st));
-    DevBuf *dst[4] = {&op->m, &op->l, &op->x, &op->s};
-    for (int k = 0; k < 4; ++k) {
-        if (sec->width_bits == 64) {
-            MBR_TRY(upload(*dst[k], f[k].data(), n * 8, st));
-        } else {
-            std::vector<uint32_t> w(f[k].begin(), f[k].end());
-            MBR_TRY(upload(*dst[k], w.data(), n * 4, st));
-        }
+    if (sec->width_bits == 64) {
+        MBR_TRY(upload(op->ml, ml.data(), 2 * n * 8, st));
+        MBR_TRY(upload(op->xs, xs.data(), 2 * n * 8, st));
+        MBR_TRY(plan_launch<uint64_t>(op.get()));
+    } else {
+        const std::vector<uint32_t> ml32(ml.begin(), ml.end()), xs32(xs.begin(), xs.end());
+        MBR_TRY(upload(op->ml, ml32.data(), 2 * n * 4, st));
+        MBR_TRY(upload(op->xs, xs32.data(), 2 * n * 4, st));
+        MBR_TRY(op_sum_tables(op.get(), st));
+        MBR_TRY(plan_launch<uint32_t>(op.get()));
     }
     *out = op.release();
     return MBR_OK;
