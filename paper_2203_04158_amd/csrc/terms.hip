@@ -178,6 +178,7 @@ __device__ __forceinline__ int popc(P v) {
 // or a value >= ns outside the sector.
 template <class P, class E, int RK>
 struct OpRank {
+    static constexpr bool kFromLds = RK == kSumLds || RK == kStagLds;
     const OpArgs<P> &a;
     const E *tab;          // staggered table
     const uint32_t *base;  // sum tables
@@ -249,13 +250,14 @@ __device__ __forceinline__ void op_range(const OpArgs<P> &a, const R &rk, OpQueu
                 v[u] = p->v[i + u * kOpSlots];
                 ok[u] = (al & ml.a) == ml.b;
             }
-            // ranks, then gathers, then sums: each in flight for all the tuples of the step.  A tuple that does not
-            // act on this row still gets a rank (any pattern is safe to look up) but reads no x.
+            // ranks, then gathers, then sums: each in flight for all the tuples of the step
             if constexpr (RANGE != kDiagonal) {
 #pragma unroll
                 for (int u = 0; u < kOpUnroll; ++u) {
                     if constexpr (RANGE == kKeeping) {
-                        r[u] = rk.at(ok[u] ? al ^ xs[u].a : al);
+                        // from LDS the rank of every pattern is looked up, whether its tuple acts or not
+                        r[u] = 0;
+                        if (R::kFromLds || ok[u]) r[u] = rk.at(ok[u] ? al ^ xs[u].a : al);
                     } else {
                         r[u] = ok[u] ? rk.find(al ^ xs[u].a) : ~0ull;
                         ok[u] = r[u] < a.ns;
@@ -416,6 +418,176 @@ __global__ void __launch_bounds__(kOpBlock) op_apply_kernel(OpArgs<P> a) {
     }
 }
 
+// The product over rows that share their high part, for operators whose sector
+// has sum tables (below) and whose off-diagonal tuples all keep it.  A tuple
+// is a product of a factor on the high orbitals and one on the low ones, and
+// in a wave of rows with one high part everything about the high factor is the
+// same for all lanes: whether it acts, its sign, and the first row of the
+// block it leads to.  The tuples are ordered by their low factor.  The sieve
+// (a tuple per lane, as above) leaves in the queue, per surviving tuple, its
+// signed prefactor and its target block; a run of equal low factors is then
+// evaluated with one test, one table read and one sign per row, and a gather
+// and a fused multiply-add per tuple:
+//   y_row += sign_low(row) * sum_t v_t x[block_t + off[low ^ x_low]].
+// The 14-site ring has 196 low factors for 2,772 tuples; the step above spends
+// 19 vector instructions per tuple and 64 row slots, this one 3.
+struct OpLowQueue {
+    double v[kOpQueue];
+    uint2 low[kOpQueue];       // low factor: m | l << 16, x | s << 16
+    uint32_t block[kOpQueue];  // first row of the target block
+};
+
+struct OpTile {
+    uint32_t row0, n;  // up to 64 rows of one high part
+};
+
+struct OpLowArgs {
+    OpArgs<uint32_t> op;
+    const OpTile *tiles;
+    uint32_t n_tiles;
+};
+
+template <int RANGE, bool SPLIT>
+__device__ __forceinline__ void op_low_range(const OpArgs<uint32_t> &a, const uint16_t *off, OpLowQueue &qu, int64_t begin,
+                                             int64_t end, uint32_t part, uint32_t al, uint32_t ref, uint32_t same, double &acc, bool &any) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t lmask = a.n_off - 1, low = al & lmask;
+    uint32_t cnt = 0;
+    auto eval = [&](uint32_t n) {
+        const uint2 key = qu.low[lane], prev = qu.low[lane ? lane - 1 : 0];
+        uint64_t starts = __ballot((uint32_t)lane < n && (lane == 0 || key.x != prev.x || key.y != prev.y));
+        while (starts) {
+            const uint32_t j = (uint32_t)__builtin_ctzll(starts);
+            starts &= starts - 1;
+            const uint32_t k = starts ? (uint32_t)__builtin_ctzll(starts) : n;
+            const uint2 f = qu.low[j];
+            if ((low & (f.x & 0xFFFFu)) == f.x >> 16) {
+                double sum = 0.0;
+                if constexpr (RANGE == kDiagonal) {
+                    for (uint32_t e = j; e < k; ++e) sum += qu.v[e];
+                    any = true;
+                } else {
+                    const double *px = a.xin + off[low ^ (f.y & 0xFFFFu)];
+                    uint32_t e = j;
+                    for (; e + 4 <= k; e += 4) {
+                        const double x0 = px[qu.block[e]], x1 = px[qu.block[e + 1]], x2 = px[qu.block[e + 2]], x3 = px[qu.block[e + 3]];
+                        sum = __builtin_fma(qu.v[e], x0, sum);
+                        sum = __builtin_fma(qu.v[e + 1], x1, sum);
+                        sum = __builtin_fma(qu.v[e + 2], x2, sum);
+                        sum = __builtin_fma(qu.v[e + 3], x3, sum);
+                    }
+                    if (e + 2 <= k) {
+                        const double x0 = px[qu.block[e]], x1 = px[qu.block[e + 1]];
+                        sum = __builtin_fma(qu.v[e], x0, sum);
+                        sum = __builtin_fma(qu.v[e + 1], x1, sum);
+                        e += 2;
+                    }
+                    if (e < k) sum = __builtin_fma(qu.v[e], px[qu.block[e]], sum);
+                }
+                const uint64_t flip = (uint64_t)(__popc(low & (f.y >> 16)) & 1) << 63;
+                acc += __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, sum) ^ flip);
+            }
+        }
+    };
+    const int64_t step = SPLIT ? (int64_t)64 * a.split : 64;
+    Two<uint32_t> nx{};
+    int64_t t = begin + (int64_t)part * 64 + lane;
+    const int64_t tend = end + lane;
+    if (t < end) nx = a.ml[t];
+    for (; t < tend; t += step) {
+        const Two<uint32_t> ml = nx;
+        const bool in = t < end;
+        if (t + step < end) nx = a.ml[t + step];
+        const bool live = in && (((ref ^ ml.b) & ml.a & same) == 0);
+        const uint64_t b = __ballot(live);
+        if (b == 0) continue;
+        if (live) {
+            const uint32_t q = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0));
+            const Two<uint32_t> xs = a.xs[t];
+            const uint64_t flip = (uint64_t)(__popc(ref & xs.b & ~lmask) & 1) << 63;
+            qu.v[q] = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, a.v[t]) ^ flip);
+            qu.low[q] = make_uint2((ml.a & lmask) | (ml.b & lmask) << 16, (xs.a & lmask) | (xs.b & lmask) << 16);
+            if constexpr (RANGE != kDiagonal) qu.block[q] = a.base[(ref ^ xs.a) >> a.low_bits];
+        }
+        cnt += (uint32_t)__popcll(b);
+        if (cnt >= 64) {
+            wave_lds_fence();
+            eval(64);
+            cnt -= 64;
+            double v2 = 0.0;
+            uint2 l2{};
+            uint32_t b2 = 0;
+            if (lane < (int)cnt) {
+                v2 = qu.v[64 + lane];
+                l2 = qu.low[64 + lane];
+                if constexpr (RANGE != kDiagonal) b2 = qu.block[64 + lane];
+            }
+            wave_lds_fence();
+            if (lane < (int)cnt) {
+                qu.v[lane] = v2;
+                qu.low[lane] = l2;
+                if constexpr (RANGE != kDiagonal) qu.block[lane] = b2;
+            }
+            wave_lds_fence();
+        }
+    }
+    if (cnt) {
+        wave_lds_fence();
+        eval(cnt);
+        wave_lds_fence();
+    }
+}
+
+template <bool SPLIT>
+__global__ void __launch_bounds__(kOpBlock) op_low_kernel(OpLowArgs args) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const OpArgs<uint32_t> &a = args.op;
+    uint16_t *off = reinterpret_cast<uint16_t *>(lds_raw);
+    const size_t tb = ((size_t)a.n_off * 2 + 15) / 16 * 16;
+    stage_to_lds(off, a.off, (uint64_t)a.n_off * 2);
+    __syncthreads();
+    const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    OpLowQueue *qu = reinterpret_cast<OpLowQueue *>(lds_raw + tb) + w;
+    const uint32_t groups = SPLIT ? kOpWaves / a.split : kOpWaves, part = SPLIT ? w % a.split : 0;
+    const uint32_t xcd = blockIdx.x & 7;
+    const uint32_t u1 = (uint32_t)((uint64_t)a.units * (xcd + 1) / 8);
+    for (uint32_t u = (uint32_t)((uint64_t)a.units * xcd / 8) + (blockIdx.x >> 3); u < u1; u += gridDim.x >> 3) {
+        const uint32_t ti = u * groups + (SPLIT ? w / a.split : w);
+        const bool some = ti < args.n_tiles;
+        if (!SPLIT && !some) continue;
+        const OpTile tl = some ? args.tiles[ti] : OpTile{0, 0};
+        double acc = 0.0;
+        if (some) {
+            const uint32_t own = tl.row0 + (lane < tl.n ? lane : tl.n - 1);
+            const uint32_t al = a.states[own];
+            uint32_t all = al, one = al;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                all &= (uint32_t)__shfl_xor((int)all, o, 64);
+                one |= (uint32_t)__shfl_xor((int)one, o, 64);
+            }
+            const uint32_t ref = (uint32_t)__builtin_amdgcn_readfirstlane((int)all);
+            const uint32_t same = (uint32_t)__builtin_amdgcn_readfirstlane((int)~(all ^ one));
+            bool any = false;
+            op_low_range<kDiagonal, SPLIT>(a, off, *qu, 0, a.n_diag, part, al, ref, same, acc, any);
+            acc = any ? acc * a.xin[own] : 0.0;
+            op_low_range<kKeeping, SPLIT>(a, off, *qu, a.n_diag, a.n_keep, part, al, ref, same, acc, any);
+        }
+        if constexpr (!SPLIT) {
+            if (lane < tl.n) a.out[tl.row0 + lane] = acc;
+        } else {
+            qu->v[lane] = acc;  // the queue is empty here
+            __syncthreads();
+            if (part == 0 && lane < tl.n) {
+                double s = acc;
+                for (uint32_t k = 1; k < a.split; ++k) s += qu[k].v[lane];
+                a.out[tl.row0 + lane] = s;
+            }
+            __syncthreads();  // before the queues fill again
+        }
+    }
+}
+
 // Sum tables.  When the members under two different high parts are either the
 // same set of low parts or share none (exact particle-number windows, and
 // with them a modular weight, make it so: the high part fixes what the low
@@ -567,6 +739,8 @@ struct mbr_operator {
     mbr::DevBuf v, ml, xs;
     mbr::DevBuf base, off;                   // sum tables (low_bits > 0)
     int32_t low_bits = 0;
+    mbr::DevBuf tiles;                       // op_low_kernel: its row tiles (n_tiles > 0)
+    uint32_t n_tiles = 0;
     uint32_t split = 1, units = 1, grid = 8;
     size_t lds = 0;
     int device = 0;
@@ -577,13 +751,14 @@ namespace {
 constexpr size_t kOpLdsMax = 160 * 1024;
 constexpr size_t kOpTables = 100 * 1024;  // sum tables up to this size are staged whole
 
-// Waves that share a row group's tuples: as few as fill the chip (about 16
-// waves per CU), and none that would not get 64 tuples to sieve.  15 orbitals
-// half filled (6,435 rows, 11,026 tuples): 16 waves, 52 us a
-// product; unsplit 329 us.
-uint32_t op_split(uint64_t ns, int64_t nt) {
-    const uint64_t groups = (ns + kOpRows - 1) / kOpRows;
-    const uint64_t want = (uint64_t)mbr::device_cu_count() * 16;
+// Waves that share the tuples of one of `groups` row groups: as few as put
+// `per_cu` waves on every CU, and none that would not get 64 tuples to sieve.
+// op_apply_kernel is content with 16 (15 orbitals half filled, 6,435 rows and
+// 11,250 tuples: 16 waves share a group, 52 us a product; unsplit 329 us).
+// op_low_kernel's waves differ more in length and want 24 (13-site ring, 226,512
+// rows: 156 us with two waves a tile, 184 with one).
+uint32_t op_split(uint64_t groups, int64_t nt, uint32_t per_cu) {
+    const uint64_t want = (uint64_t)mbr::device_cu_count() * per_cu;
     uint32_t s = 1;
     while (s < (uint32_t)kOpWaves && groups * s < want && (int64_t)s * 64 < nt) s *= 2;
     return s;
@@ -617,7 +792,7 @@ mbr_status plan_launch(mbr_operator *op) {
     return with_kernel<P>(op, [&](auto kern, size_t tables) -> mbr_status {
         op->lds = op_lds_bytes<P>(tables);
         MBR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOpLdsMax));
-        op->split = op_split(op->sec->n, op->nt);
+        op->split = op_split((op->sec->n + kOpRows - 1) / kOpRows, op->nt, 16);
         const uint64_t rows = (uint64_t)kOpRows * kOpWaves / op->split;
         op->units = (uint32_t)((op->sec->n + rows - 1) / rows);
         int per_cu = 1;
@@ -629,11 +804,12 @@ mbr_status plan_launch(mbr_operator *op) {
     });
 }
 
-// Sum tables of the sector, when it has them; op->low_bits stays 0 otherwise.
-mbr_status op_sum_tables(mbr_operator *op, hipStream_t st) {
+// Sum tables of the sector split at `low` bits, when it has them;
+// op->low_bits stays 0 otherwise.
+mbr_status op_sum_tables(mbr_operator *op, int low, hipStream_t st) {
     using namespace mbr;
     const mbr_sector *sec = op->sec;
-    const int low = std::min((sec->M + 1) / 2, 14), high = sec->M - low;
+    const int high = sec->M - low;
     const uint32_t nb = 1u << high, no = 1u << low;
     DevBuf wide, flag;
     MBR_TRY(op->base.alloc((size_t)nb * 4));
@@ -658,6 +834,48 @@ mbr_status op_sum_tables(mbr_operator *op, hipStream_t st) {
     } else {
         op->low_bits = low;
     }
+    return MBR_OK;
+}
+
+// Tiles and launch shape of op_low_kernel: the rows of every high part in
+// pieces of 64.  op->n_tiles stays 0 where op_apply_kernel is the faster one:
+// where the work is too small to repay the longer chain of a wave (fewer than
+// 2^14 rows or 2^24 pairs of row and tuple), or where the high parts leave
+// more than half of the lanes without a row.  us per product, op_apply / op_low:
+//   ring,    10 sites,   6,352 rows,  1,020 tuples: 10.7 / 9.0
+//   general, 16 orbitals, 12,870 rows, 14,656 tuples: 104 / 122
+//   ring,    11 sites,  19,404 rows,  1,353 tuples: 24.0 / 21.0
+//   hopping, 10 sites,  63,504 rows,     50 tuples:  8.9 / 11.9
+//   general, 18 orbitals, 48,620 rows, 23,733 tuples: 594 / 337
+//   ring,    12 sites,  71,188 rows,  1,752 tuples: 83.6 / 50.6
+//   ring,    14 sites, 841,332 rows,  2,772 tuples:  600 / 407
+mbr_status plan_low(mbr_operator *op, hipStream_t st) {
+    using namespace mbr;
+    if (op->sec->n < (1u << 14) || op->sec->n * (uint64_t)op->nt < (1u << 24)) return MBR_OK;
+    std::vector<uint32_t> base(op->base.bytes / 4);
+    MBR_HIP(hipMemcpyAsync(base.data(), op->base.p, op->base.bytes, hipMemcpyDeviceToHost, st));
+    MBR_HIP(hipStreamSynchronize(st));
+    std::vector<OpTile> tiles;
+    uint32_t row = 0;
+    auto until = [&](uint32_t end) {
+        for (; row < end; row += tiles.back().n) tiles.push_back(OpTile{row, std::min(64u, end - row)});
+    };
+    for (uint32_t b : base)
+        if (b != kNoEntry) until(b);  // a block ends where the next one starts
+    until((uint32_t)op->sec->n);
+    if (tiles.size() * 32 > op->sec->n) return MBR_OK;
+    MBR_TRY(upload(op->tiles, tiles.data(), tiles.size() * sizeof(OpTile), st));
+    op->n_tiles = (uint32_t)tiles.size();
+    op->split = op_split(op->n_tiles, op->nt, 24);
+    const uint32_t groups = kOpWaves / op->split;
+    op->units = (op->n_tiles + groups - 1) / groups;
+    op->lds = (((size_t)2 << op->low_bits) + 15) / 16 * 16 + kOpWaves * sizeof(OpLowQueue);
+    const auto kern = op->split > 1 ? op_low_kernel<true> : op_low_kernel<false>;
+    MBR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOpLdsMax));
+    int per_cu = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kOpBlock, op->lds) != hipSuccess || per_cu < 1) per_cu = 1;
+    op->grid = (uint32_t)std::min<uint64_t>((uint64_t)device_cu_count() * per_cu, op->units) + 7;
+    op->grid -= op->grid % 8;
     return MBR_OK;
 }
 
@@ -705,6 +923,14 @@ mbr_status apply_t(const mbr_operator *op, const double *x, double *y, hipStream
         for (int c = 0; c < tb.nch && c < 16; ++c) a.stag.rowoff[c] = tb.rowoff[c];
         a.stag.nentries = (uint64_t)tb.nrows << tb.k;
         a.stab = tb.table.p;
+    }
+    if constexpr (sizeof(P) == 4) {
+        if (op->n_tiles) {
+            const auto kern = op->split > 1 ? op_low_kernel<true> : op_low_kernel<false>;
+            kern<<<op->grid, kOpBlock, op->lds, st>>>(OpLowArgs{a, op->tiles.as<OpTile>(), op->n_tiles});
+            MBR_HIP(hipGetLastError());
+            return MBR_OK;
+        }
     }
     return with_kernel<P>(op, [&](auto kern, size_t) -> mbr_status {
         kern<<<op->grid, kOpBlock, op->lds, st>>>(a);
@@ -796,16 +1022,25 @@ mbr_status mbr_operator_create(const mbr_sector *sec, const mbr_ranker *rk, cons
         }
         range[i] = terms[i].x == 0 ? kDiagonal : k ? kKeeping : kLeaving;
     }
-    // the three ranges, each by the high bits its tuples flip, then as given
+    op->n_diag = std::count(range.begin(), range.end(), (uint8_t)kDiagonal);
+    op->n_keep = op->n_diag + std::count(range.begin(), range.end(), (uint8_t)kKeeping);
+    hipStream_t st = as_stream(stream);
+    if (sec->width_bits == 32) {
+        const int low = std::min((sec->M + 1) / 2, 14);
+        MBR_TRY(op_sum_tables(op.get(), low, st));
+        if (op->low_bits && op->n_keep == n_terms) MBR_TRY(plan_low(op.get(), st));
+    }
+    // the three ranges, each by low factor (op_low_kernel) or by the high bits its tuples flip, then as given
     std::vector<int64_t> order(n_terms);
     for (int64_t i = 0; i < n_terms; ++i) order[i] = i;
     const int half = (sec->M + 1) / 2;
+    const uint64_t lm = op->n_tiles ? (1ull << op->low_bits) - 1 : 0;
     std::stable_sort(order.begin(), order.end(), [&](int64_t i, int64_t j) {
-        const uint64_t xi = terms[i].x >> half, xj = terms[j].x >> half;
-        return std::tie(range[i], xi) < std::tie(range[j], xj);
+        const mbr_term &p = terms[i], &q = terms[j];
+        const uint64_t fp[5] = {p.m & lm, p.l & lm, p.x & lm, p.s & lm, p.x >> half};
+        const uint64_t fq[5] = {q.m & lm, q.l & lm, q.x & lm, q.s & lm, q.x >> half};
+        return range[i] != range[j] ? range[i] < range[j] : std::lexicographical_compare(fp, fp + 5, fq, fq + 5);
     });
-    op->n_diag = std::count(range.begin(), range.end(), (uint8_t)kDiagonal);
-    op->n_keep = op->n_diag + std::count(range.begin(), range.end(), (uint8_t)kKeeping);
     const size_t n = (size_t)std::max<int64_t>(n_terms, 1);
     std::vector<double> v(n, 0.0);
     std::vector<uint64_t> ml(2 * n, 0), xs(2 * n, 0);
@@ -817,7 +1052,6 @@ mbr_status mbr_operator_create(const mbr_sector *sec, const mbr_ranker *rk, cons
         xs[2 * i] = t.x;
         xs[2 * i + 1] = t.s;
     }
-    hipStream_t st = as_stream(stream);
     MBR_TRY(upload(op->v, v.data(), n * 8, st));
     if (sec->width_bits == 64) {
         MBR_TRY(upload(op->ml, ml.data(), 2 * n * 8, st));
@@ -827,8 +1061,7 @@ mbr_status mbr_operator_create(const mbr_sector *sec, const mbr_ranker *rk, cons
         const std::vector<uint32_t> ml32(ml.begin(), ml.end()), xs32(xs.begin(), xs.end());
         MBR_TRY(upload(op->ml, ml32.data(), 2 * n * 4, st));
         MBR_TRY(upload(op->xs, xs32.data(), 2 * n * 4, st));
-        MBR_TRY(op_sum_tables(op.get(), st));
-        MBR_TRY(plan_launch<uint32_t>(op.get()));
+        if (!op->n_tiles) MBR_TRY(plan_launch<uint32_t>(op.get()));
     }
     *out = op.release();
     return MBR_OK;
