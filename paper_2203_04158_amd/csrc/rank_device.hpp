@@ -55,6 +55,14 @@ __device__ __forceinline__ void stage_to_lds(void *lds, const void *__restrict__
     for (uint64_t k = (n16 << 2) + threadIdx.x; k < (bytes >> 2); k += blockDim.x) d4[k] = s4[k];
 }
 
+// Between writes and reads of LDS that only one wave uses: the hardware keeps a
+// wave's LDS accesses in order, the fences keep the compiler's.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A trie in the level-major layout of trie.hip, read from global memory.
 struct TrieWalk {
     const uint32_t *tab;

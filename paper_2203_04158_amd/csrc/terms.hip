@@ -216,14 +216,6 @@ struct OpQueue {
     double v[kOpQueue];
 };
 
-// The queue is written and read by one wave; the hardware keeps a wave's LDS
-// accesses in order, the fences keep the compiler's.
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 enum TupleRange { kDiagonal = 0, kKeeping = 1, kLeaving = 2 };
 
 // One range of tuples on the wave's rows: sieve, queue, evaluate.  `al` is the

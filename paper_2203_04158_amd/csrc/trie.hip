@@ -19,7 +19,6 @@
 // LDS and are staged there, the middle levels stay in L2/MALL and only the
 // leaf level and the membership check are HBM gathers.
 #include <algorithm>
-#include <cstring>
 #include <memory>
 
 #include "rank_device.hpp"
@@ -103,112 +102,303 @@ __global__ void __launch_bounds__(kBlock) trie_rank_kernel(const P *__restrict__
     }
 }
 
-// LSD radix sort of (key, index) pairs by key.
-template <class K>
-void radix_sort_pairs(std::vector<K> &key, std::vector<uint32_t> &idx, int key_bits) {
-    const size_t n = key.size();
-    std::vector<K> k2(n);
-    std::vector<uint32_t> i2(n);
-    const int D = 11;
-    for (int sh = 0; sh < key_bits; sh += D) {
-        std::vector<size_t> cnt((1u << D) + 1, 0);
-        for (size_t i = 0; i < n; ++i) ++cnt[((key[i] >> sh) & ((1u << D) - 1)) + 1];
-        for (size_t d = 0; d < (1u << D); ++d) cnt[d + 1] += cnt[d];
-        for (size_t i = 0; i < n; ++i) {
-            size_t p = cnt[(key[i] >> sh) & ((1u << D) - 1)]++;
-            k2[p] = key[i];
-            i2[p] = idx[i];
+// ------------------------------------------------------------------ building
+// The trie is built on the device from the sector's list.  Its nodes follow the
+// order of the chunk-reversed patterns (chunk 0 first): a stable radix sort by
+// the chunks, last to first, starting from the list, which is already in
+// order of its last chunk.  In that order the members under a node are
+// consecutive at every level, a node starts where the low bits up to its level
+// differ from the member before, and its first entry follows from a running
+// sum over the members (node_share).  tl_fill_kernel then writes every entry of
+// every level once.
+//
+// Bound by launches, allocations and the sort's scattered writes (841,332
+// states, k = 8: three passes of 26 us, then 34 us).  On the host the same work
+// (a sort and two passes per level) and the copies both ways took most of a
+// sector change: list, trie and a million ranks 12.8 -> 0.68 ms.
+constexpr unsigned kSortBlock = 256, kSortItems = 16;       // a wave sorts 1024 consecutive members
+constexpr uint32_t kSortTile = kSortBlock * kSortItems;
+constexpr int kDigits = 256;
+constexpr unsigned kLevelBlock = 256, kLevelItems = 8;
+constexpr uint32_t kLevelTile = kLevelBlock * kLevelItems;
+constexpr int kMaxH = 16;
+
+// Members of tile blockIdx.x by digit: counts[digit * tiles + tile].
+template <class P>
+__global__ void __launch_bounds__(kSortBlock) tl_count_kernel(const P *__restrict__ key, uint64_t n, int shift, uint32_t mask,
+                                                              uint32_t *__restrict__ counts) {
+    __shared__ uint32_t c[kDigits];
+    for (int d = threadIdx.x; d < kDigits; d += kSortBlock) c[d] = 0;
+    __syncthreads();
+    const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
+    for (unsigned k = 0; k < kSortItems; ++k) {
+        const uint64_t i = base + k * kSortBlock + threadIdx.x;
+        if (i < n) atomicAdd(&c[(uint32_t)(key[i] >> shift) & mask], 1u);
+    }
+    __syncthreads();
+    for (int d = threadIdx.x; d < kDigits; d += kSortBlock) counts[(uint64_t)d * gridDim.x + blockIdx.x] = c[d];
+}
+
+// Exclusive sum of v over the workgroup (B lanes); *all receives the total.
+template <class V, unsigned B>
+__device__ __forceinline__ V block_before(V v, V *red, V *all) {
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    V s = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const V u = __shfl_up(s, o, 64);
+        if (lane >= (uint32_t)o) s += u;
+    }
+    __syncthreads();  // red's previous readers are done
+    if (lane == 63) red[w] = s;
+    __syncthreads();
+    V before = 0, total = 0;
+    for (uint32_t k = 0; k < B / 64; ++k) {
+        if (k < w) before += red[k];
+        total += red[k];
+    }
+    *all = total;
+    return before + s - v;
+}
+
+// Row blockIdx.x of v (n values) to exclusive sums in place, its total to
+// totals[row].
+template <class V>
+__global__ void __launch_bounds__(1024) tl_scan_kernel(V *v, uint64_t n, V *totals) {
+    __shared__ V red[16];
+    V *row = v + (uint64_t)blockIdx.x * n;
+    V run = 0;
+    for (uint64_t i0 = 0; i0 < n; i0 += 1024) {
+        const uint64_t i = i0 + threadIdx.x;
+        const V x = i < n ? row[i] : (V)0;
+        V all;
+        const V e = block_before<V, 1024>(x, red, &all);
+        if (i < n) row[i] = run + e;
+        run += all;
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = run;
+}
+
+// One stable pass: member i of a tile goes behind all members of smaller
+// digits, those of its digit in earlier tiles, and those before it in its own.
+// idx = nullptr: the members still stand at their positions in the list.
+template <class P>
+__global__ void __launch_bounds__(kSortBlock) tl_scatter_kernel(const P *__restrict__ key, const uint32_t *__restrict__ idx,
+                                                                uint64_t n, int shift, uint32_t mask,
+                                                                const uint32_t *__restrict__ counts, const uint32_t *__restrict__ totals,
+                                                                P *__restrict__ key_out, uint32_t *__restrict__ idx_out) {
+    static_assert(kSortBlock == kDigits, "a lane per digit");
+    __shared__ uint32_t at[kSortBlock / 64][kDigits];  // per wave and digit: count, then next position
+    __shared__ uint32_t red[kSortBlock / 64];
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (uint32_t k = 0; k < kSortBlock / 64; ++k) at[k][threadIdx.x] = 0;
+    __syncthreads();
+    const uint64_t base = (uint64_t)blockIdx.x * kSortTile + w * (kSortTile / (kSortBlock / 64)) + lane;
+    P x[kSortItems];
+#pragma unroll
+    for (unsigned k = 0; k < kSortItems; ++k) {
+        const uint64_t i = base + k * 64;
+        x[k] = i < n ? key[i] : (P)0;
+        if (i < n) atomicAdd(&at[w][(uint32_t)(x[k] >> shift) & mask], 1u);
+    }
+    __syncthreads();
+    {
+        const uint32_t d = threadIdx.x;
+        uint32_t all;
+        uint32_t pos = block_before<uint32_t, kSortBlock>(totals[d], red, &all) + counts[(uint64_t)d * gridDim.x + blockIdx.x];
+        for (uint32_t k = 0; k < kSortBlock / 64; ++k) {
+            const uint32_t c = at[k][d];
+            at[k][d] = pos;
+            pos += c;
         }
-        key.swap(k2);
-        idx.swap(i2);
+    }
+    __syncthreads();
+    for (unsigned k = 0; k < kSortItems; ++k) {
+        const uint64_t i = base + k * 64;
+        const bool in = i < n;
+        const uint32_t d = (uint32_t)(x[k] >> shift) & mask;
+        uint64_t peers = __ballot(in);  // lanes of this step with the same digit
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const uint64_t m = __ballot((d >> b) & 1);
+            peers &= ((d >> b) & 1) ? m : ~m;
+        }
+        const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0));
+        const uint32_t pos = at[w][d] + before;
+        wave_lds_fence();
+        if (in && before == 0) at[w][d] += (uint32_t)__popcll(peers);
+        wave_lds_fence();
+        if (in) {
+            key_out[pos] = x[k];
+            idx_out[pos] = idx ? idx[i] : (uint32_t)i;
+        }
+    }
+}
+
+struct LevelArgs {
+    int32_t H;
+    int32_t shift[kMaxH + 1];  // shift[H] = M
+    int32_t w[kMaxH];
+    uint64_t off[kMaxH];
+};
+
+template <class P>
+__device__ __forceinline__ P low_bits(int n) {
+    return n >= (int)(8 * sizeof(P)) ? (P)~(P)0 : (P)(((P)1 << n) - 1);
+}
+
+// What a member adds to the running sum of level l: the slots of its node (last
+// chunk - first chunk + 1), the first chunk taken off at the node's first
+// member, the rest added at its last.  `dp`, `dn`: bits that differ from the
+// member before and after (all ones at the ends).
+template <class P>
+__device__ __forceinline__ int64_t node_share(P a, P dp, P dn, int l, const LevelArgs &v) {
+    const P lm = low_bits<P>(v.shift[l]);
+    const int64_t c = (int64_t)((a >> v.shift[l]) & low_bits<P>(v.w[l]));
+    return ((dn & lm) ? c + 1 : 0) - ((dp & lm) ? c : 0);
+}
+
+// A lane's consecutive members and their differences.
+template <class P>
+__device__ __forceinline__ void load_members(const P *__restrict__ key, uint64_t n, uint64_t i0, P (&a)[kLevelItems], P (&dp)[kLevelItems],
+                                             P (&dn)[kLevelItems]) {
+    P e[kLevelItems + 2];
+#pragma unroll
+    for (unsigned k = 0; k < kLevelItems + 2; ++k) {
+        const uint64_t i = i0 + k;  // member i - 1
+        e[k] = i > 0 && i <= n ? key[i - 1] : (P)0;
+    }
+#pragma unroll
+    for (unsigned k = 0; k < kLevelItems; ++k) {
+        const uint64_t i = i0 + k;
+        a[k] = e[k + 1];
+        dp[k] = i == 0 ? (P)~(P)0 : (P)(e[k] ^ e[k + 1]);
+        dn[k] = i + 1 >= n ? (P)~(P)0 : (P)(e[k + 2] ^ e[k + 1]);
+    }
+}
+
+// Sums of node_share over tile blockIdx.x, levels 1 .. H-1: sums[(l-1) * tiles + tile].
+template <class P>
+__global__ void __launch_bounds__(kLevelBlock) tl_sums_kernel(const P *__restrict__ key, uint64_t n, LevelArgs v, int64_t *__restrict__ sums) {
+    __shared__ int64_t red[kLevelBlock / 64];
+    const uint64_t i0 = (uint64_t)blockIdx.x * kLevelTile + threadIdx.x * kLevelItems;
+    P a[kLevelItems], dp[kLevelItems], dn[kLevelItems];
+    load_members<P>(key, n, i0, a, dp, dn);
+    for (int l = 1; l < v.H; ++l) {
+        int64_t s = 0, all;
+#pragma unroll
+        for (unsigned k = 0; k < kLevelItems; ++k)
+            if (i0 + k < n) s += node_share<P>(a[k], dp[k], dn[k], l, v);
+        (void)block_before<int64_t, kLevelBlock>(s, red, &all);
+        if (threadIdx.x == 0) sums[(uint64_t)(l - 1) * gridDim.x + blockIdx.x] = all;
+    }
+}
+
+// Every entry of every level.  A node's index shifted back by its first chunk
+// is 2^w - 1 (the front padding) plus the slots of the nodes before it minus that
+// chunk, which is what the running sum stands at behind the node's first
+// member.  The first member of each (node, chunk) pair writes the pair's entry:
+// the child's shifted index, or at the last level its own position.
+template <class P>
+__global__ void __launch_bounds__(kLevelBlock) tl_fill_kernel(const P *__restrict__ key, const uint32_t *__restrict__ idx, uint64_t n,
+                                                              LevelArgs v, const int64_t *__restrict__ sums, uint32_t *__restrict__ tab) {
+    __shared__ int64_t red[kLevelBlock / 64];
+    const uint64_t i0 = (uint64_t)blockIdx.x * kLevelTile + threadIdx.x * kLevelItems;
+    P a[kLevelItems], dp[kLevelItems], dn[kLevelItems];
+    load_members<P>(key, n, i0, a, dp, dn);
+    uint32_t node[kLevelItems], child[kLevelItems];
+#pragma unroll
+    for (unsigned k = 0; k < kLevelItems; ++k) node[k] = 0;  // the root
+    for (int l = 0; l < v.H; ++l) {
+        const bool last = l + 1 == v.H;
+        if (!last) {
+            int64_t s = 0, all;
+#pragma unroll
+            for (unsigned k = 0; k < kLevelItems; ++k)
+                if (i0 + k < n) s += node_share<P>(a[k], dp[k], dn[k], l + 1, v);
+            int64_t run = block_before<int64_t, kLevelBlock>(s, red, &all) + sums[(uint64_t)l * gridDim.x + blockIdx.x];
+            const P lm = low_bits<P>(v.shift[l + 1]);
+            const int64_t front = ((int64_t)1 << v.w[l + 1]) - 1;
+#pragma unroll
+            for (unsigned k = 0; k < kLevelItems; ++k) {
+                const int64_t c = (int64_t)((a[k] >> v.shift[l + 1]) & low_bits<P>(v.w[l + 1]));
+                child[k] = (uint32_t)(front + run - ((dp[k] & lm) ? c : 0));
+                if (i0 + k < n) run += node_share<P>(a[k], dp[k], dn[k], l + 1, v);
+            }
+        }
+        const P pair = low_bits<P>(v.shift[l + 1]);
+#pragma unroll
+        for (unsigned k = 0; k < kLevelItems; ++k) {
+            const uint64_t i = i0 + k;
+            if (i < n && (dp[k] & pair)) {
+                const uint32_t c = (uint32_t)((a[k] >> v.shift[l]) & low_bits<P>(v.w[l]));
+                tab[v.off[l] + node[k] + c] = last ? (idx ? idx[i] : (uint32_t)i) : child[k];
+            }
+            node[k] = child[k];
+        }
     }
 }
 
 template <class P>
-mbr_status build_levels(TrieLevels &t, const std::vector<P> &states) {
+mbr_status build_levels(TrieLevels &t, const mbr_sector *sec, hipStream_t s) {
+    using namespace mbr;
     const int M = t.M, H = t.H;
-    const size_t n = states.size();
-    // chunk-reversed key: chunk 0 becomes the most significant field, so the
-    // key order groups patterns by their low-bit prefixes at every level
-    std::vector<P> key(n);
-    std::vector<uint32_t> idx(n);
-    for (size_t i = 0; i < n; ++i) {
-        P a = states[i], k = 0;
-        int top = M;
-        for (int l = 0; l < H; ++l) {
-            top -= t.w[l];
-            P c = (a >> t.shift[l]) & (P)((1ull << t.w[l]) - 1);
-            k |= c << top;
+    const uint64_t n = sec->n;
+    const uint64_t st = (n + kSortTile - 1) / kSortTile, lt = (n + kLevelTile - 1) / kLevelTile;
+    if (st > 0x7FFFFFFFull) MBR_FAIL(MBR_ERANGE, "%llu states", (unsigned long long)n);
+    // scratch: level sums and totals | two copies of the patterns and of their positions | digit counts and totals
+    auto al = [](size_t b) { return (b + 255) / 256 * 256; };
+    const size_t o_tot = al((size_t)lt * kMaxH * 8), o_key = o_tot + al(kMaxH * 8), keyb = al(n * sizeof(P)), idxb = al(n * 4);
+    const size_t o_idx = o_key + 2 * keyb, o_cnt = o_idx + 2 * idxb, o_dig = o_cnt + al((size_t)st * kDigits * 4);
+    DevBuf scratch;
+    MBR_TRY(scratch.alloc(o_dig + kDigits * 4));
+    unsigned char *base = scratch.as<unsigned char>();
+    int64_t *sums = reinterpret_cast<int64_t *>(base), *level_total = reinterpret_cast<int64_t *>(base + o_tot);
+    P *keys[2] = {reinterpret_cast<P *>(base + o_key), reinterpret_cast<P *>(base + o_key + keyb)};
+    uint32_t *idxs[2] = {reinterpret_cast<uint32_t *>(base + o_idx), reinterpret_cast<uint32_t *>(base + o_idx + idxb)};
+    uint32_t *counts = reinterpret_cast<uint32_t *>(base + o_cnt), *digit_total = reinterpret_cast<uint32_t *>(base + o_dig);
+    const P *key = sec->states.as<P>();
+    const uint32_t *idx = nullptr;
+    int to = 0;
+    for (int l = H - 2; l >= 0; --l)
+        for (int b = 0; b < t.w[l]; b += 8) {
+            const int shift = t.shift[l] + b;
+            const uint32_t mask = (1u << std::min(8, t.w[l] - b)) - 1;
+            tl_count_kernel<P><<<(unsigned)st, kSortBlock, 0, s>>>(key, n, shift, mask, counts);
+            tl_scan_kernel<uint32_t><<<kDigits, 1024, 0, s>>>(counts, st, digit_total);
+            tl_scatter_kernel<P><<<(unsigned)st, kSortBlock, 0, s>>>(key, idx, n, shift, mask, counts, digit_total, keys[to], idxs[to]);
+            key = keys[to];
+            idx = idxs[to];
+            to ^= 1;
         }
-        key[i] = k;
-        idx[i] = (uint32_t)i;
+    LevelArgs v{};
+    v.H = H;
+    for (int l = 0; l < H; ++l) {
+        v.shift[l] = t.shift[l];
+        v.w[l] = t.w[l];
     }
-    radix_sort_pairs(key, idx, M);
-    // field of level l in the key: bits [kb[l], kb[l] + w[l])
-    std::vector<int> kb(H);
-    {
-        int top = M;
-        for (int l = 0; l < H; ++l) {
-            top -= t.w[l];
-            kb[l] = top;
-        }
+    v.shift[H] = M;
+    int64_t total_of[kMaxH] = {0};
+    if (H > 1) {
+        tl_sums_kernel<P><<<(unsigned)lt, kLevelBlock, 0, s>>>(key, n, v, sums);
+        tl_scan_kernel<int64_t><<<H - 1, 1024, 0, s>>>(sums, lt, level_total);
+        MBR_HIP(hipGetLastError());
+        MBR_HIP(hipMemcpyAsync(total_of + 1, level_total, (size_t)(H - 1) * 8, hipMemcpyDeviceToHost, s));
+        MBR_HIP(hipStreamSynchronize(s));
     }
-    auto prefix = [&](P k, int l) -> P { return l == 0 ? (P)0 : (P)(k >> (kb[l - 1])); };
-    auto chunk = [&](P k, int l) -> uint32_t { return (uint32_t)((k >> kb[l]) & (P)((1ull << t.w[l]) - 1)); };
-    // pass 1: node spans and starts per level
-    std::vector<std::vector<uint32_t>> nfirst(H), nbase(H);
     uint64_t total = 0;
     for (int l = 0; l < H; ++l) {
         const uint64_t W = 1ull << t.w[l];
-        uint64_t pos;
-        t.off[l] = total;
-        if (l == 0) {
-            nfirst[0].push_back(0);
-            nbase[0].push_back(0);
-            pos = W;
-        } else {
-            pos = W - 1;  // front padding
-            size_t i = 0;
-            while (i < n) {
-                const P pf = prefix(key[i], l);
-                size_t j = i;
-                while (j + 1 < n && prefix(key[j + 1], l) == pf) ++j;
-                const uint32_t f = chunk(key[i], l), la = chunk(key[j], l);
-                nfirst[l].push_back(f);
-                nbase[l].push_back((uint32_t)(pos - f));
-                pos += (uint64_t)(la - f) + 1;
-                i = j + 1;
-            }
-            pos += W;  // tail padding
-        }
+        const uint64_t pos = l == 0 ? W : W - 1 + (uint64_t)total_of[l] + W;  // padded in front and behind
         if (pos > 0xFFFFFFFFull) MBR_FAIL(MBR_ERANGE, "trie level %d has %llu entries", l, (unsigned long long)pos);
+        t.off[l] = v.off[l] = total;
         total += pos;
     }
     t.off[H] = total;
     t.entries = total;
-    std::vector<uint32_t> tab(total, 0);
-    // pass 2: entries; the p-th distinct (prefix, chunk) pair of level l is
-    // node p of level l + 1
-    for (int l = 0; l < H; ++l) {
-        uint32_t *lv = tab.data() + t.off[l];
-        size_t node = 0, pair = 0;
-        size_t i = 0;
-        while (i < n) {
-            const P pf = prefix(key[i], l);
-            size_t j = i;
-            while (j < n && prefix(key[j], l) == pf) {
-                const uint32_t c = chunk(key[j], l);
-                size_t e = j;
-                while (e + 1 < n && prefix(key[e + 1], l) == pf && chunk(key[e + 1], l) == c) ++e;
-                const uint64_t slot = (uint64_t)nbase[l][node] + c;
-                lv[slot] = (l == H - 1) ? idx[j] : nbase[l + 1][pair];
-                ++pair;
-                j = e + 1;
-            }
-            ++node;
-            i = j;
-        }
-    }
+    MBR_TRY(t.table.alloc(total * 4));
+    MBR_HIP(hipMemsetAsync(t.table.p, 0, total * 4, s));
+    tl_fill_kernel<P><<<(unsigned)lt, kLevelBlock, 0, s>>>(key, idx, n, v, sums, t.table.as<uint32_t>());
+    MBR_HIP(hipGetLastError());
     // stage the top levels in LDS while they fit
     t.lds_levels = 0;
     t.lds_entries = 0;
@@ -217,7 +407,8 @@ mbr_status build_levels(TrieLevels &t, const std::vector<P> &states) {
         t.lds_levels = l + 1;
         t.lds_entries = t.off[l + 1];
     }
-    return mbr::upload(t.table, tab.data(), tab.size() * 4, nullptr);
+    MBR_HIP(hipStreamSynchronize(s));  // the trie is ready for any stream, and the scratch is free
+    return MBR_OK;
 }
 
 template <class P>
@@ -284,19 +475,8 @@ extern "C" mbr_status mbr_build_trie(const mbr_sector *sec, int32_t k, mbr_ranke
         t->shift[l] = b;
         b += t->w[l];
     }
-    mbr_status st;
-    if (sec->width_bits == 32) {
-        std::vector<uint32_t> h(sec->n);
-        MBR_HIP(hipMemcpyAsync(h.data(), sec->states.p, sec->n * 4, hipMemcpyDeviceToHost, s));
-        MBR_HIP(hipStreamSynchronize(s));
-        st = build_levels<uint32_t>(*t, h);
-    } else {
-        std::vector<uint64_t> h(sec->n);
-        MBR_HIP(hipMemcpyAsync(h.data(), sec->states.p, sec->n * 8, hipMemcpyDeviceToHost, s));
-        MBR_HIP(hipStreamSynchronize(s));
-        st = build_levels<uint64_t>(*t, h);
-    }
-    if (st != MBR_OK) return st;
+    if (sec->width_bits == 32) MBR_TRY(build_levels<uint32_t>(*t, sec, s));
+    else MBR_TRY(build_levels<uint64_t>(*t, sec, s));
     auto *r = new (std::nothrow) mbr_ranker;
     if (!r) MBR_FAIL(MBR_ENOMEM, "host allocation");
     r->kind = MBR_RANKER_TRIE;
