@@ -1,15 +1,23 @@
 // Sector enumeration on the device and unrank by the stored list.
 //
 // A sector is every M-bit pattern passing a set of popcount windows, in
-// ascending numeric order (Sec. III ordering).  When the particle number N is
-// fixed the enumeration walks only the C(M,N) patterns of that number: each
-// thread owns a run of consecutive combination indices, positions itself with
-// a greedy combinadics unrank (inverse of Eq. cns) and steps to the next larger
-// pattern of equal popcount with Gosper's rule.  Runs are visited in increasing
-// order, so a count pass, an exclusive scan of the per-run counts and a write
-// pass give the sorted list without any sort.
+// ascending numeric order (Sec. III ordering).
+//
+// Up to 32 orbitals a wave takes all patterns of one high part (the low
+// `low_bits` <= 14 bits run through, 64 at a time) and drops the high part at
+// once when it already breaks a window; see sector_block_kernel.
+//
+// Beyond, the particle number N has to be fixed and the enumeration walks the
+// C(M,N) patterns of that number: each thread owns a run of consecutive
+// combination indices, positions itself with a greedy combinadics unrank
+// (inverse of Eq. cns) and steps to the next larger pattern of equal popcount
+// with Gosper's rule.
+//
+// High parts and runs are visited in increasing order, so a count pass, an
+// exclusive scan of the counts and a write pass give the sorted list without
+// any sort.
+#include <algorithm>
 #include <memory>
-#include <numeric>
 
 #include "common.hpp"
 
@@ -64,48 +72,189 @@ __device__ __forceinline__ uint64_t next_combo(uint64_t a) {
     return (((r ^ a) >> 2) >> tz) | r;
 }
 
-template <bool FIXED>
-__device__ __forceinline__ uint64_t run_start(uint64_t u0, int N, int M, const uint64_t *bt) {
-    if constexpr (FIXED) return combo_at(u0, N, M, bt);
-    else return u0;
-}
-
-template <bool FIXED>
-__device__ __forceinline__ uint64_t run_next(uint64_t a) {
-    if constexpr (FIXED) return next_combo(a);
-    else return a + 1;
-}
-
-template <bool FIXED>
 __global__ void sector_count_kernel(uint64_t S, uint64_t run, int N, int M, ConsSet cs,
                                     const uint64_t *bt, uint32_t *counts, uint64_t nruns) {
     uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     if (t >= nruns) return;
     uint64_t u0 = t * run;
     uint64_t len = (S - u0 < run) ? S - u0 : run;
-    uint64_t a = run_start<FIXED>(u0, N, M, bt);
+    uint64_t a = combo_at(u0, N, M, bt);
     uint32_t cnt = 0;
     for (uint64_t j = 0; j < len; ++j) {
         cnt += in_sector(a, cs) ? 1u : 0u;
-        if (j + 1 < len) a = run_next<FIXED>(a);
+        if (j + 1 < len) a = next_combo(a);
     }
     counts[t] = cnt;
 }
 
-template <bool FIXED, class P>
 __global__ void sector_fill_kernel(uint64_t S, uint64_t run, int N, int M, ConsSet cs,
-                                   const uint64_t *bt, const uint64_t *offsets, P *out,
+                                   const uint64_t *bt, const uint64_t *offsets, uint64_t *out,
                                    uint64_t nruns) {
     uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     if (t >= nruns) return;
     uint64_t u0 = t * run;
     uint64_t len = (S - u0 < run) ? S - u0 : run;
-    uint64_t a = run_start<FIXED>(u0, N, M, bt);
+    uint64_t a = combo_at(u0, N, M, bt);
     uint64_t o = offsets[t];
     for (uint64_t j = 0; j < len; ++j) {
-        if (in_sector(a, cs)) out[o++] = static_cast<P>(a);
-        if (j + 1 < len) a = run_next<FIXED>(a);
+        if (in_sector(a, cs)) out[o++] = a;
+        if (j + 1 < len) a = next_combo(a);
     }
+}
+
+// ------------------------------------------------------------ up to 32 bits
+// Constraints on 32-bit patterns; weights already reduced to [0, modulus).
+// The windows that hold low bits come first; those past n are open (an empty
+// mask), so that NW windows can be tested per pattern from registers.
+struct ConsSet32 {
+    uint32_t mask[kMaxCons];
+    int32_t lo[kMaxCons];
+    uint32_t width[kMaxCons];  // hi - lo
+    int32_t n;
+    uint32_t modulus, residue;  // 1 and 0 when the sector has no modular weight
+    uint32_t weight[32];
+};
+
+constexpr int kMaxLow = 14;                   // low bits a wave runs through
+constexpr int kMaxHigh = 32 - kMaxLow;
+constexpr unsigned kSecBlock = 256, kSecWaves = kSecBlock / 64;
+constexpr uint32_t kStepUnroll = 4;            // steps in flight (the table of step weights has room for them)
+constexpr uint32_t kScanChunk = 1024;         // counts per scan workgroup
+constexpr uint32_t kMaxChunks = (1u << kMaxHigh) / kScanChunk;
+
+__device__ __forceinline__ uint32_t add_mod(uint32_t a, uint32_t b, uint32_t m) {
+    const uint32_t s = a + b;  // both below m < 2^31
+    return s >= m ? s - m : s;
+}
+
+// Weight of `bits` placed at bit `shift`, from the weights in LDS.
+__device__ __forceinline__ uint32_t weight_of(uint32_t bits, int shift, const uint32_t *weight, uint32_t modulus) {
+    uint32_t w = 0;
+    for (; bits; bits &= bits - 1) w = add_mod(w, weight[shift + __builtin_ctz(bits)], modulus);
+    return w;
+}
+
+// One wave per high part h: the patterns (h << low_bits) | p, p ascending, 64 at
+// a time, tested against every window (three instructions each) and against
+// the modular weight, which is split into a part per lane (bits 0-5), one per
+// step (a table in LDS) and one per high part.  Without FILL the members are
+// counted, with it they are written from offsets[h] on.
+//
+// Bound by the issue of these tests and the chain of a wave's few open high
+// parts.  Testing every pattern of the high parts that the windows leave open
+// costs less than enumerating the C(M,N) patterns of the right particle number
+// one by one, which took an unrank per 64 patterns and, per pattern, 64-bit
+// windows, a loop over the set bits for the weight and a 64-bit remainder:
+// total momentum 3 of the 14-site ring (841,332 states), both passes:
+// 524 -> 83 us, and the counts no longer go through host memory.
+template <class P, bool FILL, int NW>
+__global__ void __launch_bounds__(kSecBlock) sector_block_kernel(int low_bits, uint32_t n_high, ConsSet32 cs,
+                                                                 uint32_t *__restrict__ counts,
+                                                                 const uint64_t *__restrict__ chunk0, P *__restrict__ out) {
+    __shared__ uint32_t weight[32];
+    __shared__ __align__(16) uint32_t step_weight[1 << (kMaxLow - 6)];
+    const uint32_t steps = low_bits > 6 ? 1u << (low_bits - 6) : 1u;
+    const uint32_t lane = threadIdx.x & 63;
+    const bool on = low_bits >= 6 || lane < (1u << low_bits);
+    const uint32_t modulus = cs.modulus;  // 1 and all weights 0 without a modular weight
+    if (threadIdx.x < 32) weight[threadIdx.x] = cs.weight[threadIdx.x];
+    __syncthreads();
+    for (uint32_t s = threadIdx.x; s < std::max(steps, kStepUnroll); s += kSecBlock) step_weight[s] = weight_of(s, 6, weight, modulus);
+    const uint32_t lane_weight = weight_of(lane, 0, weight, modulus);
+    __syncthreads();
+    const uint32_t low_mask = (1u << low_bits) - 1;
+    // a wave's high parts lie waves apart, so that no wave gets a stretch of open ones; a lane looks at one each
+    const uint32_t waves = gridDim.x * kSecWaves, wave = blockIdx.x * kSecWaves + (threadIdx.x >> 6);
+    for (uint64_t h0 = wave; h0 < n_high; h0 += 64ull * waves) {
+        const uint64_t mine = h0 + (uint64_t)lane * waves;
+        const uint32_t mh = (uint32_t)mine;
+        bool open = mine < n_high;
+        uint32_t mine_need = 0;  // weight the low bits have to bring
+        if (open) {
+            const uint32_t high = mh << low_bits;
+            for (int j = 0; j < cs.n; ++j) {
+                const int c = __popc(high & cs.mask[j]), more = __popc(cs.mask[j] & low_mask);
+                open = open && c <= cs.lo[j] + (int)cs.width[j] && c + more >= cs.lo[j];
+            }
+            if (open) {
+                mine_need = cs.residue + modulus - weight_of(mh, low_bits, weight, modulus);
+                mine_need = mine_need >= modulus ? mine_need - modulus : mine_need;
+            }
+            if constexpr (!FILL) {
+                if (!open) counts[mh] = 0;
+            }
+        }
+        for (uint64_t live = __ballot(open); live; live &= live - 1) {
+            const int i = __builtin_ctzll(live);
+            const uint32_t h = (uint32_t)h0 + (uint32_t)i * waves, high = h << low_bits;
+            const uint32_t need = (uint32_t)__builtin_amdgcn_readlane((int)mine_need, i);
+            uint32_t n = 0;
+            uint64_t o = 0;
+            if constexpr (FILL) o = chunk0[h / kScanChunk] + counts[h];
+            for (uint32_t s0 = 0; s0 < steps; s0 += kStepUnroll) {
+                uint64_t b[kStepUnroll];
+#pragma unroll
+                for (uint32_t u = 0; u < kStepUnroll; ++u) {
+                    const uint32_t s = s0 + u, a = high | (s << 6) | lane;
+                    bool ok = on & (s < steps);
+#pragma unroll
+                    for (int j = 0; j < NW; ++j) ok = ok & ((uint32_t)(__popc(a & cs.mask[j]) - cs.lo[j]) <= cs.width[j]);
+                    ok = ok & (add_mod(lane_weight, step_weight[s], modulus) == need);
+                    b[u] = __ballot(ok);
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < kStepUnroll; ++u) {
+                    if constexpr (FILL) {
+                        if ((b[u] >> lane) & 1)
+                            out[o + __builtin_amdgcn_mbcnt_hi((uint32_t)(b[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[u], 0))] = (P)(high | ((s0 + u) << 6) | lane);
+                        o += (uint64_t)__popcll(b[u]);
+                    } else {
+                        n += (uint32_t)__popcll(b[u]);
+                    }
+                }
+            }
+            if constexpr (!FILL) {
+                if (lane == 0) counts[h] = n;
+            }
+        }
+    }
+}
+
+// Counts to offsets within chunks of kScanChunk, in place; sums[c] = the
+// chunk's total.
+__global__ void __launch_bounds__(kScanChunk) sector_scan_kernel(uint32_t *__restrict__ counts, uint32_t n, uint64_t *__restrict__ sums) {
+    __shared__ uint32_t wave_sum[kScanChunk / 64];
+    const uint32_t i = blockIdx.x * kScanChunk + threadIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t c = i < n ? counts[i] : 0u;
+    uint32_t v = c;  // a chunk holds at most 2^24 patterns
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = (uint32_t)__shfl_up((int)v, o, 64);
+        if (lane >= (uint32_t)o) v += u;
+    }
+    if (lane == 63) wave_sum[w] = v;
+    __syncthreads();
+    uint32_t before = 0;
+    for (uint32_t k = 0; k < w; ++k) before += wave_sum[k];
+    if (i < n) counts[i] = before + v - c;
+    if (threadIdx.x == kScanChunk - 1) sums[blockIdx.x] = before + v;
+}
+
+// Chunk totals to chunk offsets, in place, the sector size behind them.
+__global__ void __launch_bounds__(64) sector_chunks_kernel(uint64_t *sums, uint32_t n) {
+    __shared__ uint64_t s[kMaxChunks];
+    for (uint32_t i = threadIdx.x; i < n; i += 64) s[i] = sums[i];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t t = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+            const uint64_t c = s[i];
+            s[i] = t;
+            t += c;
+        }
+        sums[n] = t;
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += 64) sums[i] = s[i];
 }
 
 // First position that breaks a caller's list: for j >= 1, list[j] below its
@@ -160,6 +309,109 @@ int implied_n(int M, const std::vector<mbr_popc_cons> &cons) {
     return covered == full ? n : -1;
 }
 
+// The list of a sector of more than 32 orbitals and N particles, run by run.
+mbr_status list_runs(mbr_sector &sec, int N, uint64_t S, hipStream_t s) {
+    using namespace mbr;
+    const int M = sec.M;
+    const uint64_t *bt = nullptr;
+    MBR_TRY(device_binom(&bt));
+    uint64_t run = 64;
+    while ((S + run - 1) / run > (1ull << 24)) run *= 2;
+    uint64_t nruns = (S + run - 1) / run;
+
+    ConsSet cs{};
+    cs.n = (int32_t)sec.cons.size();
+    for (int j = 0; j < cs.n; ++j) {
+        cs.mask[j] = sec.cons[j].mask;
+        cs.lo[j] = sec.cons[j].lo;
+        cs.hi[j] = sec.cons[j].hi;
+    }
+    cs.modulus = sec.modulus;
+    cs.residue = sec.residue;
+    for (size_t i = 0; i < sec.weights.size(); ++i) cs.weight[i] = sec.weights[i];
+    DevBuf d_counts, d_off;
+    MBR_TRY(d_counts.alloc(nruns * sizeof(uint32_t)));
+    unsigned blk = 256;
+    unsigned grid = static_cast<unsigned>((nruns + blk - 1) / blk);
+    sector_count_kernel<<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_counts.as<uint32_t>(), nruns);
+    MBR_HIP(hipGetLastError());
+    std::vector<uint32_t> counts(nruns);
+    MBR_HIP(hipMemcpyAsync(counts.data(), d_counts.p, nruns * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    MBR_HIP(hipStreamSynchronize(s));
+    std::vector<uint64_t> off(nruns);
+    uint64_t total = 0;
+    for (uint64_t t = 0; t < nruns; ++t) {
+        off[t] = total;
+        total += counts[t];
+    }
+    if (total >= 0xFFFFFFFFull) MBR_FAIL(MBR_ERANGE, "sector of %llu states", (unsigned long long)total);
+    sec.n = total;
+    MBR_TRY(sec.states.alloc(total * 8));
+    MBR_TRY(upload(d_off, off.data(), nruns * sizeof(uint64_t), s));
+    if (total > 0) {
+        sector_fill_kernel<<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_off.as<uint64_t>(), sec.states.as<uint64_t>(), nruns);
+        MBR_HIP(hipGetLastError());
+        MBR_HIP(hipStreamSynchronize(s));
+    }
+    return MBR_OK;
+}
+
+// The list of a sector of up to 32 orbitals, high part by high part.
+mbr_status list_blocks(mbr_sector &sec, hipStream_t s) {
+    using namespace mbr;
+    const int M = sec.M;
+    // 2^10 to 2^14 patterns per wave, about 2^16 waves from 26 orbitals on
+    const int low = std::min(M, std::max(10, std::min(kMaxLow, M - 16)));
+    const uint32_t n_high = 1u << (M - low), chunks = (n_high + kScanChunk - 1) / kScanChunk;
+    ConsSet32 cs{};
+    int n_low = 0;  // windows with low bits; the others hold or fail with the high part
+    for (const bool with_low : {true, false}) {
+        for (const mbr_popc_cons &c : sec.cons) {
+            if (((c.mask & ((1ull << low) - 1)) != 0) != with_low) continue;
+            cs.mask[cs.n] = (uint32_t)c.mask;
+            cs.lo[cs.n] = c.lo;
+            cs.width[cs.n++] = (uint32_t)(c.hi - c.lo);
+        }
+        if (with_low) n_low = cs.n;
+    }
+    cs.modulus = sec.modulus > 0 ? (uint32_t)sec.modulus : 1u;
+    cs.residue = (uint32_t)sec.residue;
+    for (size_t i = 0; i < sec.weights.size(); ++i) cs.weight[i] = (uint32_t)(sec.weights[i] < 0 ? sec.weights[i] + sec.modulus : sec.weights[i]);
+    DevBuf scratch;  // chunk offsets and the size, then the counts
+    MBR_TRY(scratch.alloc((size_t)(chunks + 1) * 8 + (size_t)n_high * 4));
+    uint64_t *sums = scratch.as<uint64_t>();
+    uint32_t *counts = reinterpret_cast<uint32_t *>(sums + chunks + 1);
+    const unsigned grid = grid_for(n_high, kSecWaves, device_cu_count() * 8);
+    // windows tested per pattern
+    const int nw = n_low <= 1 ? 1 : n_low <= 3 ? 3 : kMaxCons;
+    const auto count = nw == 1 ? sector_block_kernel<uint32_t, false, 1> : nw == 3 ? sector_block_kernel<uint32_t, false, 3>
+                                                                                    : sector_block_kernel<uint32_t, false, kMaxCons>;
+    count<<<grid, kSecBlock, 0, s>>>(low, n_high, cs, counts, nullptr, nullptr);
+    sector_scan_kernel<<<chunks, kScanChunk, 0, s>>>(counts, n_high, sums);
+    sector_chunks_kernel<<<1, 64, 0, s>>>(sums, chunks);
+    MBR_HIP(hipGetLastError());
+    uint64_t total = 0;
+    MBR_HIP(hipMemcpyAsync(&total, sums + chunks, 8, hipMemcpyDeviceToHost, s));
+    MBR_HIP(hipStreamSynchronize(s));
+    if (total >= 0xFFFFFFFFull) MBR_FAIL(MBR_ERANGE, "sector of %llu states", (unsigned long long)total);
+    sec.n = total;
+    MBR_TRY(sec.states.alloc(total * (sec.width_bits / 8)));
+    if (total > 0) {
+        if (sec.width_bits == 32) {
+            const auto fill = nw == 1 ? sector_block_kernel<uint32_t, true, 1> : nw == 3 ? sector_block_kernel<uint32_t, true, 3>
+                                                                                           : sector_block_kernel<uint32_t, true, kMaxCons>;
+            fill<<<grid, kSecBlock, 0, s>>>(low, n_high, cs, counts, sums, sec.states.as<uint32_t>());
+        } else {
+            const auto fill = nw == 1 ? sector_block_kernel<uint64_t, true, 1> : nw == 3 ? sector_block_kernel<uint64_t, true, 3>
+                                                                                           : sector_block_kernel<uint64_t, true, kMaxCons>;
+            fill<<<grid, kSecBlock, 0, s>>>(low, n_high, cs, counts, sums, sec.states.as<uint64_t>());
+        }
+        MBR_HIP(hipGetLastError());
+        MBR_HIP(hipStreamSynchronize(s));
+    }
+    return MBR_OK;
+}
+
 mbr_status sector_build_impl(int32_t M, int32_t width_bits, int32_t n_cons, const mbr_popc_cons *cons,
                              const int32_t *weights, int32_t modulus, int32_t residue, mbr_sector **out,
                              void *stream) {
@@ -180,88 +432,26 @@ mbr_status sector_build_impl(int32_t M, int32_t width_bits, int32_t n_cons, cons
     if (modulus < 0 || (modulus > 0 && (!weights || residue < 0 || residue >= modulus)))
         MBR_FAIL(MBR_EINVAL, "modular constraint: modulus %d, residue %d", modulus, residue);
     int N = implied_n(M, cv);
-    uint64_t S;
+    uint64_t S = 0;
     if (N >= 0) {
         if (N > M) MBR_FAIL(MBR_EINVAL, "N=%d exceeds M=%d", N, M);
         S = binom(M, N);
         if (S > (1ull << 40)) MBR_FAIL(MBR_EUNSUPPORTED, "C(%d,%d) patterns to scan", M, N);
     } else {
         if (M > 32) MBR_FAIL(MBR_EUNSUPPORTED, "M=%d without a fixed particle number", M);
-        S = 1ull << M;
     }
     hipStream_t s = as_stream(stream);
-    const uint64_t *bt = nullptr;
-    MBR_TRY(device_binom(&bt));
-    uint64_t run = 64;
-    while ((S + run - 1) / run > (1ull << 24)) run *= 2;
-    uint64_t nruns = (S + run - 1) / run;
-
-    ConsSet cs{};
-    cs.n = n_cons;
-    for (int j = 0; j < n_cons; ++j) {
-        cs.mask[j] = cv[j].mask;
-        cs.lo[j] = cv[j].lo;
-        cs.hi[j] = cv[j].hi;
-    }
-    cs.modulus = modulus;
-    cs.residue = residue;
-    for (int i = 0; i < M && modulus > 0; ++i) cs.weight[i] = weights[i] % modulus;
-    DevBuf d_counts, d_off;
-    MBR_TRY(d_counts.alloc(nruns * sizeof(uint32_t)));
-    unsigned blk = 256;
-    unsigned grid = static_cast<unsigned>((nruns + blk - 1) / blk);
-    if (N >= 0)
-        sector_count_kernel<true><<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_counts.as<uint32_t>(), nruns);
-    else
-        sector_count_kernel<false><<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_counts.as<uint32_t>(), nruns);
-    MBR_HIP(hipGetLastError());
-    std::vector<uint32_t> counts(nruns);
-    MBR_HIP(hipMemcpyAsync(counts.data(), d_counts.p, nruns * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    MBR_HIP(hipStreamSynchronize(s));
-    std::vector<uint64_t> off(nruns);
-    uint64_t total = 0;
-    for (uint64_t t = 0; t < nruns; ++t) {
-        off[t] = total;
-        total += counts[t];
-    }
-    if (total >= 0xFFFFFFFFull) MBR_FAIL(MBR_ERANGE, "sector of %llu states", (unsigned long long)total);
-
-    auto *sec = new (std::nothrow) mbr_sector;
-    if (!sec) MBR_FAIL(MBR_ENOMEM, "host allocation");
+    auto sec = std::make_unique<mbr_sector>();
     sec->M = M;
     sec->width_bits = width_bits;
-    sec->n = total;
     sec->cons = cv;
     sec->modulus = modulus;
     sec->residue = residue;
-    for (int i = 0; i < M && modulus > 0; ++i) sec->weights.push_back(cs.weight[i]);
+    for (int i = 0; i < M && modulus > 0; ++i) sec->weights.push_back(weights[i] % modulus);
     MBR_HIP(hipGetDevice(&sec->device));
-    mbr_status st = sec->states.alloc(total * (width_bits / 8));
-    if (st == MBR_OK) st = upload(d_off, off.data(), nruns * sizeof(uint64_t), s);
-    if (st != MBR_OK) {
-        delete sec;
-        return st;
-    }
-    if (total > 0) {
-        if (width_bits == 32) {
-            if (N >= 0)
-                sector_fill_kernel<true, uint32_t><<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_off.as<uint64_t>(), sec->states.as<uint32_t>(), nruns);
-            else
-                sector_fill_kernel<false, uint32_t><<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_off.as<uint64_t>(), sec->states.as<uint32_t>(), nruns);
-        } else {
-            if (N >= 0)
-                sector_fill_kernel<true, uint64_t><<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_off.as<uint64_t>(), sec->states.as<uint64_t>(), nruns);
-            else
-                sector_fill_kernel<false, uint64_t><<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_off.as<uint64_t>(), sec->states.as<uint64_t>(), nruns);
-        }
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) {
-            delete sec;
-            MBR_FAIL(MBR_EHIP, "sector fill: %s", hipGetErrorString(e));
-        }
-    }
-    *out = sec;
+    if (M <= 32) MBR_TRY(list_blocks(*sec, s));
+    else MBR_TRY(list_runs(*sec, N, S, s));
+    *out = sec.release();
     return MBR_OK;
 }
 
