@@ -314,7 +314,9 @@ mbr_status mbr_learned_params(const mbr_ranker *r, float *host_out, void *stream
  * forward pass (d_pred[B]) and mean-squared-loss gradients (d_grad[6337], same
  * order as mbr_learned_params) for B patterns d_q (uint32) and targets d_tgt,
  * with fp32 parameters d_params (rounded to bf16 inside, as in training).
- * B must be a multiple of 64. */
+ * B must be a multiple of 64.  mbr_mlp_gradients waits for its work; its
+ * partials lie in a static device array of its own (6.5 MB per device), or in
+ * an allocation while another thread's call holds that array. */
 mbr_status mbr_mlp_forward(const float *d_params, const uint32_t *d_q, int32_t B,
                            float *d_pred, void *stream);
 mbr_status mbr_mlp_gradients(const float *d_params, const uint32_t *d_q, const float *d_tgt,
@@ -323,10 +325,9 @@ mbr_status mbr_mlp_gradients(const float *d_params, const uint32_t *d_q, const f
 /* mbr_mlp_gradients without any device allocation and without host
  * synchronisation, for callers that cannot allocate: a training step captured
  * in a HIP graph, or a loop that may not call hipMalloc.  Same arguments,
- * kernels and results as mbr_mlp_gradients; the scratch (rounded weights,
- * per-sample activations, per-64-sample gradient partials) is one static
- * device array of about 11.8 MB that each device holds until the process
- * ends, sized for B <= 8192 (MBR_ERANGE beyond).  Every scratch word a call
+ * kernels and results as mbr_mlp_gradients; the scratch (gradient partials) is
+ * one static device array of about 6.5 MB that each device holds until the
+ * process ends (batches of B <= 8192; MBR_ERANGE beyond).  Every scratch word a call
  * reads is written earlier in the same call, so nothing needs clearing, but
  * calls that overlap on one device (other streams, other threads) share that
  * array and race: serialise them.  Only enqueues work on `stream`. */

@@ -33,13 +33,14 @@
 // output fragments of tiles 2c and 2c+1 side by side, and the weights are
 // loaded in that order.  Activations go from fp32 to bf16 in registers
 // (rounded, then ReLU as a packed 16-bit integer maximum).  Training runs in
-// fp32 on the vector ALUs (forward with the bf16 weights, backward,
+// fp32, also on the matrix cores (forward with the bf16 weights, backward,
 // fixed-order batch reductions, Adam).
+#include <algorithm>
 #include <cmath>
 #include <memory>
 #include <mutex>
 
-#include "common.hpp"
+#include "rank_device.hpp"
 
 namespace {
 
@@ -419,163 +420,230 @@ __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, uint64_t k) {
     return z ^ (z >> 31);
 }
 
-// Scratch of one batch, feature-major ([feature][sample]) so that the
-// per-sample threads write and the reduction reads contiguous rows.
-struct TrainScratch {
-    float *h1, *h2, *dz1, *dz2;  // [64][B]
-    float *dy;                   // [B]
-    uint32_t *x;                 // [B] patterns
-    float *loss_part;            // [B / 64]
-};
+// fp32 value of the bf16 rounding of a parameter.
+__device__ __forceinline__ float rounded(float w) { return bf2f(f2bf(w)); }
 
-// One thread per sample: forward with bf16-rounded weights in fp32, loss,
-// backward to dz2 and dz1.  Samples come from (q, tgt) when given, else are
-// drawn from the sector: idx = splitmix64(seed, step*B + s) mod n.
-__global__ void __launch_bounds__(64) mlp_fwd_bwd_kernel(const float *__restrict__ wr, int B,
-                                                         const uint32_t *__restrict__ q,
-                                                         const float *__restrict__ tgt,
-                                                         const uint32_t *__restrict__ states,
-                                                         uint64_t n, uint64_t seed, uint64_t step,
-                                                         TrainScratch S) {
-    __shared__ float w1[kH * kIn], w2[kH * kH], b1[kH], b2[kH], w3[kH];
-    __shared__ float sh1[kH][64], sdz2[kH][64];  // per-thread vectors, [feature][thread]
-    const int tid = threadIdx.x;
-    for (int i = threadIdx.x; i < kH * kIn; i += blockDim.x) w1[i] = wr[P_W1 + i];
-    for (int i = threadIdx.x; i < kH * kH; i += blockDim.x) w2[i] = wr[P_W2 + i];
-    for (int i = threadIdx.x; i < kH; i += blockDim.x) {
-        b1[i] = wr[P_B1 + i];
-        b2[i] = wr[P_B2 + i];
-        w3[i] = wr[P_W3 + i];
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4 &c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+constexpr int kPart = kParams + 1;       // a workgroup's partial: gradients, then the squared error
+constexpr int kPartials = 256;           // partials of a batch at most
+constexpr unsigned kGradBlock = 256;     // four waves, each 16 rows of every layer
+constexpr int kTileNT = 2;               // 16-sample groups of a tile
+
+// Gradient partials of a batch, one per workgroup, each over the tiles of
+// 16 NT samples that it takes in turn: forward with the bf16-rounded weights,
+// squared error, backward and the products over the samples, all in fp32 and
+// without leaving the workgroup.  Every product runs on the matrix cores in
+// fp32 (v_mfma_f32_16x16x4_f32: lane l holds A[l%16][l/16] and B[l/16][l%16] of
+// a 4-deep step, and C[4 (l/16) + r][l%16]).  Wave w owns rows 16w .. 16w+15 of
+// each layer: its weights stay in registers, as do its gradients; activations
+// and their gradients pass between waves through LDS, where one array serves
+// both orders (rows as K of the next layer, samples as K of the gradient).
+// Samples come from (q, tgt) when given, else are drawn from the sector:
+// idx = splitmix64(seed, step*B + s) mod n.
+//
+// Bound at the batches that training uses by the chain of a tile (five
+// products with a barrier between them): 4,096 samples in 11.4 us on 128
+// workgroups, and 3.3 us for the sum.  One thread per sample on 64 lanes, with
+// the activations through memory to a second kernel, took 132 + 39 us and its
+// sum 16 us.  At 2^20 samples 0.49 ms, 80 TFLOP/s of the 138 that a large
+// fp32 product reaches (12.7 ms before).  Against 64 bits the gradient is off
+// by 5e-8 to 8e-8 (8e-8 to 1.7e-7 before) at 64 to 8,192 samples.  Tiles of 16
+// samples gain nothing: 37.1 against 35.0 us a call at 4,096.
+template <int NT>
+__global__ void __launch_bounds__(kGradBlock) mlp_grad_kernel(const float *__restrict__ w, int B,
+                                                              const uint32_t *__restrict__ q,
+                                                              const float *__restrict__ tgt,
+                                                              const uint32_t *__restrict__ states,
+                                                              uint64_t n, uint64_t seed, uint64_t step,
+                                                              float *__restrict__ part) {
+    constexpr int S = 16 * NT, LD = S + 1;
+    __shared__ float h1[kH * LD], d1[kH * LD], d2[kH * LD];  // [feature][sample]
+    __shared__ float ysum[kGradBlock / 64][S], ts[S];
+    __shared__ uint32_t xs[S];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
+    const int row = 16 * wv + 4 * g;  // this lane's rows of a C fragment: row .. row + 3
+    float a1[kIn / 4], a2[kH / 4], a2t[kH / 4];
+#pragma unroll
+    for (int k = 0; k < kIn / 4; ++k) a1[k] = rounded(w[P_W1 + (16 * wv + c) * kIn + 4 * k + g]);
+#pragma unroll
+    for (int k = 0; k < kH / 4; ++k) {
+        a2[k] = rounded(w[P_W2 + (16 * wv + c) * kH + 4 * k + g]);
+        a2t[k] = rounded(w[P_W2 + (4 * k + g) * kH + 16 * wv + c]);
     }
-    __syncthreads();
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    float sq = 0.f;
-    if (s < B) {
-        uint32_t a;
-        float t;
-        if (q) {
-            a = q[s];
-            t = tgt[s];
-        } else {
-            const uint64_t idx = splitmix64_at(seed, step * (uint64_t)B + (uint64_t)s) % n;
-            a = states[idx];
-            t = (float)((double)idx / (double)n);
-        }
-        S.x[s] = a;
-        for (int i = 0; i < kH; ++i) {
-            float z = b1[i];
-            uint32_t m = a;
-            while (m) {
-                const int k = __ffs(m) - 1;
-                m &= m - 1;
-                z += w1[i * kIn + k];
+    f32x4 b1, b2, w3;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        b1[r] = rounded(w[P_B1 + row + r]);
+        b2[r] = rounded(w[P_B2 + row + r]);
+        w3[r] = rounded(w[P_W3 + row + r]);
+    }
+    const float b3 = rounded(w[P_B3]);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 gw2[4] = {zero, zero, zero, zero}, gw1[2] = {zero, zero}, gb1 = zero, gb2 = zero, gw3 = zero;
+    float gb3 = 0.f, sq = 0.f;
+    for (int tile = blockIdx.x; tile < B / S; tile += gridDim.x) {
+        __syncthreads();  // the tile before is done with LDS
+        if (threadIdx.x < S) {
+            const int s = tile * S + threadIdx.x;
+            if (q) {
+                xs[threadIdx.x] = q[s];
+                ts[threadIdx.x] = tgt[s];
+            } else {
+                const uint64_t idx = splitmix64_at(seed, step * (uint64_t)B + (uint64_t)s) % n;
+                xs[threadIdx.x] = states[idx];
+                ts[threadIdx.x] = (float)((double)idx / (double)n);
             }
-            const float h = z > 0.f ? z : 0.f;
-            sh1[i][tid] = h;
-            S.h1[(size_t)i * B + s] = h;
         }
-        float y = wr[P_B3];
-        for (int j = 0; j < kH; ++j) {
-            float z = b2[j];
-#pragma unroll 16
-            for (int i = 0; i < kH; ++i) z += w2[j * kH + i] * sh1[i][tid];
-            const float h = z > 0.f ? z : 0.f;
-            S.h2[(size_t)j * B + s] = h;
-            y += w3[j] * h;
-            sdz2[j][tid] = z > 0.f ? 1.f : 0.f;  // ReLU mask, scaled below
+        __syncthreads();
+        // layer 1: K is the input bits
+        f32x4 h[NT];
+        uint32_t x[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            x[t] = xs[16 * t + c];
+            h[t] = b1;
         }
-        const float d = 2.f * (y - t) / (float)B;
-        sq = (y - t) * (y - t);
-        S.dy[s] = d;
-        for (int j = 0; j < kH; ++j) {
-            const float g = sdz2[j][tid] * d * w3[j];
-            sdz2[j][tid] = g;
-            S.dz2[(size_t)j * B + s] = g;
+#pragma unroll
+        for (int k = 0; k < kIn / 4; ++k)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) h[t] = mfma_f32(a1[k], (x[t] >> (4 * k + g)) & 1u ? 1.f : 0.f, h[t]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                h[t][r] = h[t][r] > 0.f ? h[t][r] : 0.f;
+                h1[(row + r) * LD + 16 * t + c] = h[t][r];
+            }
+        __syncthreads();
+        // layer 2, and the output's share of these rows
+        f32x4 z[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) z[t] = b2;
+#pragma unroll
+        for (int k = 0; k < kH / 4; ++k)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) z[t] = mfma_f32(a2[k], h1[(4 * k + g) * LD + 16 * t + c], z[t]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            float y = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                z[t][r] = z[t][r] > 0.f ? z[t][r] : 0.f;
+                y += w3[r] * z[t][r];
+            }
+            y += __shfl_xor(y, 16, 64);
+            y += __shfl_xor(y, 32, 64);
+            if (g == 0) ysum[wv][16 * t + c] = y;
         }
-        for (int i = 0; i < kH; ++i) {
-            float g = 0.f;
-#pragma unroll 16
-            for (int j = 0; j < kH; ++j) g += w2[j * kH + i] * sdz2[j][tid];
-            S.dz1[(size_t)i * B + s] = sh1[i][tid] > 0.f ? g : 0.f;
+        __syncthreads();
+        // output, its error, and back to layer 2
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int s = 16 * t + c;
+            const float y = b3 + ((ysum[0][s] + ysum[1][s]) + (ysum[2][s] + ysum[3][s]));
+            const float e = y - ts[s], d = 2.f * e / (float)B;
+            if (wv == 0 && g == 0) {
+                sq += e * e;
+                gb3 += d;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float dz = z[t][r] > 0.f ? d * w3[r] : 0.f;
+                gw3[r] += d * z[t][r];
+                gb2[r] += dz;
+                d2[(row + r) * LD + s] = dz;
+            }
+        }
+        __syncthreads();
+        // back to layer 1
+        f32x4 u[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) u[t] = zero;
+#pragma unroll
+        for (int k = 0; k < kH / 4; ++k)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) u[t] = mfma_f32(a2t[k], d2[(4 * k + g) * LD + 16 * t + c], u[t]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float dz = h[t][r] > 0.f ? u[t][r] : 0.f;
+                gb1[r] += dz;
+                d1[(row + r) * LD + 16 * t + c] = dz;
+            }
+        wave_lds_fence();  // a wave reads only its own rows of d1
+        // weight gradients: K is the samples
+#pragma unroll
+        for (int k = 0; k < S / 4; ++k) {
+            const float a = d2[(16 * wv + c) * LD + 4 * k + g];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) gw2[j] = mfma_f32(a, h1[(16 * j + c) * LD + 4 * k + g], gw2[j]);
+            const float e = d1[(16 * wv + c) * LD + 4 * k + g];
+            const uint32_t xk = xs[4 * k + g];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) gw1[j] = mfma_f32(e, (xk >> (16 * j + c)) & 1u ? 1.f : 0.f, gw1[j]);
         }
     }
-    // per-wave partial of the squared error
-    for (int o = 32; o > 0; o >>= 1) sq += __shfl_down(sq, o, 64);
-    if ((threadIdx.x & 63) == 0) S.loss_part[s >> 6] = sq;
+    float *out = part + (size_t)blockIdx.x * kPart;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[P_W2 + (row + r) * kH + 16 * j + c] = gw2[j][r];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) out[P_W1 + (row + r) * kIn + 16 * j + c] = gw1[j][r];
+        // the sums over samples of the 16 lanes of a row
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            gb1[r] += __shfl_xor(gb1[r], o, 64);
+            gb2[r] += __shfl_xor(gb2[r], o, 64);
+            gw3[r] += __shfl_xor(gw3[r], o, 64);
+        }
+        if (c == 0) {
+            out[P_B1 + row + r] = gb1[r];
+            out[P_B2 + row + r] = gb2[r];
+            out[P_W3 + row + r] = gw3[r];
+        }
+    }
+    if (wv == 0) {
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            gb3 += __shfl_xor(gb3, o, 64);
+            sq += __shfl_xor(sq, o, 64);
+        }
+        if (lane == 0) {
+            out[P_B3] = gb3;
+            out[kParams] = sq;
+        }
+    }
 }
 
-constexpr int kChunk = 64;  // samples per gradient-partial workgroup
+// Sum of the partials, fixed order: 8 waves take every 8th partial of 64
+// parameters, then wave 0 adds the wave sums.  Optionally applies one Adam
+// step to the fp32 masters and refreshes the rounded copies (fp32 value and
+// bf16 bits); with loss, the mean squared error of the B samples.
+constexpr unsigned kSumBlock = 512;
 
-// Gradient partials of one chunk of kChunk samples, all 6337 parameters.
-__global__ void __launch_bounds__(256) mlp_grad_part_kernel(int B, TrainScratch S, float *__restrict__ part) {
-    __shared__ float ta[kH][kChunk + 1];
-    __shared__ float tb[kH][kChunk + 1];
-    __shared__ uint32_t xs[kChunk];
-    __shared__ float dys[kChunk];
-    const int c0 = blockIdx.x * kChunk;
-    const int cn = min(kChunk, B - c0);
-    float *out = part + (size_t)blockIdx.x * kParams;
-    // phase A: dz2 (ta) and h1 (tb): gW2[j][i] = sum_s dz2[j][s] h1[i][s], gb2
-    for (int e = threadIdx.x; e < kH * kChunk; e += blockDim.x) {
-        const int f = e / kChunk, s = e % kChunk;
-        ta[f][s] = s < cn ? S.dz2[(size_t)f * B + c0 + s] : 0.f;
-        tb[f][s] = s < cn ? S.h1[(size_t)f * B + c0 + s] : 0.f;
-    }
-    for (int s = threadIdx.x; s < kChunk; s += blockDim.x) {
-        xs[s] = s < cn ? S.x[c0 + s] : 0u;
-        dys[s] = s < cn ? S.dy[c0 + s] : 0.f;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < kH * kH; e += blockDim.x) {
-        const int j = e / kH, i = e % kH;
-        float g = 0.f;
-        for (int s = 0; s < kChunk; ++s) g += ta[j][s] * tb[i][s];
-        out[P_W2 + e] = g;
-    }
-    for (int j = threadIdx.x; j < kH; j += blockDim.x) {
-        float g = 0.f;
-        for (int s = 0; s < kChunk; ++s) g += ta[j][s];
-        out[P_B2 + j] = g;
-    }
-    __syncthreads();
-    // phase B: dz1 (ta) and h2 (tb): gW1[i][k] = sum_s dz1[i][s] x_k(s), gb1, gw3, gb3
-    for (int e = threadIdx.x; e < kH * kChunk; e += blockDim.x) {
-        const int f = e / kChunk, s = e % kChunk;
-        ta[f][s] = s < cn ? S.dz1[(size_t)f * B + c0 + s] : 0.f;
-        tb[f][s] = s < cn ? S.h2[(size_t)f * B + c0 + s] : 0.f;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < kH * kIn; e += blockDim.x) {
-        const int i = e / kIn, k = e % kIn;
-        float g = 0.f;
-        for (int s = 0; s < kChunk; ++s) g += ((xs[s] >> k) & 1u) ? ta[i][s] : 0.f;
-        out[P_W1 + e] = g;
-    }
-    for (int i = threadIdx.x; i < kH; i += blockDim.x) {
-        float g1 = 0.f, g3 = 0.f;
-        for (int s = 0; s < kChunk; ++s) {
-            g1 += ta[i][s];
-            g3 += dys[s] * tb[i][s];
-        }
-        out[P_B1 + i] = g1;
-        out[P_W3 + i] = g3;
-    }
-    if (threadIdx.x == 0) {
-        float g = 0.f;
-        for (int s = 0; s < kChunk; ++s) g += dys[s];
-        out[P_B3] = g;
-    }
-}
-
-// Sum the chunk partials in chunk order; optionally apply one Adam step to the
-// fp32 masters and refresh the rounded copies (fp32 value and bf16 bits).
-__global__ void mlp_reduce_adam_kernel(const float *__restrict__ part, int nchunk, float *grad,
-                                       float *w, float *m, float *v, float *wr, uint16_t *wb,
-                                       float lr, float b1c, float b2c, int adam) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= kParams) return;
+__global__ void __launch_bounds__(kSumBlock) mlp_reduce_adam_kernel(const float *__restrict__ part, int np, float *grad, float *loss, int B,
+                                                                    float *w, float *m, float *v, float *wr, uint16_t *wb, float lr,
+                                                                    float b1c, float b2c, int adam) {
+    __shared__ float red[kSumBlock / 64][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = blockIdx.x * 64 + lane;
     float g = 0.f;
-    for (int c = 0; c < nchunk; ++c) g += part[(size_t)c * kParams + p];
+    if (p < kPart)
+#pragma unroll 8
+        for (int k = wave; k < np; k += kSumBlock / 64) g += part[(size_t)k * kPart + p];
+    red[wave][lane] = g;
+    __syncthreads();
+    if (wave != 0 || p >= kPart) return;
+    g = 0.f;
+    for (int k = 0; k < (int)(kSumBlock / 64); ++k) g += red[k][lane];
+    if (p == kParams) {
+        if (loss) *loss = g / (float)B;
+        return;
+    }
     if (grad) grad[p] = g;
     if (!adam) return;
     const float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
@@ -599,86 +667,57 @@ __global__ void mlp_round_kernel(const float *__restrict__ w, float *wr, uint16_
     wr[p] = bf2f(b);
 }
 
-__global__ void mlp_loss_kernel(const float *__restrict__ lp, int nparts, int B, float *loss) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    float s = 0.f;
-    for (int i = 0; i < nparts; ++i) s += lp[i];
-    *loss = s / (float)B;
-}
+constexpr size_t part_bytes(int partials) { return (size_t)partials * kPart * 4; }
+constexpr unsigned kSumGrid = (kPart + 63) / 64;
 
-// Bytes of a batch's activation scratch and of its chunk partials.
-constexpr size_t act_bytes(size_t b) { return b * 4 * (4 * kH + 2) + (b / 64 + 1) * 4; }
-constexpr size_t part_bytes(size_t b) { return (b + kChunk - 1) / kChunk * kParams * 4; }
+// Workgroups (and partials) of a batch of B samples (a multiple of 32).
+int partials_of(int B) { return std::min(B / (16 * kTileNT), kPartials); }
 
-// Activation scratch of B samples laid out in the memory at f.
-TrainScratch carve(float *f, size_t n) {
-    TrainScratch S{};
-    S.h1 = f;
-    S.h2 = f + n * kH;
-    S.dz1 = f + 2 * n * kH;
-    S.dz2 = f + 3 * n * kH;
-    S.dy = f + 4 * n * kH;
-    S.x = reinterpret_cast<uint32_t *>(f + 4 * n * kH + n);
-    S.loss_part = f + 4 * n * kH + 2 * n;
-    return S;
-}
-
-// Batch scratch of B samples.
-struct TrainBufs {
-    mbr::DevBuf scratch, part;
-    TrainScratch S{};
-    int B = 0;
-    mbr_status alloc(int b) {
-        B = b;
-        MBR_TRY(scratch.alloc(act_bytes((size_t)b)));
-        S = carve(scratch.as<float>(), (size_t)b);
-        MBR_TRY(part.alloc(part_bytes((size_t)b)));
-        return MBR_OK;
-    }
-};
-
-// Scratch of mbr_mlp_gradients_noalloc in one file-scope device array: the
-// rounded weights (fp32 and bf16), then the activations and the chunk
-// partials of a batch of up to kStaticBatch samples.  Each device holds its
-// own copy for the life of the process; host code uses only the address
-// hipGetSymbolAddress returns for the current device (static_scratch).
+// Scratch of the gradient entry points in file-scope device arrays, one for
+// each of them: the partials of a batch.  Each device holds its own copies for
+// the life of the process; host code uses only the address hipGetSymbolAddress
+// returns for the current device (static_scratch).
 constexpr int kStaticBatch = 8192;
-constexpr size_t kAl = 256;
-constexpr size_t al256(size_t v) { return (v + kAl - 1) / kAl * kAl; }
-constexpr size_t kStWr = 0;
-constexpr size_t kStWb = al256(kStWr + (size_t)kParams * 4);
-constexpr size_t kStAct = al256(kStWb + (size_t)kParams * 2);
-constexpr size_t kStPart = al256(kStAct + act_bytes(kStaticBatch));
-constexpr size_t kStaticBytes = al256(kStPart + part_bytes(kStaticBatch));
-static __device__ __align__(256) unsigned char scratch[kStaticBytes];
+static __device__ __align__(256) float scratch[kPartials * kPart];         // mbr_mlp_gradients_noalloc
+static __device__ __align__(256) float shared_scratch[kPartials * kPart];  // mbr_mlp_gradients, one call at a time
 
 constexpr int kMaxDevices = 64;
 std::mutex g_static_mu;
-void *g_static_ptr[kMaxDevices] = {nullptr};
+float *g_static_ptr[2][kMaxDevices] = {{nullptr}};
+std::mutex g_shared_mu[kMaxDevices];  // holders of shared_scratch
 
-// Device address of `scratch` on the current device, looked up once per device.
-mbr_status static_scratch(unsigned char **out) {
+// Device address of `scratch` (0) or `shared_scratch` (1) on the current
+// device, looked up once per device.
+mbr_status static_scratch(int which, float **out, int *device) {
     int dev = 0;
     MBR_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) MBR_FAIL(MBR_EUNSUPPORTED, "device %d beyond %d", dev, kMaxDevices);
     std::lock_guard<std::mutex> lk(g_static_mu);
-    if (!g_static_ptr[dev]) {
+    if (!g_static_ptr[which][dev]) {
         void *p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+        const hipError_t e = which ? hipGetSymbolAddress(&p, HIP_SYMBOL(shared_scratch)) : hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess || !p)
             MBR_FAIL(MBR_EHIP, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(e));
-        g_static_ptr[dev] = p;
+        g_static_ptr[which][dev] = static_cast<float *>(p);
     }
-    *out = static_cast<unsigned char *>(g_static_ptr[dev]);
+    *out = g_static_ptr[which][dev];
+    if (device) *device = dev;
     return MBR_OK;
 }
 
-// Forward/backward and chunk partials of one batch.
-mbr_status batch_grad(TrainBufs &T, const float *wr, const uint32_t *q, const float *tgt,
-                      const uint32_t *states, uint64_t n, uint64_t seed, uint64_t step, hipStream_t s) {
-    const int B = T.B;
-    mlp_fwd_bwd_kernel<<<(B + 63) / 64, 64, 0, s>>>(wr, B, q, tgt, states, n, seed, step, T.S);
-    mlp_grad_part_kernel<<<(B + kChunk - 1) / kChunk, 256, 0, s>>>(B, T.S, T.part.as<float>());
+// Gradient partials of one batch.
+mbr_status batch_grad(const float *w, int B, const uint32_t *q, const float *tgt, const uint32_t *states, uint64_t n, uint64_t seed,
+                      uint64_t step, float *part, hipStream_t s) {
+    mlp_grad_kernel<kTileNT><<<partials_of(B), kGradBlock, 0, s>>>(w, B, q, tgt, states, n, seed, step, part);
+    MBR_HIP(hipGetLastError());
+    return MBR_OK;
+}
+
+// Gradients and loss of one batch through the partials at `part`.
+mbr_status batch_sum(const float *w, int B, const uint32_t *q, const float *tgt, float *grad, float *loss, float *part, hipStream_t s) {
+    MBR_TRY(batch_grad(w, B, q, tgt, nullptr, 0, 0, 0, part, s));
+    mlp_reduce_adam_kernel<<<kSumGrid, kSumBlock, 0, s>>>(part, partials_of(B), grad, loss, B, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                                          0.f, 1.f, 1.f, 0);
     MBR_HIP(hipGetLastError());
     return MBR_OK;
 }
@@ -808,22 +847,22 @@ mbr_status mbr_learned_train(const mbr_sector *sec, const mbr_learned_opts *o,
     MBR_HIP(hipMemsetAsync(lm->m.p, 0, kParams * 4, s));
     MBR_HIP(hipMemsetAsync(lm->v.p, 0, kParams * 4, s));
     mlp_round_kernel<<<(kParams + 255) / 256, 256, 0, s>>>(lm->w.as<float>(), lm->wr.as<float>(), lm->wb.as<uint16_t>());
-    TrainBufs T;
-    MBR_TRY(T.alloc(o->batch));
+    DevBuf part;
+    const int np = partials_of(o->batch);
+    MBR_TRY(part.alloc(part_bytes(np)));
     const uint64_t per_epoch = o->samples_per_epoch ? o->samples_per_epoch : sec->n;
     const uint64_t steps_per_epoch = (per_epoch + o->batch - 1) / o->batch;
     const uint64_t total = steps_per_epoch * (uint64_t)o->epochs;
-    const int nchunk = (o->batch + kChunk - 1) / kChunk;
     double b1p = 1.0, b2p = 1.0;
     for (uint64_t st = 0; st < total; ++st) {
-        MBR_TRY(batch_grad(T, lm->wr.as<float>(), nullptr, nullptr, sec->states.as<uint32_t>(), sec->n,
-                           o->seed, st, s));
+        MBR_TRY(batch_grad(lm->wr.as<float>(), o->batch, nullptr, nullptr, sec->states.as<uint32_t>(), sec->n, o->seed, st,
+                           part.as<float>(), s));
         b1p *= 0.9;
         b2p *= 0.999;
         // cosine decay of the step size over the run
         const double lr = o->lr * 0.5 * (1.0 + std::cos(3.14159265358979323846 * (double)st / (double)total));
-        mlp_reduce_adam_kernel<<<(kParams + 255) / 256, 256, 0, s>>>(
-            T.part.as<float>(), nchunk, nullptr, lm->w.as<float>(), lm->m.as<float>(), lm->v.as<float>(),
+        mlp_reduce_adam_kernel<<<kSumGrid, kSumBlock, 0, s>>>(
+            part.as<float>(), np, nullptr, nullptr, o->batch, lm->w.as<float>(), lm->m.as<float>(), lm->v.as<float>(),
             lm->wr.as<float>(), lm->wb.as<uint16_t>(), (float)lr, (float)(1.0 - b1p), (float)(1.0 - b2p), 1);
         MBR_HIP(hipGetLastError());
     }
@@ -1004,20 +1043,20 @@ mbr_status mbr_mlp_gradients(const float *d_params, const uint32_t *d_q, const f
     if (!d_params || !d_q || !d_tgt || !d_grad) MBR_FAIL(MBR_EINVAL, "null pointer");
     if (B <= 0 || B % 64 != 0) MBR_FAIL(MBR_EINVAL, "B=%d must be a positive multiple of 64", B);
     hipStream_t s = as_stream(stream);
-    DevBuf wr, wb;
-    MBR_TRY(wr.alloc(kParams * 4));
-    MBR_TRY(wb.alloc(kParams * 2));
-    mlp_round_kernel<<<(kParams + 255) / 256, 256, 0, s>>>(d_params, wr.as<float>(), wb.as<uint16_t>());
-    TrainBufs T;
-    MBR_TRY(T.alloc(B));
-    MBR_TRY(batch_grad(T, wr.as<float>(), d_q, d_tgt, nullptr, 0, 0, 0, s));
-    mlp_reduce_adam_kernel<<<(kParams + 255) / 256, 256, 0, s>>>(T.part.as<float>(), (B + kChunk - 1) / kChunk,
-                                                                 d_grad, nullptr, nullptr, nullptr, nullptr,
-                                                                 nullptr, 0.f, 1.f, 1.f, 0);
-    if (d_loss) mlp_loss_kernel<<<1, 1, 0, s>>>(T.S.loss_part, B / 64, B, d_loss);
-    MBR_HIP(hipGetLastError());
+    float *part = nullptr;
+    int dev = 0;
+    MBR_TRY(static_scratch(1, &part, &dev));
+    // The call waits for its work, so whoever holds the lock has the scratch to
+    // itself; a call that comes meanwhile (another thread) allocates its own.
+    std::unique_lock<std::mutex> lk(g_shared_mu[dev], std::try_to_lock);
+    DevBuf own;
+    if (!lk.owns_lock()) {
+        MBR_TRY(own.alloc(part_bytes(partials_of(B))));
+        part = own.as<float>();
+    }
+    const mbr_status st = batch_sum(d_params, B, d_q, d_tgt, d_grad, d_loss, part, s);
     MBR_HIP(hipStreamSynchronize(s));
-    return MBR_OK;
+    return st;
 }
 
 mbr_status mbr_mlp_gradients_noalloc(const float *d_params, const uint32_t *d_q, const float *d_tgt, int32_t B,
@@ -1027,23 +1066,10 @@ mbr_status mbr_mlp_gradients_noalloc(const float *d_params, const uint32_t *d_q,
     if (B <= 0 || B % 64 != 0) MBR_FAIL(MBR_EINVAL, "B=%d must be a positive multiple of 64", B);
     if (B > kStaticBatch)
         MBR_FAIL(MBR_ERANGE, "B=%d exceeds the %d samples of the static scratch", B, kStaticBatch);
-    unsigned char *base = nullptr;
-    MBR_TRY(static_scratch(&base));
-    hipStream_t s = as_stream(stream);
-    float *wr = reinterpret_cast<float *>(base + kStWr);
-    uint16_t *wb = reinterpret_cast<uint16_t *>(base + kStWb);
-    const TrainScratch S = carve(reinterpret_cast<float *>(base + kStAct), (size_t)B);
-    float *part = reinterpret_cast<float *>(base + kStPart);
+    float *part = nullptr;
+    MBR_TRY(static_scratch(0, &part, nullptr));
     // every scratch word the kernels read is written first in this call
-    mlp_round_kernel<<<(kParams + 255) / 256, 256, 0, s>>>(d_params, wr, wb);
-    mlp_fwd_bwd_kernel<<<(B + 63) / 64, 64, 0, s>>>(wr, B, d_q, d_tgt, nullptr, 0, 0, 0, S);
-    mlp_grad_part_kernel<<<(B + kChunk - 1) / kChunk, 256, 0, s>>>(B, S, part);
-    mlp_reduce_adam_kernel<<<(kParams + 255) / 256, 256, 0, s>>>(part, (B + kChunk - 1) / kChunk, d_grad, nullptr,
-                                                                 nullptr, nullptr, nullptr, nullptr, 0.f, 1.f, 1.f,
-                                                                 0);
-    if (d_loss) mlp_loss_kernel<<<1, 1, 0, s>>>(S.loss_part, B / 64, B, d_loss);
-    MBR_HIP(hipGetLastError());
-    return MBR_OK;
+    return batch_sum(d_params, B, d_q, d_tgt, d_grad, d_loss, part, as_stream(stream));
 }
 
 }  // extern "C"
