@@ -41,6 +41,7 @@ struct LzDev {
     int32_t *active; // per-sector flag
     int32_t *steps;  // per-sector completed steps
     int32_t *j;      // basis index of the current vector (reorthogonalising path)
+    uint32_t *done;  // counters of the running kernel's finished workgroups (last_workgroup; 0 between kernels)
 };
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -77,6 +78,56 @@ __device__ __forceinline__ double sector_sum(const double *p, uint32_t n, double
     return block_sum(v, red);
 }
 
+// The same sum over partials that other workgroups of this kernel have just
+// written with publish(): read past the caches that may hold older values.
+__device__ __forceinline__ double sector_sum_published(const double *p, uint32_t n, double *red) {
+    auto ld = [&](uint32_t i) { return __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    double v = 0;
+    uint32_t i = threadIdx.x;
+    for (; i + 7 * blockDim.x < n; i += 8 * blockDim.x) {
+        double t[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) t[q] = ld(i + q * blockDim.x);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v += t[q];
+    }
+    for (; i < n; i += blockDim.x) v += ld(i);
+    return block_sum(v, red);
+}
+
+__device__ __forceinline__ void publish(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// True in the workgroup that gets here last of the kernel's gridDim.x: its
+// threads may then read what the others published.  A workgroup's thread 0 has
+// written all it publishes before it calls; it waits until those stores have
+// reached memory before it counts itself.  Counting is in two levels, on 128-byte
+// lines of their own: a thousand workgroups on one counter queue up behind each
+// other for 11 us, on kDoneLines counters for less than 1 us.  All counters
+// are 0 again for the next kernel.
+constexpr uint32_t kDoneLines = 32, kDoneStride = 32;
+constexpr size_t kDoneBytes = (kDoneLines + 1) * kDoneStride * 4;
+
+__device__ __forceinline__ bool count_in(uint32_t *counter, uint32_t of) {
+    const uint32_t n = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n + 1 != of) return false;
+    __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
+__device__ __forceinline__ bool last_workgroup(uint32_t *done) {
+    __shared__ uint32_t is_last;
+    if (threadIdx.x == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const uint32_t line = blockIdx.x % kDoneLines, lines = gridDim.x < kDoneLines ? gridDim.x : kDoneLines;
+        const bool last_of_line = count_in(done + (1 + line) * kDoneStride, (gridDim.x - line + kDoneLines - 1) / kDoneLines);
+        is_last = last_of_line && count_in(done, lines) ? 1u : 0u;
+    }
+    __syncthreads();
+    return is_last != 0;
+}
+
 // alpha_j = c1 * sum(pd); c3 = alpha_j * c1 (coefficient of the stored q_j in w).
 __global__ void lz_alpha(const HvSector *secs, LzDev d, int m, uint32_t s_first) {
     __shared__ double red[kRedWaves];
@@ -90,34 +141,37 @@ __global__ void lz_alpha(const HvSector *secs, LzDev d, int m, uint32_t s_first)
     }
 }
 
-// beta_j = sqrt(sum(pn)); the sector stops at breakdown, at its dimension or at
-// m steps; otherwise the scalars of the next step are prepared.
-__global__ void lz_beta(const HvSector *secs, LzDev d, int m, double tol, int reorth,
-                        uint32_t s_first) {
+// Whether a sector stops after step j: at breakdown, at its dimension or at m
+// steps.
+__device__ __forceinline__ bool lz_stops(const HvSector &sc, const LzDev &d, uint32_t s, int j, int m, double b, double tol) {
+    const double a = d.alpha[(size_t)s * m + j];
+    const double bprev = j > 0 ? d.beta[(size_t)s * m + j - 1] : 0.0;
+    const uint64_t dim = (uint64_t)sc.cup * sc.cdn;
+    return (b <= tol * (fabs(a) + bprev)) || (uint64_t)(j + 1) >= dim || j + 1 >= m;
+}
+
+// Record beta_j = b of sector s and, unless it stops, the scalars of its next
+// step (plain path).  One thread.
+__device__ __forceinline__ void lz_record_beta(const HvSector &sc, const LzDev &d, uint32_t s, int m, double b, double tol) {
+    const int j = d.steps[s];
+    const bool stop = lz_stops(sc, d, s, j, m, b, tol);
+    d.beta[(size_t)s * m + j] = stop ? 0.0 : b;
+    d.steps[s] = j + 1;
+    if (stop) {
+        d.active[s] = 0;
+    } else {
+        d.c2[s] = b * d.c1[s];
+        d.c1[s] = 1.0 / b;
+    }
+}
+
+// beta_j = sqrt(sum(pn)) of every sector (plain path, several sectors).
+__global__ void lz_beta(const HvSector *secs, LzDev d, int m, double tol, uint32_t s_first) {
     __shared__ double red[kRedWaves];
     const uint32_t s = s_first + blockIdx.x;
     if (!d.active[s]) return;
     double sum = sector_sum(d.pn + secs[s].slot0, secs[s].nslots, red);
-    if (threadIdx.x == 0) {
-        const int j = d.steps[s];
-        const double b = sqrt(sum);
-        const double a = d.alpha[(size_t)s * m + j];
-        const double bprev = j > 0 ? d.beta[(size_t)s * m + j - 1] : 0.0;
-        const uint64_t dim = (uint64_t)secs[s].cup * secs[s].cdn;
-        const bool stop = (b <= tol * (fabs(a) + bprev)) || (uint64_t)(j + 1) >= dim || j + 1 >= m;
-        d.beta[(size_t)s * m + j] = stop ? 0.0 : b;
-        d.steps[s] = j + 1;
-        if (stop) {
-            d.active[s] = 0;
-        } else if (reorth) {
-            d.c1[s] = 1.0;
-            d.c2[s] = b;
-            d.c3[s] = 1.0 / b;
-        } else {
-            d.c2[s] = b * d.c1[s];
-            d.c1[s] = 1.0 / b;
-        }
-    }
+    if (threadIdx.x == 0) lz_record_beta(secs[s], d, s, m, sqrt(sum), tol);
 }
 
 // w = u - c q over elements [base, base + rows) of u (in place), returning
@@ -203,17 +257,20 @@ __global__ void __launch_bounds__(kBlock) lz_update(const HvTile *tiles, uint32_
     }
 }
 
-// One sector per launch: lz_alpha folded into lz_update.  Every workgroup
-// forms alpha_j from the sector's partials itself (the same sum in the same
-// order as lz_alpha, so the same bits), workgroup 0 records it, and the
-// update w = u - c3 q follows without a separate launch.
+// One sector per launch: lz_alpha, lz_update and lz_beta in one.  Every
+// workgroup forms alpha_j from the sector's partials itself (the same sum in
+// the same order as lz_alpha, so the same bits), the update w = u - c3 q
+// follows, and the workgroup that finishes last records alpha_j and forms beta_j
+// from the partials of all (again lz_beta's sum).  A kernel of its own
+// for beta cost 4.0 us a step on the L=12 chain (853,776 rows), most of it the
+// launch; here it adds 2.4 us to the update's 8.5.
 template <class T>
 __global__ void __launch_bounds__(kBlock) lz_alpha_update(const HvTile *tiles, uint32_t n_tiles,
                                                           const HvSector *secs, T *__restrict__ u,
                                                           const T *__restrict__ q, LzDev d, int m,
-                                                          uint32_t s) {
+                                                          double tol, uint32_t s) {
     __shared__ double red[kRedWaves];
-    __shared__ double c3s;
+    __shared__ double c3s, sum_s;
     if (!d.active[s]) {
         for (uint32_t ti = blockIdx.x; ti < n_tiles; ti += gridDim.x)
             if (threadIdx.x == 0) d.pn[tiles[ti].slot] = 0.0;
@@ -223,10 +280,7 @@ __global__ void __launch_bounds__(kBlock) lz_alpha_update(const HvTile *tiles, u
     if (threadIdx.x == 0) {
         const double a = d.c1[s] * sum;
         c3s = a * d.c1[s];
-        if (blockIdx.x == 0) {
-            d.alpha[(size_t)s * m + d.steps[s]] = a;
-            d.c3[s] = c3s;
-        }
+        sum_s = sum;
     }
     __syncthreads();
     const T c = (T)c3s;
@@ -237,15 +291,22 @@ __global__ void __launch_bounds__(kBlock) lz_alpha_update(const HvTile *tiles, u
         const uint32_t rows = tl.nblk * sc.cdn;
         const double acc = tile_axpy_norm(u, q, c, base, rows);
         double bs = block_sum(acc, red);
-        if (threadIdx.x == 0) d.pn[tl.slot] = bs;
+        if (threadIdx.x == 0) publish(d.pn + tl.slot, bs);
+    }
+    if (!last_workgroup(d.done)) return;
+    const double norm2 = sector_sum_published(d.pn + secs[s].slot0, secs[s].nslots, red);
+    if (threadIdx.x == 0) {
+        d.alpha[(size_t)s * m + d.steps[s]] = d.c1[s] * sum_s;
+        lz_record_beta(secs[s], d, s, m, sqrt(norm2), tol);
     }
 }
 
-// Per-slot |v|^2 of a vector (start normalisation).
+// Start vector: v0 in the vectors' type to `out` (zeros to `prev` when given),
+// and its |v|^2 per slot.
 template <class T>
-__global__ void __launch_bounds__(kBlock) lz_norm_parts(const HvTile *tiles, uint32_t n_tiles,
-                                                        const HvSector *secs, const T *__restrict__ v,
-                                                        double *parts) {
+__global__ void __launch_bounds__(kBlock) lz_start_vectors(const HvTile *tiles, uint32_t n_tiles,
+                                                           const HvSector *secs, const double *__restrict__ v0,
+                                                           T *__restrict__ out, T *__restrict__ prev, double *parts) {
     __shared__ double red[kRedWaves];
     for (uint32_t ti = blockIdx.x; ti < n_tiles; ti += gridDim.x) {
         const HvTile tl = tiles[ti];
@@ -253,8 +314,12 @@ __global__ void __launch_bounds__(kBlock) lz_norm_parts(const HvTile *tiles, uin
         const uint64_t base = sc.off + (uint64_t)tl.rup0 * sc.cdn;
         const uint32_t rows = tl.nblk * sc.cdn;
         double acc = 0;
+#pragma unroll 4
         for (uint32_t e = threadIdx.x; e < rows; e += blockDim.x) {
-            double w = (double)v[base + e];
+            const T v = (T)v0[base + e];
+            out[base + e] = v;
+            if (prev) prev[base + e] = (T)0;
+            const double w = (double)v;
             acc += w * w;
         }
         double s = block_sum(acc, red);
@@ -276,19 +341,6 @@ __global__ void lz_start_scalars(const HvSector *secs, LzDev d, int reorth) {
         d.c3[s] = nrm > 0 ? 1.0 / nrm : 0.0;
         if (s == 0) *d.j = 0;
     }
-}
-
-template <class T>
-__global__ void lz_convert(const double *__restrict__ v0, T *__restrict__ out, uint64_t n) {
-    uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += stride)
-        out[i] = (T)v0[i];
-}
-
-template <class T>
-__global__ void lz_fill_zero(T *__restrict__ out, uint64_t n) {
-    uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += stride) out[i] = (T)0;
 }
 
 // The reorthogonalising kernels move the rows of a tile (or merged group) as
@@ -333,52 +385,126 @@ struct Span {
     }
 };
 
-// dst = c3 * w per sector.  With use_j the destination is basis vector j+1
-// (v_{j+1} = w / beta_j, only sectors still running); otherwise vector 0.
+// dst = c w over a tile's rows.
 template <class T>
-__global__ void __launch_bounds__(kBlock) lz_scale_into(const HvTile *tiles, uint32_t n_tiles,
-                                                        const HvSector *secs, const T *__restrict__ w,
-                                                        T *__restrict__ V, uint64_t ld, LzDev d,
-                                                        int use_j) {
-    const int64_t j = use_j ? (int64_t)(*d.j) + 1 : 0;
-    T *dst = V + (uint64_t)j * ld;
-    for (uint32_t ti = blockIdx.x; ti < n_tiles; ti += gridDim.x) {
-        const HvTile tl = tiles[ti];
-        if (use_j && !d.active[tl.sector]) continue;
-        const HvSector sc = secs[tl.sector];
-        const T c = (T)d.c3[tl.sector];
-        const Span<T> sp(sc.off + (uint64_t)tl.rup0 * sc.cdn, tl.nblk * sc.cdn);
-        if (threadIdx.x < sp.left) {
-            const uint64_t r = sp.leftover(threadIdx.x);
-            dst[r] = w[r] * c;
-        }
-        for (uint32_t i = threadIdx.x; i < sp.nv; i += blockDim.x) {
-            const uint64_t r = sp.a0 + (uint64_t)i * Pack<T>::n;
-            Pack<T> v = ld_pack(w + r);
+__device__ __forceinline__ void tile_scale(const T *__restrict__ w, T *__restrict__ dst, T c, const Span<T> &sp) {
+    if (threadIdx.x < sp.left) {
+        const uint64_t r = sp.leftover(threadIdx.x);
+        dst[r] = w[r] * c;
+    }
+    for (uint32_t i = threadIdx.x; i < sp.nv; i += blockDim.x) {
+        const uint64_t r = sp.a0 + (uint64_t)i * Pack<T>::n;
+        Pack<T> v = ld_pack(w + r);
 #pragma unroll
-            for (int e = 0; e < Pack<T>::n; ++e) v.e[e] *= c;
-            st_pack(dst + r, v);
-        }
+        for (int e = 0; e < Pack<T>::n; ++e) v.e[e] *= c;
+        st_pack(dst + r, v);
     }
 }
 
-// Reorthogonalising path: w = u - c3 v_j in place, then per-slot partials of
-// <v_k, w> for k = 0..j (classical Gram-Schmidt coefficients).  The basis
+// First basis vector: c3 * w per sector.
+template <class T>
+__global__ void __launch_bounds__(kBlock) lz_first(const HvTile *tiles, uint32_t n_tiles, const HvSector *secs,
+                                                   const T *__restrict__ w, T *__restrict__ V, LzDev d) {
+    for (uint32_t ti = blockIdx.x; ti < n_tiles; ti += gridDim.x) {
+        const HvTile tl = tiles[ti];
+        const HvSector sc = secs[tl.sector];
+        tile_scale<T>(w, V, (T)d.c3[tl.sector], Span<T>(sc.off + (uint64_t)tl.rup0 * sc.cdn, tl.nblk * sc.cdn));
+    }
+}
+
+// End of a reorthogonalising step: beta_j = |w| of every sector and, where it
+// goes on, v_{j+1} = w / beta_j.  Every workgroup sums its sector's partials
+// itself, always in the same order; the one with the sector's first group
+// records beta_j and the step.  A sector that stops is skipped by all its
+// workgroups, whether they see the flag that the recording one clears or find
+// the same condition, so the flag needs no order between them.  The basis index
+// is read by all and moved on by the last workgroup, when `advance` is set.
+template <class T>
+__global__ void __launch_bounds__(kBlock) lz_next(const HvTile *tiles, uint32_t n_tiles, const HvSector *secs,
+                                                  const T *__restrict__ w, T *__restrict__ V, uint64_t ld, LzDev d, int m,
+                                                  double tol, int advance) {
+    __shared__ double red[kRedWaves];
+    __shared__ double norm2;
+    __shared__ int active;
+    const int j = *d.j;
+    for (uint32_t ti = blockIdx.x; ti < n_tiles; ti += gridDim.x) {
+        const HvTile tl = tiles[ti];
+        const uint32_t s = tl.sector;
+        const HvSector sc = secs[s];
+        __syncthreads();  // the shared values' readers of the tile before are done
+        if (threadIdx.x == 0) active = d.active[s];  // one view of the flag for the whole workgroup
+        __syncthreads();
+        if (!active) continue;
+        const double sum = sector_sum(d.pn + sc.slot0, sc.nslots, red);
+        if (threadIdx.x == 0) norm2 = sum;
+        __syncthreads();
+        const double b = sqrt(norm2);
+        const bool stop = lz_stops(sc, d, s, j, m, b, tol);
+        if (tl.slot == sc.slot0 && threadIdx.x == 0) {
+            d.beta[(size_t)s * m + j] = stop ? 0.0 : b;
+            d.steps[s] = j + 1;
+            if (stop) {
+                d.active[s] = 0;
+            } else {
+                d.c1[s] = 1.0;
+                d.c2[s] = b;
+            }
+        }
+        if (!stop) tile_scale<T>(w, V + (uint64_t)(j + 1) * ld, (T)(1.0 / b), Span<T>(sc.off + (uint64_t)tl.rup0 * sc.cdn, tl.nblk * sc.cdn));
+    }
+    __syncthreads();
+    if (advance && last_workgroup(d.done) && threadIdx.x == 0 && j < m) *d.j = j + 1;
+}
+
+// Reorthogonalising path: alpha_j from the product's partials (summed by every
+// workgroup in the order of lz_alpha; the one with the sector's first group
+// records it), w = u - alpha_j v_j in place, then per-slot partials of <v_k, w>
+// for k = 0..j (classical Gram-Schmidt coefficients).  The basis
 // vectors are taken kKc at a time: one pass over the tile's rows loads a pack
 // of each of them together (a short last chunk repeats its last vector, whose
 // sums are then dropped) and one block reduction serves all kKc sums.  Each
 // sum is fixed-order: per lane (its leftover row, then its packs in order,
-// element by element), then across the wave, then over the waves in order.
+// element by element), then across the wave (wave_sum8), then over the waves in
+// order.
 constexpr int kKc = 8;
-constexpr uint64_t kGroupRows = 4096;  // rows per merged group of the Gram-Schmidt kernels
+constexpr uint32_t kFoldGroups = 64;   // groups per sector up to which lz_subtract sums the coefficients itself
+
+// Rows per merged group of the batched Gram-Schmidt kernels: 4096, so that one
+// block reduction serves many rows, but fewer where that would leave the chip
+// short of workgroups (eight per CU wanted).  Ten sites, 1,048,576 rows, 40
+// steps: 4.91 ms with 4,096 rows a group, 4.35 with 2,048, 4.31 with 512.
+inline uint64_t group_rows(uint64_t total) {
+    const uint64_t g = total / ((uint64_t)device_cu_count() * 8);
+    return g < 512 ? 512 : g > 4096 ? 4096 : g;
+}
+
+// Sums of eight values over the wave: three exchanges that halve the values a
+// lane still holds, then three on the one left, ten shuffles where eight
+// separate sums take 48.  Lane l < 8 ends with the sum of value
+// wave_sum8_index(l).
+__device__ __forceinline__ int wave_sum8_index(int lane) { return 4 * (lane & 1) + 2 * ((lane >> 1) & 1) + ((lane >> 2) & 1); }
+
+__device__ __forceinline__ double wave_sum8(const double (&v)[kKc]) {
+    static_assert(kKc == 8, "three halvings");
+    const int lane = threadIdx.x & 63;
+    double a[4], b[2], c;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = ((lane & 1) ? v[4 + i] : v[i]) + __shfl_xor((lane & 1) ? v[i] : v[4 + i], 1, 64);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) b[i] = ((lane & 2) ? a[2 + i] : a[i]) + __shfl_xor((lane & 2) ? a[i] : a[2 + i], 2, 64);
+    c = ((lane & 4) ? b[1] : b[0]) + __shfl_xor((lane & 4) ? b[0] : b[1], 4, 64);
+    for (int o = 8; o < 64; o <<= 1) c += __shfl_xor(c, o, 64);
+    return c;
+}
 
 template <class T>
 __global__ void __launch_bounds__(kBlock) lz_update_dots(const HvTile *tiles, uint32_t n_tiles,
-                                                         const HvSector *secs, T *__restrict__ W,
+                                                         const HvSector *secs, const HvSector *hsecs, T *__restrict__ W,
                                                          const T *__restrict__ V, uint64_t ld,
                                                          int m, LzDev d) {
     constexpr int n = Pack<T>::n;
     __shared__ double red[kKc][kRedWaves];
+    __shared__ double alpha_s;
     const int j = *d.j;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     for (uint32_t ti = blockIdx.x; ti < n_tiles; ti += gridDim.x) {
@@ -387,7 +513,13 @@ __global__ void __launch_bounds__(kBlock) lz_update_dots(const HvTile *tiles, ui
         double *pc = d.pc + (size_t)tl.slot * (m + 1);
         const HvSector sc = secs[tl.sector];
         const Span<T> sp(sc.off + (uint64_t)tl.rup0 * sc.cdn, tl.nblk * sc.cdn);
-        const T c = (T)d.c3[tl.sector];
+        const double usum = sector_sum(d.pd + hsecs[tl.sector].slot0, hsecs[tl.sector].nslots, red[0]);
+        if (threadIdx.x == 0) {
+            alpha_s = usum;  // <v_j, u>, v_j being normalised
+            if (tl.slot == sc.slot0) d.alpha[(size_t)tl.sector * m + j] = usum;
+        }
+        __syncthreads();
+        const T c = (T)alpha_s;
         const T *vj = V + (uint64_t)j * ld;
         const bool has_left = threadIdx.x < sp.left;
         const uint64_t rl = has_left ? sp.leftover(threadIdx.x) : 0;
@@ -425,12 +557,9 @@ __global__ void __launch_bounds__(kBlock) lz_update_dots(const HvTile *tiles, ui
 #pragma unroll
                     for (int e = 0; e < n; ++e) acc[q] += (double)v[q].e[e] * (double)x.e[e];
             }
-#pragma unroll
-            for (int q = 0; q < kKc; ++q) acc[q] = wave_sum(acc[q]);
+            const double wsum = wave_sum8(acc);
             __syncthreads();  // the previous chunk's readers of red are done
-            if (lane == 0)
-#pragma unroll
-                for (int q = 0; q < kKc; ++q) red[q][wv] = acc[q];
+            if (lane < kKc) red[wave_sum8_index(lane)][wv] = wsum;
             __syncthreads();
             if ((int)threadIdx.x < nk) {
                 double sum = 0;
@@ -483,11 +612,13 @@ __global__ void __launch_bounds__(kCgsBlock) lz_reduce_cgs(const HvSector *secs,
     }
 }
 
-// w -= sum_k c_k v_k (fp64 accumulation, k in order), then partial |w|^2.  The
+// w -= sum_k c_k v_k (fp64 accumulation, k in order), then partial |w|^2.  With
+// FOLD (few groups per sector) a block sums the c_k from the groups' partials
+// itself, in group order, instead of reading lz_reduce_cgs's.  The
 // block stages c_0..c_j in LDS followed by kKc - 1 zeros, so every chunk of kKc
 // basis vectors is whole: a vector past j is read at index j and subtracted
 // with coefficient 0, which leaves w unchanged.  Dynamic LDS: (m + kKc) doubles.
-template <class T>
+template <class T, bool FOLD>
 __global__ void __launch_bounds__(kBlock) lz_subtract(const HvTile *tiles, uint32_t n_tiles,
                                                       const HvSector *secs, T *__restrict__ W,
                                                       const T *__restrict__ V, uint64_t ld, int m,
@@ -507,7 +638,18 @@ __global__ void __launch_bounds__(kBlock) lz_subtract(const HvTile *tiles, uint3
         const Span<T> sp(sc.off + (uint64_t)tl.rup0 * sc.cdn, tl.nblk * sc.cdn);
         const double *c = d.cgs + (size_t)tl.sector * (m + 1);
         __syncthreads();  // the previous tile's readers of cs are done
-        for (int k = threadIdx.x; k < kend; k += blockDim.x) cs[k] = k <= j ? c[k] : 0.0;
+        if constexpr (FOLD) {
+            const double *pc = d.pc + (size_t)sc.slot0 * (m + 1);
+            for (int k = threadIdx.x; k < kend; k += blockDim.x) {
+                double v = 0;
+                if (k <= j)
+#pragma unroll 8
+                    for (uint32_t i = 0; i < sc.nslots; ++i) v += pc[(size_t)i * (m + 1) + k];
+                cs[k] = v;
+            }
+        } else {
+            for (int k = threadIdx.x; k < kend; k += blockDim.x) cs[k] = k <= j ? c[k] : 0.0;
+        }
         __syncthreads();
         double acc = 0;
         if (threadIdx.x < sp.left) {
@@ -554,57 +696,109 @@ __global__ void lz_advance(LzDev d, int m) {
 }
 
 // ---------------------------------------------------------------- tridiagonal
+// 1 / q to the last bit or the one beside it, by two Newton steps from the
+// hardware estimate: half the chain of a division.
+__device__ __forceinline__ double recip(double q) {
+    double r = __builtin_amdgcn_rcp(q);
+    r = __builtin_fma(__builtin_fma(-q, r, 1.0), r, r);
+    return __builtin_fma(__builtin_fma(-q, r, 1.0), r, r);
+}
+
 // Number of eigenvalues below x: negative pivots of the LDL^T factorisation of
-// T - x I (Sturm sequence).
-__device__ __forceinline__ int sturm_count(const double *a, const double *b, int n, double x) {
+// T - x I (Sturm sequence), b2 the squared off-diagonal.  Pivots smaller than
+// 1e-290 count as that, with their sign (a zero as negative), so that their
+// reciprocals stay finite.
+__device__ __forceinline__ int sturm_count(const double *a, const double *b2, int n, double x) {
     int c = 0;
     double q = a[0] - x;
     if (q < 0) ++c;
     for (int i = 1; i < n; ++i) {
-        const double qq = (q == 0.0) ? -1e-300 : q;
-        q = (a[i] - x) - b[i - 1] * b[i - 1] / qq;
+        const double qq = fabs(q) < 1e-290 ? (q > 0 ? 1e-290 : -1e-290) : q;
+        q = __builtin_fma(-b2[i - 1], recip(qq), a[i] - x);
         if (q < 0) ++c;
     }
     return c;
 }
 
-// One wave per matrix: 64-way multisection of the Gershgorin interval, keeping
-// the sub-interval where the Sturm count first reaches one.
-__global__ void tridiag_lowest_kernel(const double *alpha, const double *beta, const int32_t *len,
-                                      int ld, int nb, double *e0) {
+// The same count with the off-diagonal squared on the way.
+__device__ __forceinline__ int sturm_count_far(const double *a, const double *b, int n, double x) {
+    int c = 0;
+    double q = a[0] - x;
+    if (q < 0) ++c;
+    for (int i = 1; i < n; ++i) {
+        const double qq = fabs(q) < 1e-290 ? (q > 0 ? 1e-290 : -1e-290) : q;
+        q = __builtin_fma(-(b[i - 1] * b[i - 1]), recip(qq), a[i] - x);
+        if (q < 0) ++c;
+    }
+    return c;
+}
+
+// One workgroup per matrix: multisection of the Gershgorin interval, a lane a
+// point, keeping the sub-interval where the Sturm count first reaches one.  The
+// matrix is staged in LDS as far as it fits.  Bound by the serial chain of the
+// counts: 40 steps, 37 us with a wave and divisions, 23 us so.
+constexpr int kTriBlock = 256;
+constexpr int kTriLds = 2048;
+
+__global__ void __launch_bounds__(kTriBlock) tridiag_lowest_kernel(const double *alpha, const double *beta, const int32_t *len,
+                                                                   int ld, int nb, double *e0) {
+    __shared__ double sa[kTriLds], sb2[kTriLds], lo_w[kTriBlock / 64], hi_w[kTriBlock / 64];
+    __shared__ int first_w[kTriBlock / 64];
     const int bi = blockIdx.x;
     if (bi >= nb) return;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int n = len[bi];
     if (n > ld) n = ld;
     const double *a = alpha + (size_t)bi * ld;
     const double *b = beta + (size_t)bi * ld;
     if (n <= 0) {
-        if (lane == 0) e0[bi] = 0.0;
+        if (threadIdx.x == 0) e0[bi] = 0.0;
         return;
     }
+    const bool staged = n <= kTriLds;
     double lo = a[0], hi = a[0];
-    for (int i = 0; i < n; ++i) {
-        const double r = (i > 0 ? fabs(b[i - 1]) : 0.0) + (i + 1 < n ? fabs(b[i]) : 0.0);
-        lo = fmin(lo, a[i] - r);
-        hi = fmax(hi, a[i] + r);
+    for (int i = threadIdx.x; i < n; i += kTriBlock) {
+        const double d = a[i], bl = i > 0 ? fabs(b[i - 1]) : 0.0, br = i + 1 < n ? fabs(b[i]) : 0.0;
+        lo = fmin(lo, d - (bl + br));
+        hi = fmax(hi, d + (bl + br));
+        if (staged) {
+            sa[i] = d;
+            sb2[i] = i + 1 < n ? b[i] * b[i] : 0.0;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, o, 64));
+        hi = fmax(hi, __shfl_xor(hi, o, 64));
+    }
+    if (lane == 0) {
+        lo_w[w] = lo;
+        hi_w[w] = hi;
+    }
+    __syncthreads();
+    for (int k = 0; k < kTriBlock / 64; ++k) {
+        lo = fmin(lo, lo_w[k]);
+        hi = fmax(hi, hi_w[k]);
     }
     const double pad = 1e-12 * fmax(1.0, fmax(fabs(lo), fabs(hi)));
     lo -= pad;
     hi += pad;
     for (int it = 0; it < 40; ++it) {
         if (!(hi - lo > 4.5e-16 * fmax(fabs(lo), fabs(hi)) + 1e-300)) break;
-        const double h = (hi - lo) / 65.0;
-        const double x = lo + h * (double)(lane + 1);
-        const int c = sturm_count(a, b, n, x);
+        const double h = (hi - lo) / (kTriBlock + 1.0);
+        const double x = lo + h * (double)(threadIdx.x + 1);
+        const int c = staged ? sturm_count(sa, sb2, n, x) : sturm_count_far(a, b, n, x);
         const unsigned long long ball = __ballot(c >= 1);
-        const int first = ball ? (__ffsll((long long)ball) - 1) : 64;
+        __syncthreads();  // first_w's readers of the iteration before are done
+        if (lane == 0) first_w[w] = ball ? 64 * w + (__ffsll((long long)ball) - 1) : kTriBlock;
+        __syncthreads();
+        int first = kTriBlock;
+        for (int k = kTriBlock / 64 - 1; k >= 0; --k) first = first_w[k] < kTriBlock ? first_w[k] : first;
         const double nlo = lo + h * (double)first;
-        const double nhi = (first == 64) ? hi : lo + h * (double)(first + 1);
+        const double nhi = (first == kTriBlock) ? hi : lo + h * (double)(first + 1);
         lo = nlo;
         hi = nhi;
     }
-    if (lane == 0) e0[bi] = 0.5 * (lo + hi);
+    if (threadIdx.x == 0) e0[bi] = 0.5 * (lo + hi);
 }
 
 }  // namespace
@@ -626,23 +820,31 @@ struct mbr_lanczos {
     DevBuf d_rtiles, d_rsecs;
     std::vector<uint32_t> rt0, rnt;
     uint32_t n_rtiles = 0;
+    bool fold_cgs = false;  // few enough groups per sector for lz_subtract to sum their partials
     DevBuf bufA, bufB, basis, work;
-    DevBuf alpha, beta, c1, c2, c3, pd, pn, pc, cgs, norm0, active, steps, jcount, e0;
+    DevBuf alpha, beta, c1, c2, c3, pd, pn, pc, cgs, norm0, active, steps, jcount, done, e0;
     LzDev dev{};
     int parity = 0;  // plain path: 0 -> q_j in A, 1 -> q_j in B
     bool started = false;
     uint32_t generation = 0;  // Hamiltonian launch shape the tiles were taken from
     unsigned grid = 0;
-    hipGraphExec_t graph[2] = {nullptr, nullptr};
+    hipGraphExec_t graph[2] = {nullptr, nullptr};  // one step, by parity
+    hipGraphExec_t graph_many = nullptr;           // kGraphSteps steps from parity 0
     hipStream_t cap_stream = nullptr;
     ~mbr_lanczos() {
         for (auto &g : graph)
             if (g) (void)hipGraphExecDestroy(g);
+        if (graph_many) (void)hipGraphExecDestroy(graph_many);
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
     }
 };
 
 namespace {
+
+// Steps of a graph when many are asked for (even, so that the plain path's two
+// vectors end where they began): the pause between two graphs costs as much as
+// a small kernel (40 steps of the L=12 chain 1.56 ms step by step, 1.38 so).
+constexpr int kGraphSteps = 8;
 
 double default_tol(const mbr_lanczos *lz) {
     if (lz->o.breakdown_tol > 0) return lz->o.breakdown_tol;
@@ -672,12 +874,12 @@ mbr_status enqueue_plain(mbr_lanczos *lz, int par, uint32_t s0, uint32_t nsec, u
     MBR_TRY(hubbard_launch(lz->h, X, P, ep, s));
     const unsigned g = std::min<unsigned>(lz->grid, nt);
     if (nsec == 1) {
-        lz_alpha_update<T><<<g, kBlock, 0, s>>>(tiles, nt, secs, P, X, lz->dev, lz->m, s0);
+        lz_alpha_update<T><<<g, kBlock, 0, s>>>(tiles, nt, secs, P, X, lz->dev, lz->m, default_tol(lz), s0);
     } else {
         lz_alpha<<<nsec, kBlock, 0, s>>>(secs, lz->dev, lz->m, s0);
         lz_update<T><<<g, kBlock, 0, s>>>(tiles, nt, secs, P, X, lz->dev);
+        lz_beta<<<nsec, kBlock, 0, s>>>(secs, lz->dev, lz->m, default_tol(lz), s0);
     }
-    lz_beta<<<nsec, kBlock, 0, s>>>(secs, lz->dev, lz->m, default_tol(lz), 0, s0);
     MBR_HIP(hipGetLastError());
     return MBR_OK;
 }
@@ -711,13 +913,15 @@ mbr_status enqueue_reorth(mbr_lanczos *lz, uint32_t s0, uint32_t nsec, uint32_t 
     // unequal size; per sector: the tile grid of the other kernels
     const unsigned g = all ? std::max<unsigned>(1, std::min<unsigned>(gn, 1u << 20))
                            : std::min<unsigned>(lz->grid, gn);
-    lz_alpha<<<nsec, kBlock, 0, s>>>(secs, lz->dev, lz->m, s0);
-    lz_update_dots<T><<<g, kBlock, 0, s>>>(groups, gn, rsecs, W, V, lz->ld, lz->m, lz->dev);
-    lz_reduce_cgs<<<nsec, kCgsBlock, 0, s>>>(rsecs, lz->dev, lz->m, s0);
-    lz_subtract<T><<<g, kBlock, (size_t)(lz->m + kKc) * sizeof(double), s>>>(groups, gn, rsecs, W, V, lz->ld,
-                                                                           lz->m, lz->dev);
-    lz_beta<<<nsec, kBlock, 0, s>>>(rsecs, lz->dev, lz->m, default_tol(lz), 1, s0);
-    lz_scale_into<T><<<g, kBlock, 0, s>>>(groups, gn, rsecs, W, V, lz->ld, lz->dev, 1);
+    lz_update_dots<T><<<g, kBlock, 0, s>>>(groups, gn, rsecs, secs, W, V, lz->ld, lz->m, lz->dev);
+    const size_t lds = (size_t)(lz->m + kKc) * sizeof(double);
+    if (lz->fold_cgs) {
+        lz_subtract<T, true><<<g, kBlock, lds, s>>>(groups, gn, rsecs, W, V, lz->ld, lz->m, lz->dev);
+    } else {
+        lz_reduce_cgs<<<nsec, kCgsBlock, 0, s>>>(rsecs, lz->dev, lz->m, s0);
+        lz_subtract<T, false><<<g, kBlock, lds, s>>>(groups, gn, rsecs, W, V, lz->ld, lz->m, lz->dev);
+    }
+    lz_next<T><<<g, kBlock, 0, s>>>(groups, gn, rsecs, W, V, lz->ld, lz->dev, lz->m, default_tol(lz), all ? 1 : 0);
     MBR_HIP(hipGetLastError());
     return MBR_OK;
 }
@@ -736,7 +940,7 @@ mbr_status enqueue_step(mbr_lanczos *lz, int par, hipStream_t s) {
             else MBR_TRY(enqueue_plain<T>(lz, par, si, 1, sc.slot0, sc.nslots, false, s));
         }
     }
-    if (reorth) {
+    if (reorth && !lz->o.batched) {
         lz_advance<<<1, 1, 0, s>>>(lz->dev, lz->m);
         MBR_HIP(hipGetLastError());
     }
@@ -747,18 +951,20 @@ mbr_status step_any(mbr_lanczos *lz, int par, hipStream_t s) {
     return lz->prec == MBR_F64 ? enqueue_step<double>(lz, par, s) : enqueue_step<float>(lz, par, s);
 }
 
-mbr_status capture(mbr_lanczos *lz, int par) {
+// A graph of `steps` steps from parity `par`.
+mbr_status capture(mbr_lanczos *lz, int par, int steps, hipGraphExec_t *out) {
     if (!lz->cap_stream) MBR_HIP(hipStreamCreateWithFlags(&lz->cap_stream, hipStreamNonBlocking));
     hipGraph_t g = nullptr;
     MBR_HIP(hipStreamBeginCapture(lz->cap_stream, hipStreamCaptureModeThreadLocal));
-    mbr_status st = step_any(lz, par, lz->cap_stream);
+    mbr_status st = MBR_OK;
+    for (int i = 0; i < steps && st == MBR_OK; ++i) st = step_any(lz, lz->o.reorth ? par : (par + i) & 1, lz->cap_stream);
     hipError_t e = hipStreamEndCapture(lz->cap_stream, &g);
     if (st != MBR_OK) {
         if (g) (void)hipGraphDestroy(g);
         return st;
     }
     if (e != hipSuccess) MBR_FAIL(MBR_EHIP, "graph capture: %s", hipGetErrorString(e));
-    e = hipGraphInstantiate(&lz->graph[par], g, nullptr, nullptr, 0);
+    e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) MBR_FAIL(MBR_EHIP, "graph instantiate: %s", hipGetErrorString(e));
     return MBR_OK;
@@ -768,16 +974,12 @@ template <class T>
 mbr_status lz_start_t(mbr_lanczos *lz, const double *v0, hipStream_t s) {
     const HvSector *secs = lz->d_secs.as<HvSector>();
     const HvTile *tiles = lz->d_tiles_slot.as<HvTile>();
-    const unsigned eg = (unsigned)std::min<uint64_t>((lz->total + kBlock - 1) / kBlock, 8192);
     const bool reorth = lz->o.reorth != 0;
     T *X = reorth ? lz->work.as<T>() : lz->bufA.as<T>();
-    lz_convert<T><<<eg, kBlock, 0, s>>>(v0, X, lz->total);
-    if (!reorth) lz_fill_zero<T><<<eg, kBlock, 0, s>>>(lz->bufB.as<T>(), lz->total);
-    lz_norm_parts<T><<<lz->grid, kBlock, 0, s>>>(tiles, lz->n_slots, secs, X, lz->dev.pn);
+    lz_start_vectors<T><<<lz->grid, kBlock, 0, s>>>(tiles, lz->n_slots, secs, v0, X, reorth ? nullptr : lz->bufB.as<T>(), lz->dev.pn);
     lz_start_scalars<<<lz->ns, kBlock, 0, s>>>(secs, lz->dev, reorth ? 1 : 0);
     if (reorth)
-        lz_scale_into<T><<<lz->grid, kBlock, 0, s>>>(tiles, lz->n_slots, secs, X, lz->basis.as<T>(),
-                                                      lz->ld, lz->dev, 0);
+        lz_first<T><<<lz->grid, kBlock, 0, s>>>(tiles, lz->n_slots, secs, X, lz->basis.as<T>(), lz->dev);
     MBR_HIP(hipGetLastError());
     return MBR_OK;
 }
@@ -814,7 +1016,7 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
         // reduction per group and basis vector instead of one per tile.
         // Per-sector launches keep the tiles (a lone sector needs them all to
         // fill the GPU).
-        const uint64_t grow = o->batched ? kGroupRows : 0;
+        const uint64_t grow = o->batched ? group_rows(lz->total) : 0;
         std::vector<HvTile> groups;
         std::vector<HvSector> rsecs = lz->secs;
         lz->rt0.assign(lz->ns, 0);
@@ -837,6 +1039,9 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
             rsecs[si].nslots = lz->rnt[si];
         }
         lz->n_rtiles = (uint32_t)groups.size();
+        uint32_t most = 0;
+        for (uint32_t g : lz->rnt) most = std::max(most, g);
+        lz->fold_cgs = most <= kFoldGroups;
         MBR_TRY(upload(lz->d_rtiles, groups.data(), groups.size() * sizeof(HvTile), s));
         MBR_TRY(upload(lz->d_rsecs, rsecs.data(), rsecs.size() * sizeof(HvSector), s));
     }
@@ -863,12 +1068,14 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
     MBR_TRY(lz->active.alloc(ns * 4));
     MBR_TRY(lz->steps.alloc(ns * 4));
     MBR_TRY(lz->jcount.alloc(8));
+    MBR_TRY(lz->done.alloc(kDoneBytes));
     MBR_TRY(lz->e0.alloc(ns * 8));
     MBR_HIP(hipMemset(lz->alpha.p, 0, ns * m * 8));
     MBR_HIP(hipMemset(lz->beta.p, 0, ns * m * 8));
     MBR_HIP(hipMemset(lz->active.p, 0, ns * 4));
     MBR_HIP(hipMemset(lz->steps.p, 0, ns * 4));
     MBR_HIP(hipMemset(lz->jcount.p, 0, 8));
+    MBR_HIP(hipMemset(lz->done.p, 0, kDoneBytes));
     LzDev &d = lz->dev;
     d.alpha = lz->alpha.as<double>();
     d.beta = lz->beta.as<double>();
@@ -883,6 +1090,7 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
     d.active = lz->active.as<int32_t>();
     d.steps = lz->steps.as<int32_t>();
     d.j = lz->jcount.as<int32_t>();
+    d.done = lz->done.as<uint32_t>();
     lz->grid = (unsigned)std::min<uint64_t>(lz->n_slots, (uint64_t)device_cu_count() * 8);
     *out = lz.release();
     return MBR_OK;
@@ -905,15 +1113,24 @@ mbr_status mbr_lanczos_step(mbr_lanczos *lz, int32_t nsteps, void *stream) {
         MBR_FAIL(MBR_EINVAL, "the Hamiltonian's launch shape changed after this Lanczos handle was created");
     hipStream_t s = as_stream(stream);
     const bool reorth = lz->o.reorth != 0;
-    for (int i = 0; i < nsteps; ++i) {
+    // several steps per graph where a step is a handful of kernels (one launch set for all sectors, or few sectors)
+    const bool many = lz->o.use_graph && (lz->o.batched || lz->ns <= 4);
+    for (int i = 0; i < nsteps;) {
+        if (many && lz->parity == 0 && nsteps - i >= kGraphSteps) {
+            if (!lz->graph_many) MBR_TRY(capture(lz, 0, kGraphSteps, &lz->graph_many));
+            MBR_HIP(hipGraphLaunch(lz->graph_many, s));
+            i += kGraphSteps;
+            continue;
+        }
         const int par = reorth ? 0 : lz->parity;
         if (lz->o.use_graph) {
-            if (!lz->graph[par]) MBR_TRY(capture(lz, par));
+            if (!lz->graph[par]) MBR_TRY(capture(lz, par, 1, &lz->graph[par]));
             MBR_HIP(hipGraphLaunch(lz->graph[par], s));
         } else {
             MBR_TRY(step_any(lz, par, s));
         }
         if (!reorth) lz->parity ^= 1;
+        ++i;
     }
     return MBR_OK;
 }
@@ -921,7 +1138,7 @@ mbr_status mbr_lanczos_step(mbr_lanczos *lz, int32_t nsteps, void *stream) {
 mbr_status mbr_lanczos_result(mbr_lanczos *lz, double *e0, int32_t *steps_done, void *stream) {
     if (!lz) MBR_FAIL(MBR_EINVAL, "null handle");
     hipStream_t s = as_stream(stream);
-    tridiag_lowest_kernel<<<lz->ns, 64, 0, s>>>(lz->dev.alpha, lz->dev.beta, lz->dev.steps, lz->m,
+    tridiag_lowest_kernel<<<lz->ns, kTriBlock, 0, s>>>(lz->dev.alpha, lz->dev.beta, lz->dev.steps, lz->m,
                                                 lz->ns, lz->e0.as<double>());
     MBR_HIP(hipGetLastError());
     if (e0) MBR_HIP(hipMemcpyAsync(e0, lz->e0.p, lz->ns * 8, hipMemcpyDeviceToHost, s));
@@ -950,7 +1167,7 @@ mbr_status mbr_tridiag_lowest(const double *d_alpha, const double *d_beta, const
     if (n_batch < 0 || ld < 1) MBR_FAIL(MBR_EINVAL, "ld=%d n_batch=%d", ld, n_batch);
     if (n_batch == 0) return MBR_OK;
     if (!d_alpha || !d_beta || !d_len || !d_e0) MBR_FAIL(MBR_EINVAL, "null pointer");
-    tridiag_lowest_kernel<<<n_batch, 64, 0, as_stream(stream)>>>(d_alpha, d_beta, d_len, ld, n_batch,
+    tridiag_lowest_kernel<<<n_batch, kTriBlock, 0, as_stream(stream)>>>(d_alpha, d_beta, d_len, ld, n_batch,
                                                                  d_e0);
     MBR_HIP(hipGetLastError());
     return MBR_OK;
