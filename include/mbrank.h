@@ -199,13 +199,13 @@ mbr_status mbr_build_trie(const mbr_sector *s, int32_t k, mbr_ranker **out, void
 
 /* Bitmap trie (the radix-2^k trie of Sec. IV in a GPU layout): chunks
  * dispatched from the most significant end (the top chunk holds M mod k bits
- * when k does not divide M), every node one record of a 32-bit base, for
- * k >= 6 the set-bit counts before each 32-bit word of the map (one byte
- * each), and a 2^k-bit map of the chunk values that occur under it: 8, 16, 32
- * or 64 bytes (k <= 5, 6, 7, 8; the same size on every level) aligned to its
- * size.  The child for chunk value c is
- * record base + (set bits below c) of the next level; at the last level that
- * count gives the rank (base = position of the node's first member).  A clear
+ * when k does not divide M), every node one record that holds a 2^k-bit map of
+ * the chunk values that occur under it, in 16-byte parts of a 32-bit base and
+ * 96 bits of the map (k <= 5: one part of a base and 32 bits): 8, 16, 32 or 64
+ * bytes (k <= 5, 6, 7, 8; the same size on every level) aligned to its
+ * size.  The child for chunk value c is record base + (set bits below c) of
+ * the next level, counted within c's part; at the last level that count gives
+ * the rank (the first base = position of the node's first member).  A clear
  * bit means the pattern is not in the sector, so no state list is read.
  * k in 1..8; the sector must be non-empty; the ranker keeps a reference to
  * `s` (destroy it first).  Synchronises `stream`. */

@@ -14,11 +14,17 @@
 // Records are 2^s bytes (8 B for k <= 5, 16 B for k = 6, 32 B for k = 7,
 // 64 B for k = 8), the same size on every level (the root's short chunk
 // included, one record), aligned to their size, so a record never straddles a
-// 64-byte line: one line per level and query.  Word 0 is the base; for k >= 6
-// one (k = 6, 7) or two (k = 8) words follow with, in byte w, the set bits of
-// map words 0..w-1; then the 2^k-bit map.  A step reads the base, the prefix
-// byte and one map word, so it costs one popcount whatever k is.
-// The top levels that fit 48 KB are staged in LDS.  With k = 8 the sector
+// 64-byte line: one line per level and query.  Up to k = 5 a record is {base,
+// map}.  From k = 6 on it is made of 16-byte parts, each {child or rank of the
+// part's first chunk value, 96 bits of the map}, so that a step takes one
+// 16-byte load whatever the chunk value, and up to three popcounts.  (A base,
+// prefix bytes and the map apart took two loads a step, and the walks are bound
+// by the rate of their scattered loads: 8,000,003 lookups of 64-bit patterns
+// among 7.1 M states, k = 8, 143 -> 115 us; 2^24 in 32-bit patterns of a sector
+// with 242,250 leaf records 258 -> 215 us.)
+// The top levels that fit 48 KB are staged in LDS; large batches on a trie whose
+// next level fits 144 KB run with one workgroup of 1024 lanes per CU that stages
+// that level too.  With k = 8 the sector
 // M = 32, N = 16 with >= 6 of orbitals 0-7 occupied needs about 4 M leaf
 // records (its packed trie holds 332 M entries).
 #include <algorithm>
@@ -32,6 +38,12 @@ namespace {
 constexpr unsigned kBlock = 256;
 constexpr int kQ = 4;                      // independent walks in flight per lane
 constexpr size_t kLdsBudget = 48 * 1024;   // bytes of top levels staged per workgroup
+constexpr unsigned kWideBlock = 1024;
+constexpr size_t kWideBudget = 144 * 1024; // the same for a workgroup that has a CU to itself
+// Batch from which the wider staging is taken: 8,000,003 lookups (36 orbitals,
+// k = 8, three levels in memory against two) 165 -> 143 us, 1,000,003 25.0 -> 24.1,
+// 300,003 13.0 either way.
+constexpr uint64_t kWideMin = 1 << 19;
 constexpr int kMaxH = 32;
 
 struct BtArgs {
@@ -43,40 +55,55 @@ struct BtArgs {
     uint32_t cmask[kMaxH];    // chunk mask
 };
 
-// Words before the map in a record of RW words: the base, and the prefix
-// bytes of the map words when there is more than one.
-__host__ __device__ constexpr int map_offset(int rw) { return rw == 2 ? 1 : rw == 16 ? 3 : 2; }
+constexpr uint32_t kPartBits = 96;  // chunk values per 16-byte part (records of 4 words and more)
 
-// One level of the walk: the record at `rec` (RW words), chunk value c.
-// Returns whether c occurs; `next` receives base + set bits below c.
-template <int RW>
-__device__ __forceinline__ bool bt_step(const uint32_t *rec, uint32_t c, uint32_t &next) {
-    const uint32_t bit = c & 31;
-    uint32_t base, cw, pre;
-    if constexpr (RW == 2) {
-        const uint2 v = *reinterpret_cast<const uint2 *>(rec);
-        base = v.x;
-        cw = v.y;
-        pre = 0;
-    } else {
-        const uint4 h = *reinterpret_cast<const uint4 *>(rec);  // base, prefix words (and map words for k = 6)
-        const uint32_t word = c >> 5;
-        uint32_t pw = h.y;
-        if constexpr (RW == 4) {
-            cw = word ? h.w : h.z;
-        } else {
-            cw = rec[map_offset(RW) + word];
-            if constexpr (RW == 16) pw = word >= 4 ? h.z : h.y;
-        }
-        pre = (pw >> (8 * (word & 3))) & 0xffu;
-        base = h.x;
-    }
-    next = base + pre + __popc(cw & ((1u << bit) - 1u));
-    return (cw >> bit) & 1u;
+// Part of a record that holds chunk value c < 256.
+__host__ __device__ constexpr uint32_t part_of(uint32_t c) { return (c * 683u) >> 16; }
+static_assert(part_of(95) == 0 && part_of(96) == 1 && part_of(191) == 1 && part_of(192) == 2 && part_of(255) == 2, "c / 96");
+
+// Word of a record of rw words that holds the bit of chunk value c, and the bit.
+__host__ __device__ constexpr uint32_t map_word(uint32_t rw, uint32_t c) {
+    return rw == 2 ? 1 : 4 * part_of(c) + 1 + (c - kPartBits * part_of(c)) / 32;
 }
+__host__ __device__ constexpr uint32_t map_bit(uint32_t c) { return c % 32; }  // 96 is a multiple of 32
 
-template <class P, int RW>
-__global__ void __launch_bounds__(kBlock) bt_rank_kernel(const P *__restrict__ q, uint64_t n,
+// What a step reads of a record: {base, map} or the 16-byte part of chunk value
+// c; and its answer: whether c occurs, and the child or rank, base + set bits
+// below c.  The words are combined with masks, not chosen by branches, which
+// would put the loads of the walks that advance together one after another.
+template <int RW>
+struct BtPart {
+    uint4 v;
+    __device__ __forceinline__ void load(const uint32_t *rec, uint32_t c) {
+        if constexpr (RW == 2) {
+            const uint2 h = *reinterpret_cast<const uint2 *>(rec);
+            v = make_uint4(h.x, h.y, 0, 0);
+        } else {
+            v = *reinterpret_cast<const uint4 *>(rec + (RW == 4 ? 0u : 4 * part_of(c)));
+        }
+    }
+    __device__ __forceinline__ bool step(uint32_t c, uint32_t &next) const {
+        const uint32_t bit = 1u << map_bit(c), below = bit - 1u;
+        if constexpr (RW == 2) {
+            next = v.x + __popc(v.y & below);
+            return (v.y & bit) != 0;
+        } else {
+            const uint32_t word = RW == 4 ? c >> 5 : (c >> 5) - 3 * part_of(c);
+            const uint32_t past0 = word > 0 ? ~0u : 0u, past1 = RW > 4 && word > 1 ? ~0u : 0u;  // whole words below c's
+            uint32_t own = (v.y & ~past0) | (v.z & past0);
+            next = v.x + __popc(v.y & past0);
+            if constexpr (RW > 4) {
+                own = (own & ~past1) | (v.w & past1);
+                next += __popc(v.z & past1);
+            }
+            next += __popc(own & below);
+            return (own & bit) != 0;
+        }
+    }
+};
+
+template <class P, int RW, unsigned BLOCK>
+__global__ void __launch_bounds__(BLOCK) bt_rank_kernel(const P *__restrict__ q, uint64_t n,
                                                          uint32_t *__restrict__ out, BtArgs a) {
     extern __shared__ __align__(16) uint32_t top[];
     stage_to_lds(top, a.rec, (uint64_t)a.lds_words * 4);
@@ -95,25 +122,28 @@ __global__ void __launch_bounds__(kBlock) bt_rank_kernel(const P *__restrict__ q
         }
         // staged levels from LDS, the rest through the caches; a walk that
         // leaves the sector stays on record 0 of each further level
+        auto advance = [&](const uint32_t *lv, int l) {
+            uint32_t c[kQ];
+            BtPart<RW> part[kQ];
+#pragma unroll
+            for (int u = 0; u < kQ; ++u) {
+                c[u] = (uint32_t)(x[u] >> a.shift[l]) & a.cmask[l];
+                part[u].load(lv + node[u] * RW, c[u]);  // words < 2^32
+            }
+#pragma unroll
+            for (int u = 0; u < kQ; ++u) {
+                uint32_t nx;
+                const bool occurs = part[u].step(c[u], nx);
+                ok[u] = ok[u] && occurs;
+                node[u] = ok[u] ? nx : 0u;
+            }
+        };
         int l = 0;
         for (; l < a.lds_levels; ++l) {
-#pragma unroll
-            for (int u = 0; u < kQ; ++u) {
-                uint32_t nx;
-                const uint32_t c = (uint32_t)(x[u] >> a.shift[l]) & a.cmask[l];
-                ok[u] = bt_step<RW>(top + a.off[l] + node[u] * RW, c, nx) && ok[u];
-                node[u] = ok[u] ? nx : 0u;
-            }
+            advance(top + a.off[l], l);
         }
         for (; l < a.H; ++l) {
-            const uint32_t *lv = a.rec + a.off[l];
-#pragma unroll
-            for (int u = 0; u < kQ; ++u) {
-                uint32_t nx;
-                const uint32_t c = (uint32_t)(x[u] >> a.shift[l]) & a.cmask[l];
-                ok[u] = bt_step<RW>(lv + node[u] * RW, c, nx) && ok[u];  // words < 2^32
-                node[u] = ok[u] ? nx : 0u;
-            }
+            advance(a.rec + a.off[l], l);
         }
 #pragma unroll
         for (int u = 0; u < kQ; ++u) {
@@ -123,16 +153,9 @@ __global__ void __launch_bounds__(kBlock) bt_rank_kernel(const P *__restrict__ q
     }
 }
 
-// Words of a record for k-bit chunks: base, prefix words, map, rounded up to
-// a power of two.
-uint32_t record_words(int w) {
-    const uint32_t map_words = ((1u << w) + 31) / 32;
-    const uint32_t pref_words = map_words > 1 ? (map_words + 3) / 4 : 0;
-    const uint32_t bytes = 4 * (1 + pref_words + map_words);
-    uint32_t r = 8;
-    while (r < bytes) r *= 2;
-    return r / 4;
-}
+// Words of a record for k-bit chunks: {base, map}, or its 16-byte parts rounded
+// up to a power of two.
+uint32_t record_words(int w) { return w <= 5 ? 2 : w == 6 ? 4 : w == 7 ? 8 : 16; }
 
 // Records of every level from the ascending list (one counting pass, one
 // filling pass).
@@ -179,22 +202,19 @@ mbr_status build_records(BitmapTrie &t, const std::vector<P> &s) {
                 rec[t.off[l] + (uint64_t)cur[l] * t.rw[l]] = l + 1 < H ? (uint32_t)(cur[l + 1] + 1) : (uint32_t)i;
             }
             const uint32_t c = (uint32_t)(a >> t.shift[l]) & ((1u << t.w[l]) - 1u);
-            rec[t.off[l] + (uint64_t)cur[l] * t.rw[l] + map_offset(t.rw[l]) + (c >> 5)] |= 1u << (c & 31);
+            rec[t.off[l] + (uint64_t)cur[l] * t.rw[l] + map_word(t.rw[l], c)] |= 1u << map_bit(c);
         }
     }
-    // prefix bytes: set bits of the map words before each word
-    const uint32_t map_words = ((1u << kw) + 31) / 32;
-    if (map_words > 1)
-        for (int l = 0; l < H; ++l)
-            for (uint64_t nd = 0; nd < nodes[l]; ++nd) {
-                uint32_t *r = rec.data() + t.off[l] + nd * t.rw[l];
-                const uint32_t *m = r + map_offset(t.rw[l]);
-                uint32_t run = 0;
-                for (uint32_t w = 0; w < map_words; ++w) {
-                    r[1 + w / 4] |= run << (8 * (w % 4));
-                    run += (uint32_t)__builtin_popcount(m[w]);
-                }
+    // what the later parts of a record start from
+    const uint32_t parts = kw == 8 ? 3 : kw == 7 ? 2 : 1;
+    for (int l = 0; l < H; ++l)
+        for (uint64_t nd = 0; nd < nodes[l] && parts > 1; ++nd) {
+            uint32_t *r = rec.data() + t.off[l] + nd * t.rw[l];
+            for (uint32_t p = 1; p < parts; ++p) {
+                const uint32_t *q = r + 4 * (p - 1);
+                r[4 * p] = q[0] + (uint32_t)(__builtin_popcount(q[1]) + __builtin_popcount(q[2]) + __builtin_popcount(q[3]));
             }
+        }
     MBR_TRY(t.table.alloc(words * 4));
     MBR_HIP(hipMemcpy(t.table.p, rec.data(), words * 4, hipMemcpyHostToDevice));
     uint64_t lw = 0;
@@ -205,6 +225,24 @@ mbr_status build_records(BitmapTrie &t, const std::vector<P> &s) {
     }
     t.lds_levels = ll;
     t.lds_words = lw;
+    while (ll < H && (t.off[ll + 1]) * 4 <= kWideBudget) {
+        lw = t.off[ll + 1];
+        ++ll;
+    }
+    t.wide_levels = ll;
+    t.wide_words = lw;
+    return MBR_OK;
+}
+
+template <class P, int RW, unsigned BLOCK>
+mbr_status run_bt(const P *q, uint64_t n, uint32_t *out, const BtArgs &a, hipStream_t s) {
+    auto kern = bt_rank_kernel<P, RW, BLOCK>;
+    const size_t lds = (size_t)a.lds_words * 4;
+    if (lds > 64 * 1024)
+        MBR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWideBudget));
+    const unsigned grid = mbr::grid_for(n, BLOCK * kQ, mbr::device_cu_count() * (BLOCK == kWideBlock ? 1 : 8));
+    kern<<<grid, BLOCK, lds, s>>>(q, n, out, a);
+    MBR_HIP(hipGetLastError());
     return MBR_OK;
 }
 
@@ -222,17 +260,18 @@ mbr_status launch_bt(const mbr_ranker *r, const void *q, uint64_t n, uint32_t *o
         a.shift[l] = (uint32_t)t.shift[l];
         a.cmask[l] = (1u << t.w[l]) - 1u;
     }
-    const unsigned grid = mbr::grid_for(n, kBlock * kQ, mbr::device_cu_count() * 8);
-    const size_t lds = (size_t)t.lds_words * 4;
+    const bool wide = t.wide_levels > t.lds_levels && n >= kWideMin;
+    if (wide) {
+        a.lds_levels = t.wide_levels;
+        a.lds_words = (uint32_t)t.wide_words;
+    }
     const P *qp = static_cast<const P *>(q);
     switch (t.rw[0]) {
-    case 2: bt_rank_kernel<P, 2><<<grid, kBlock, lds, s>>>(qp, n, out, a); break;
-    case 4: bt_rank_kernel<P, 4><<<grid, kBlock, lds, s>>>(qp, n, out, a); break;
-    case 8: bt_rank_kernel<P, 8><<<grid, kBlock, lds, s>>>(qp, n, out, a); break;
-    default: bt_rank_kernel<P, 16><<<grid, kBlock, lds, s>>>(qp, n, out, a); break;
+    case 2: return wide ? run_bt<P, 2, kWideBlock>(qp, n, out, a, s) : run_bt<P, 2, kBlock>(qp, n, out, a, s);
+    case 4: return wide ? run_bt<P, 4, kWideBlock>(qp, n, out, a, s) : run_bt<P, 4, kBlock>(qp, n, out, a, s);
+    case 8: return wide ? run_bt<P, 8, kWideBlock>(qp, n, out, a, s) : run_bt<P, 8, kBlock>(qp, n, out, a, s);
+    default: return wide ? run_bt<P, 16, kWideBlock>(qp, n, out, a, s) : run_bt<P, 16, kBlock>(qp, n, out, a, s);
     }
-    MBR_HIP(hipGetLastError());
-    return MBR_OK;
 }
 
 }  // namespace

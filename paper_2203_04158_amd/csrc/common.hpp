@@ -163,6 +163,8 @@ struct BitmapTrie {
     uint64_t nodes[32] = {0};   // records of level l
     int32_t lds_levels = 0;     // levels 0..lds_levels-1 are staged in LDS
     uint64_t lds_words = 0;
+    int32_t wide_levels = 0;    // the same for the launch of one large workgroup per CU
+    uint64_t wide_words = 0;
     mbr::DevBuf table;
 };
 
