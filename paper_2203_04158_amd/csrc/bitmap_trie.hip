@@ -28,9 +28,9 @@
 // M = 32, N = 16 with >= 6 of orbitals 0-7 occupied needs about 4 M leaf
 // records (its packed trie holds 332 M entries).
 #include <algorithm>
-#include <cstring>
 #include <memory>
 
+#include "level_scan.hpp"
 #include "rank_device.hpp"
 
 namespace {
@@ -157,66 +157,143 @@ __global__ void __launch_bounds__(BLOCK) bt_rank_kernel(const P *__restrict__ q,
 // up to a power of two.
 uint32_t record_words(int w) { return w <= 5 ? 2 : w == 6 ? 4 : w == 7 ? 8 : 16; }
 
-// Records of every level from the ascending list (one counting pass, one
-// filling pass).
+// ------------------------------------------------------------------ building
+// The list is in ascending order, so the members under a node are consecutive
+// on every level and the nodes come in the order of their records: a node
+// starts where the bits above its chunk differ from the member before, and its
+// record's index is the number of starts before it.  One pass counts the starts
+// per tile and level, one writes each record's base (by the node's first
+// member) and sets its map's bits (by the first member of each chunk value), one
+// gives the later parts their bases.  7.1 M 64-bit patterns in five levels: 0.23 ms
+// with the allocations; on the host, with both copies, 75 ms.
+struct BtLevels {
+    int32_t H;
+    uint32_t rw;              // words per record
+    int32_t shift[kMaxH + 1]; // bit offset of level l's chunk; shift[H] = 0 (below the last)
+    uint32_t off[kMaxH];
+    uint32_t cmask[kMaxH];
+};
+
+// Whether a member whose bits differ by dp from the member before starts a node
+// of the level whose chunk's top lies at bit `up`.
 template <class P>
-mbr_status build_records(BitmapTrie &t, const std::vector<P> &s) {
-    const int H = t.H;
-    std::vector<uint64_t> nodes(H, 0);
-    for (int l = 0; l < H; ++l) {
-        const int up = t.shift[l] + t.w[l];
-        P prev = 0;
-        uint64_t cnt = 0;
-        for (size_t i = 0; i < s.size(); ++i) {
-            const P pre = up >= (int)(8 * sizeof(P)) ? (P)0 : (P)(s[i] >> up);
-            if (i == 0 || pre != prev) ++cnt;
-            prev = pre;
-        }
-        nodes[l] = cnt;
+__device__ __forceinline__ bool starts(P dp, int up, uint64_t i) {
+    return i == 0 || (up < (int)(8 * sizeof(P)) && (dp >> up) != 0);
+}
+
+// Bit above level l's chunk.
+__device__ __forceinline__ int above(const BtLevels &v, int l, int M) { return l == 0 ? M : v.shift[l - 1]; }
+
+// Starts in tile blockIdx.x, level by level: sums[l * tiles + tile].
+template <class P>
+__global__ void __launch_bounds__(kLevelBlock) bt_count_kernel(const P *__restrict__ key, uint64_t n, int M, BtLevels v, uint32_t *__restrict__ sums) {
+    __shared__ uint32_t red[kLevelBlock / 64];
+    const uint64_t i0 = (uint64_t)blockIdx.x * kLevelTile + threadIdx.x * kLevelItems;
+    P a[kLevelItems], dp[kLevelItems], dn[kLevelItems];
+    load_members<P>(key, n, i0, a, dp, dn);
+    for (int l = 0; l < v.H; ++l) {
+        uint32_t s = 0, all;
+#pragma unroll
+        for (unsigned k = 0; k < kLevelItems; ++k) s += i0 + k < n && starts<P>(dp[k], above(v, l, M), i0 + k) ? 1u : 0u;
+        (void)block_before<uint32_t, kLevelBlock>(s, red, &all);
+        if (threadIdx.x == 0) sums[(uint64_t)l * gridDim.x + blockIdx.x] = all;
     }
-    uint64_t words = 0;
-    const int kw = *std::max_element(t.w, t.w + H);
+}
+
+template <class P>
+__global__ void __launch_bounds__(kLevelBlock) bt_fill_kernel(const P *__restrict__ key, uint64_t n, int M, BtLevels v,
+                                                              const uint32_t *__restrict__ sums, uint32_t *__restrict__ rec) {
+    __shared__ uint32_t red[kLevelBlock / 64];
+    const uint64_t i0 = (uint64_t)blockIdx.x * kLevelTile + threadIdx.x * kLevelItems;
+    P a[kLevelItems], dp[kLevelItems], dn[kLevelItems];
+    load_members<P>(key, n, i0, a, dp, dn);
+    uint32_t node[kLevelItems], child[kLevelItems];
+#pragma unroll
+    for (unsigned k = 0; k < kLevelItems; ++k) node[k] = 0;  // the root
+    for (int l = 0; l < v.H; ++l) {
+        if (l + 1 < v.H) {
+            uint32_t s = 0, all;
+#pragma unroll
+            for (unsigned k = 0; k < kLevelItems; ++k) s += i0 + k < n && starts<P>(dp[k], v.shift[l], i0 + k) ? 1u : 0u;
+            uint32_t run = block_before<uint32_t, kLevelBlock>(s, red, &all) + sums[(uint64_t)(l + 1) * gridDim.x + blockIdx.x];
+#pragma unroll
+            for (unsigned k = 0; k < kLevelItems; ++k) {
+                run += i0 + k < n && starts<P>(dp[k], v.shift[l], i0 + k) ? 1u : 0u;
+                child[k] = run - 1;  // the member's node on the next level
+            }
+        } else {
+#pragma unroll
+            for (unsigned k = 0; k < kLevelItems; ++k) child[k] = (uint32_t)(i0 + k);
+        }
+#pragma unroll
+        for (unsigned k = 0; k < kLevelItems; ++k) {
+            if (i0 + k < n) {
+                uint32_t *r = rec + v.off[l] + (uint64_t)node[k] * v.rw;
+                if (starts<P>(dp[k], above(v, l, M), i0 + k)) r[0] = child[k];
+                if (starts<P>(dp[k], v.shift[l], i0 + k)) {
+                    const uint32_t c = (uint32_t)(a[k] >> v.shift[l]) & v.cmask[l];
+                    atomicOr(r + map_word(v.rw, c), 1u << map_bit(c));
+                }
+            }
+            node[k] = child[k];
+        }
+    }
+}
+
+// What the later parts of the records from `rec` on start from.
+__global__ void __launch_bounds__(kBlock) bt_parts_kernel(uint32_t *rec, uint64_t records, uint32_t rw, uint32_t parts) {
+    const uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+    if (i >= records) return;
+    uint32_t *r = rec + i * rw;
+    uint32_t base = r[0];
+    for (uint32_t p = 1; p < parts; ++p) {
+        const uint32_t *q = r + 4 * (p - 1);
+        base += __popc(q[1]) + __popc(q[2]) + __popc(q[3]);
+        r[4 * p] = base;
+    }
+}
+
+template <class P>
+mbr_status build_records(BitmapTrie &t, const mbr_sector *sec, hipStream_t s) {
+    using namespace mbr;
+    const int H = t.H, kw = *std::max_element(t.w, t.w + H);
+    const uint64_t n = sec->n, tiles = (n + kLevelTile - 1) / kLevelTile;
+    const P *key = sec->states.as<P>();
+    BtLevels v{};
+    v.H = H;
+    v.rw = record_words(kw);  // one record size for all levels (the root's short chunk included)
     for (int l = 0; l < H; ++l) {
-        t.rw[l] = record_words(kw);  // one record size for all levels (the root's short chunk included)
+        v.shift[l] = t.shift[l];
+        v.cmask[l] = (1u << t.w[l]) - 1u;
+    }
+    DevBuf scratch;  // starts per level and tile, then per level
+    MBR_TRY(scratch.alloc((tiles * H + H) * 4));
+    uint32_t *sums = scratch.as<uint32_t>(), *totals = sums + tiles * H;
+    bt_count_kernel<P><<<(unsigned)tiles, kLevelBlock, 0, s>>>(key, n, t.M, v, sums);
+    row_scan_kernel<uint32_t><<<H, 1024, 0, s>>>(sums, tiles, totals);
+    MBR_HIP(hipGetLastError());
+    uint32_t nodes[kMaxH] = {0};
+    MBR_HIP(hipMemcpyAsync(nodes, totals, (size_t)H * 4, hipMemcpyDeviceToHost, s));
+    MBR_HIP(hipStreamSynchronize(s));
+    uint64_t words = 0;
+    for (int l = 0; l < H; ++l) {
+        t.rw[l] = v.rw;
         words = (words + 15) & ~(uint64_t)15;  // every level starts on a 64-byte line
         t.off[l] = words;
         t.nodes[l] = nodes[l];
-        words += nodes[l] * t.rw[l];
+        words += (uint64_t)nodes[l] * v.rw;
     }
     t.off[H] = words;
     if (words >= (1ull << 32)) MBR_FAIL(MBR_EUNSUPPORTED, "bitmap trie of %llu words", (unsigned long long)words);
-    std::vector<uint32_t> rec(words, 0u);
-    std::vector<int64_t> cur(H, -1);
-    std::vector<P> prev(H, 0);
-    for (size_t i = 0; i < s.size(); ++i) {
-        const P a = s[i];
-        for (int l = 0; l < H; ++l) {
-            const int up = t.shift[l] + t.w[l];
-            const P pre = up >= (int)(8 * sizeof(P)) ? (P)0 : (P)(a >> up);
-            if (cur[l] < 0 || pre != prev[l]) {
-                ++cur[l];
-                prev[l] = pre;
-                // first child of a new node: the next record of the level
-                // below (created for this member in the same pass), or at the
-                // last level the position of its first member
-                rec[t.off[l] + (uint64_t)cur[l] * t.rw[l]] = l + 1 < H ? (uint32_t)(cur[l + 1] + 1) : (uint32_t)i;
-            }
-            const uint32_t c = (uint32_t)(a >> t.shift[l]) & ((1u << t.w[l]) - 1u);
-            rec[t.off[l] + (uint64_t)cur[l] * t.rw[l] + map_word(t.rw[l], c)] |= 1u << map_bit(c);
-        }
-    }
-    // what the later parts of a record start from
-    const uint32_t parts = kw == 8 ? 3 : kw == 7 ? 2 : 1;
-    for (int l = 0; l < H; ++l)
-        for (uint64_t nd = 0; nd < nodes[l] && parts > 1; ++nd) {
-            uint32_t *r = rec.data() + t.off[l] + nd * t.rw[l];
-            for (uint32_t p = 1; p < parts; ++p) {
-                const uint32_t *q = r + 4 * (p - 1);
-                r[4 * p] = q[0] + (uint32_t)(__builtin_popcount(q[1]) + __builtin_popcount(q[2]) + __builtin_popcount(q[3]));
-            }
-        }
+    for (int l = 0; l < H; ++l) v.off[l] = (uint32_t)t.off[l];
     MBR_TRY(t.table.alloc(words * 4));
-    MBR_HIP(hipMemcpy(t.table.p, rec.data(), words * 4, hipMemcpyHostToDevice));
+    uint32_t *rec = t.table.as<uint32_t>();
+    MBR_HIP(hipMemsetAsync(rec, 0, words * 4, s));
+    bt_fill_kernel<P><<<(unsigned)tiles, kLevelBlock, 0, s>>>(key, n, t.M, v, sums, rec);
+    const uint32_t parts = kw == 8 ? 3 : kw == 7 ? 2 : 1;
+    for (int l = 0; l < H && parts > 1; ++l)
+        bt_parts_kernel<<<(unsigned)((nodes[l] + (uint64_t)kBlock - 1) / kBlock), kBlock, 0, s>>>(rec + t.off[l], nodes[l], v.rw, parts);
+    MBR_HIP(hipGetLastError());
     uint64_t lw = 0;
     int ll = 0;
     while (ll < H && (t.off[ll + 1]) * 4 <= kLdsBudget) {
@@ -231,6 +308,7 @@ mbr_status build_records(BitmapTrie &t, const std::vector<P> &s) {
     }
     t.wide_levels = ll;
     t.wide_words = lw;
+    MBR_HIP(hipStreamSynchronize(s));  // the trie is ready for any stream, and the scratch is free
     return MBR_OK;
 }
 
@@ -305,19 +383,8 @@ extern "C" mbr_status mbr_build_bitmap_trie(const mbr_sector *sec, int32_t k, mb
         below -= t->w[l];
         t->shift[l] = below;
     }
-    mbr_status st;
-    if (sec->width_bits == 32) {
-        std::vector<uint32_t> h(sec->n);
-        MBR_HIP(hipMemcpyAsync(h.data(), sec->states.p, sec->n * 4, hipMemcpyDeviceToHost, s));
-        MBR_HIP(hipStreamSynchronize(s));
-        st = build_records<uint32_t>(*t, h);
-    } else {
-        std::vector<uint64_t> h(sec->n);
-        MBR_HIP(hipMemcpyAsync(h.data(), sec->states.p, sec->n * 8, hipMemcpyDeviceToHost, s));
-        MBR_HIP(hipStreamSynchronize(s));
-        st = build_records<uint64_t>(*t, h);
-    }
-    if (st != MBR_OK) return st;
+    if (sec->width_bits == 32) MBR_TRY(build_records<uint32_t>(*t, sec, s));
+    else MBR_TRY(build_records<uint64_t>(*t, sec, s));
     auto *r = new (std::nothrow) mbr_ranker;
     if (!r) MBR_FAIL(MBR_ENOMEM, "host allocation");
     r->kind = MBR_RANKER_BITMAP_TRIE;

@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <memory>
 
+#include "level_scan.hpp"
 #include "rank_device.hpp"
 
 void trie_free(TrieLevels *t) { delete t; }
@@ -119,8 +120,6 @@ __global__ void __launch_bounds__(kBlock) trie_rank_kernel(const P *__restrict__
 constexpr unsigned kSortBlock = 256, kSortItems = 16;       // a wave sorts 1024 consecutive members
 constexpr uint32_t kSortTile = kSortBlock * kSortItems;
 constexpr int kDigits = 256;
-constexpr unsigned kLevelBlock = 256, kLevelItems = 8;
-constexpr uint32_t kLevelTile = kLevelBlock * kLevelItems;
 constexpr int kMaxH = 16;
 
 // Members of tile blockIdx.x by digit: counts[digit * tiles + tile].
@@ -137,45 +136,6 @@ __global__ void __launch_bounds__(kSortBlock) tl_count_kernel(const P *__restric
     }
     __syncthreads();
     for (int d = threadIdx.x; d < kDigits; d += kSortBlock) counts[(uint64_t)d * gridDim.x + blockIdx.x] = c[d];
-}
-
-// Exclusive sum of v over the workgroup (B lanes); *all receives the total.
-template <class V, unsigned B>
-__device__ __forceinline__ V block_before(V v, V *red, V *all) {
-    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    V s = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        const V u = __shfl_up(s, o, 64);
-        if (lane >= (uint32_t)o) s += u;
-    }
-    __syncthreads();  // red's previous readers are done
-    if (lane == 63) red[w] = s;
-    __syncthreads();
-    V before = 0, total = 0;
-    for (uint32_t k = 0; k < B / 64; ++k) {
-        if (k < w) before += red[k];
-        total += red[k];
-    }
-    *all = total;
-    return before + s - v;
-}
-
-// Row blockIdx.x of v (n values) to exclusive sums in place, its total to
-// totals[row].
-template <class V>
-__global__ void __launch_bounds__(1024) tl_scan_kernel(V *v, uint64_t n, V *totals) {
-    __shared__ V red[16];
-    V *row = v + (uint64_t)blockIdx.x * n;
-    V run = 0;
-    for (uint64_t i0 = 0; i0 < n; i0 += 1024) {
-        const uint64_t i = i0 + threadIdx.x;
-        const V x = i < n ? row[i] : (V)0;
-        V all;
-        const V e = block_before<V, 1024>(x, red, &all);
-        if (i < n) row[i] = run + e;
-        run += all;
-    }
-    if (threadIdx.x == 0) totals[blockIdx.x] = run;
 }
 
 // One stable pass: member i of a tile goes behind all members of smaller
@@ -241,39 +201,15 @@ struct LevelArgs {
     uint64_t off[kMaxH];
 };
 
-template <class P>
-__device__ __forceinline__ P low_bits(int n) {
-    return n >= (int)(8 * sizeof(P)) ? (P)~(P)0 : (P)(((P)1 << n) - 1);
-}
-
 // What a member adds to the running sum of level l: the slots of its node (last
 // chunk - first chunk + 1), the first chunk taken off at the node's first
-// member, the rest added at its last.  `dp`, `dn`: bits that differ from the
-// member before and after (all ones at the ends).
+// member, the rest added at its last.  `dp`, `dn` as from
+// load_members.
 template <class P>
 __device__ __forceinline__ int64_t node_share(P a, P dp, P dn, int l, const LevelArgs &v) {
     const P lm = low_bits<P>(v.shift[l]);
     const int64_t c = (int64_t)((a >> v.shift[l]) & low_bits<P>(v.w[l]));
     return ((dn & lm) ? c + 1 : 0) - ((dp & lm) ? c : 0);
-}
-
-// A lane's consecutive members and their differences.
-template <class P>
-__device__ __forceinline__ void load_members(const P *__restrict__ key, uint64_t n, uint64_t i0, P (&a)[kLevelItems], P (&dp)[kLevelItems],
-                                             P (&dn)[kLevelItems]) {
-    P e[kLevelItems + 2];
-#pragma unroll
-    for (unsigned k = 0; k < kLevelItems + 2; ++k) {
-        const uint64_t i = i0 + k;  // member i - 1
-        e[k] = i > 0 && i <= n ? key[i - 1] : (P)0;
-    }
-#pragma unroll
-    for (unsigned k = 0; k < kLevelItems; ++k) {
-        const uint64_t i = i0 + k;
-        a[k] = e[k + 1];
-        dp[k] = i == 0 ? (P)~(P)0 : (P)(e[k] ^ e[k + 1]);
-        dn[k] = i + 1 >= n ? (P)~(P)0 : (P)(e[k + 2] ^ e[k + 1]);
-    }
 }
 
 // Sums of node_share over tile blockIdx.x, levels 1 .. H-1: sums[(l-1) * tiles + tile].
@@ -364,7 +300,7 @@ mbr_status build_levels(TrieLevels &t, const mbr_sector *sec, hipStream_t s) {
             const int shift = t.shift[l] + b;
             const uint32_t mask = (1u << std::min(8, t.w[l] - b)) - 1;
             tl_count_kernel<P><<<(unsigned)st, kSortBlock, 0, s>>>(key, n, shift, mask, counts);
-            tl_scan_kernel<uint32_t><<<kDigits, 1024, 0, s>>>(counts, st, digit_total);
+            row_scan_kernel<uint32_t><<<kDigits, 1024, 0, s>>>(counts, st, digit_total);
             tl_scatter_kernel<P><<<(unsigned)st, kSortBlock, 0, s>>>(key, idx, n, shift, mask, counts, digit_total, keys[to], idxs[to]);
             key = keys[to];
             idx = idxs[to];
@@ -380,7 +316,7 @@ mbr_status build_levels(TrieLevels &t, const mbr_sector *sec, hipStream_t s) {
     int64_t total_of[kMaxH] = {0};
     if (H > 1) {
         tl_sums_kernel<P><<<(unsigned)lt, kLevelBlock, 0, s>>>(key, n, v, sums);
-        tl_scan_kernel<int64_t><<<H - 1, 1024, 0, s>>>(sums, lt, level_total);
+        row_scan_kernel<int64_t><<<H - 1, 1024, 0, s>>>(sums, lt, level_total);
         MBR_HIP(hipGetLastError());
         MBR_HIP(hipMemcpyAsync(total_of + 1, level_total, (size_t)(H - 1) * 8, hipMemcpyDeviceToHost, s));
         MBR_HIP(hipStreamSynchronize(s));
