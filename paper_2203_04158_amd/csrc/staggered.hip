@@ -157,16 +157,25 @@ __device__ __forceinline__ RT stag_query(P x, const E *tab, const StagArgs &a) {
     return ok ? (RT)r : (RT)~(RT)0;
 }
 
-// Queries are handled as vectors of V patterns, kVecs vectors per lane and
+// Queries are handled as vectors of V patterns, VECS vectors per lane and
 // batch (grid stride between a lane's vectors, so a wave's accesses stay
 // contiguous).  The first batch is loaded before the table is staged so that
 // its latency overlaps the staging; the n mod V last queries are ranked one
 // per lane at the end.
-constexpr int kVecs = 4;
+//
+// VECS is 1 while that gives at most eight workgroups per CU, which then take
+// turns at loading, looking up and storing, and 2 beyond, where each stages
+// the table for more queries.  us for 2^22 / 2^24 queries with 1, 2 and 4
+// (24 orbitals half filled, k = 8): 10.8 / 35.3, 11.7 / 33.3, 12.4 / 34.4; spin
+// ranks on 14 sites: 12.6 / 40.2, 13.6 / 37.5, 15.0 / 39.3.
+constexpr unsigned kPerCu = 8;
+
+// Whether a launch of nv vectors takes one per lane and batch.
+bool one_vector(uint64_t nv) { return nv <= (uint64_t)kBlock * mbr::device_cu_count() * kPerCu; }
 
 // USE_LDS = false reads the table through the caches instead (tables larger
 // than the LDS budget, e.g. k = 16 or 64-bit patterns with wide chunks).
-template <class P, class E, bool USE_LDS, int V, class RT>
+template <class P, class E, bool USE_LDS, int V, int VECS, class RT>
 __global__ void __launch_bounds__(kBlock) rank_staggered_kernel(const P *__restrict__ q, uint64_t n,
                                                                 RT *__restrict__ out,
                                                                 const E *__restrict__ gtab,
@@ -175,10 +184,10 @@ __global__ void __launch_bounds__(kBlock) rank_staggered_kernel(const P *__restr
     const uint64_t nv = n / V;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t t0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    P x[kVecs][V];
+    P x[VECS][V];
     auto load = [&](uint64_t base) {
 #pragma unroll
-        for (int u = 0; u < kVecs; ++u) {
+        for (int u = 0; u < VECS; ++u) {
             const uint64_t j = base + u * stride;
             if (j < nv) load_vec<P, V>(q, j, x[u]);
         }
@@ -190,10 +199,10 @@ __global__ void __launch_bounds__(kBlock) rank_staggered_kernel(const P *__restr
         load_table(t, gtab, a.nentries);
         tab = t;
     }
-    for (uint64_t base = t0; base < nv; base += stride * kVecs) {
+    for (uint64_t base = t0; base < nv; base += stride * VECS) {
         if (base != t0) load(base);
 #pragma unroll
-        for (int u = 0; u < kVecs; ++u) {
+        for (int u = 0; u < VECS; ++u) {
             const uint64_t j = base + u * stride;
             if (j < nv) {
                 RT r[V];
@@ -234,7 +243,7 @@ __device__ __forceinline__ uint32_t spin_query(P x, const E *tab, const SpinArgs
     return ok ? (uint32_t)(ru * a.mult + rd) : MBR_NOT_FOUND;
 }
 
-template <class P, class E, bool USE_LDS, int V>
+template <class P, class E, bool USE_LDS, int V, int VECS>
 __global__ void __launch_bounds__(kBlock) rank_spin_kernel(const P *__restrict__ q, uint64_t n,
                                                            uint32_t *__restrict__ out,
                                                            const E *__restrict__ gtab, SpinArgs a) {
@@ -242,10 +251,10 @@ __global__ void __launch_bounds__(kBlock) rank_spin_kernel(const P *__restrict__
     const uint64_t nv = n / V;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t t0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    P x[kVecs][V];
+    P x[VECS][V];
     auto load = [&](uint64_t base) {
 #pragma unroll
-        for (int u = 0; u < kVecs; ++u) {
+        for (int u = 0; u < VECS; ++u) {
             const uint64_t j = base + u * stride;
             if (j < nv) load_vec<P, V>(q, j, x[u]);
         }
@@ -257,10 +266,10 @@ __global__ void __launch_bounds__(kBlock) rank_spin_kernel(const P *__restrict__
         load_table(t, gtab, a.half.nentries);
         tab = t;
     }
-    for (uint64_t base = t0; base < nv; base += stride * kVecs) {
+    for (uint64_t base = t0; base < nv; base += stride * VECS) {
         if (base != t0) load(base);
 #pragma unroll
-        for (int u = 0; u < kVecs; ++u) {
+        for (int u = 0; u < VECS; ++u) {
             const uint64_t j = base + u * stride;
             if (j < nv) {
                 uint32_t r[V];
@@ -306,7 +315,7 @@ bool vec_aligned(const void *q, const RT *out) {
     return ((uintptr_t)q % 16 == 0) && ((uintptr_t)out % (sizeof(RT) * V) == 0);
 }
 
-template <class P, class E, int V, class RT>
+template <class P, class E, int V, int VECS, class RT>
 mbr_status launch_stag_v(const mbr_ranker *r, const void *q, uint64_t n, RT *out, hipStream_t s) {
     StagArgs a = make_args(r->stag, r->N);
     const E *tab = r->stag.table.as<E>();
@@ -318,13 +327,13 @@ mbr_status launch_stag_v(const mbr_ranker *r, const void *q, uint64_t n, RT *out
         tab = r->stag.trim.as<E>();
     }
     size_t lds = a.nentries * sizeof(E);
-    unsigned grid = mbr::grid_for((n + V - 1) / V, kBlock * kVecs, mbr::device_cu_count() * 8);
+    unsigned grid = mbr::grid_for((n + V - 1) / V, kBlock * VECS, mbr::device_cu_count() * kPerCu);
     if (lds <= kLdsTable) {
-        auto kern = rank_staggered_kernel<P, E, true, V, RT>;
+        auto kern = rank_staggered_kernel<P, E, true, V, VECS, RT>;
         MBR_TRY(set_lds(kern, lds));
         kern<<<grid, kBlock, lds, s>>>(static_cast<const P *>(q), n, out, tab, a);
     } else {
-        rank_staggered_kernel<P, E, false, V, RT><<<grid, kBlock, 0, s>>>(static_cast<const P *>(q), n, out,
+        rank_staggered_kernel<P, E, false, V, VECS, RT><<<grid, kBlock, 0, s>>>(static_cast<const P *>(q), n, out,
                                                                          tab, a);
     }
     MBR_HIP(hipGetLastError());
@@ -333,11 +342,16 @@ mbr_status launch_stag_v(const mbr_ranker *r, const void *q, uint64_t n, RT *out
 
 template <class P, class E, class RT>
 mbr_status launch_stag(const mbr_ranker *r, const void *q, uint64_t n, RT *out, hipStream_t s) {
-    if (vec_aligned<P, RT>(q, out)) return launch_stag_v<P, E, 16 / sizeof(P), RT>(r, q, n, out, s);
-    return launch_stag_v<P, E, 1, RT>(r, q, n, out, s);
+    constexpr int V = 16 / sizeof(P);
+    const uint64_t entries = r->stag.trim_entries ? r->stag.trim_entries : (uint64_t)r->stag.nrows << r->stag.k;
+    if (vec_aligned<P, RT>(q, out)) {
+        if (entries * sizeof(E) > kLdsTable) return launch_stag_v<P, E, V, 4, RT>(r, q, n, out, s);  // lookups in memory: as many as fit in flight
+        return one_vector((n + V - 1) / V) ? launch_stag_v<P, E, V, 1, RT>(r, q, n, out, s) : launch_stag_v<P, E, V, 2, RT>(r, q, n, out, s);
+    }
+    return launch_stag_v<P, E, 1, 4, RT>(r, q, n, out, s);  // unaligned: more single patterns in flight instead
 }
 
-template <class P, class E, int V>
+template <class P, class E, int V, int VECS>
 mbr_status launch_spin_v(const mbr_ranker *r, const void *q, uint64_t n, uint32_t *out,
                          hipStream_t s) {
     SpinArgs a{};
@@ -347,13 +361,13 @@ mbr_status launch_spin_v(const mbr_ranker *r, const void *q, uint64_t n, uint32_
     a.n_dn = r->n_dn;
     a.mult = (uint32_t)mbr::binom(r->L, r->n_dn);
     size_t lds = a.half.nentries * sizeof(E);
-    unsigned grid = mbr::grid_for((n + V - 1) / V, kBlock * kVecs, mbr::device_cu_count() * 8);
+    unsigned grid = mbr::grid_for((n + V - 1) / V, kBlock * VECS, mbr::device_cu_count() * kPerCu);
     if (lds <= kLdsTable) {
-        auto kern = rank_spin_kernel<P, E, true, V>;
+        auto kern = rank_spin_kernel<P, E, true, V, VECS>;
         MBR_TRY(set_lds(kern, lds));
         kern<<<grid, kBlock, lds, s>>>(static_cast<const P *>(q), n, out, r->stag.table.as<E>(), a);
     } else {
-        rank_spin_kernel<P, E, false, V><<<grid, kBlock, 0, s>>>(static_cast<const P *>(q), n, out,
+        rank_spin_kernel<P, E, false, V, VECS><<<grid, kBlock, 0, s>>>(static_cast<const P *>(q), n, out,
                                                                 r->stag.table.as<E>(), a);
     }
     MBR_HIP(hipGetLastError());
@@ -363,8 +377,12 @@ mbr_status launch_spin_v(const mbr_ranker *r, const void *q, uint64_t n, uint32_
 template <class P, class E>
 mbr_status launch_spin(const mbr_ranker *r, const void *q, uint64_t n, uint32_t *out,
                        hipStream_t s) {
-    if (vec_aligned<P>(q, out)) return launch_spin_v<P, E, 16 / sizeof(P)>(r, q, n, out, s);
-    return launch_spin_v<P, E, 1>(r, q, n, out, s);
+    constexpr int V = 16 / sizeof(P);
+    if (vec_aligned<P>(q, out)) {
+        if (((uint64_t)r->stag.nrows << r->stag.k) * sizeof(E) > kLdsTable) return launch_spin_v<P, E, V, 4>(r, q, n, out, s);
+        return one_vector((n + V - 1) / V) ? launch_spin_v<P, E, V, 1>(r, q, n, out, s) : launch_spin_v<P, E, V, 2>(r, q, n, out, s);
+    }
+    return launch_spin_v<P, E, 1, 4>(r, q, n, out, s);
 }
 
 }  // namespace
