@@ -2365,9 +2365,17 @@ mbr_status mbr_hubbard_create(const mbr_hubbard_desc *d, mbr_hubbard **out, void
         *out = h.release();
         return MBR_OK;
     }
-    // default launch shape: two lookups per half rank, two alpha_up blocks per tile
+    // default launch shape: two lookups per half rank; the block kernel for
+    // sectors of more than 512 spin-down configurations, except in fp32 with
+    // bond-dependent hopping, where the rows kernel packs several of their
+    // blocks into a tile.  us per product, block / rows kernel: 12-site chain
+    // half filled 13.9 / 16.4 (fp64) and 8.1 / 24.7 (fp32), 14 sites with (4,7)
+    // 31.9 / 38.0; impurity model, 12 sites, all sectors 264 / 293 (fp64) and
+    // 184 / 168 (fp32).
     const int k = d->k > 0 ? std::min(d->k, L) : (L + 1) / 2;
-    mbr_status st = configure(h.get(), k, 0, 512, s);
+    bool uniform = true;
+    for (const mbr_bond &b : h->bonds) uniform = uniform && b.t == h->bonds[0].t;
+    mbr_status st = configure(h.get(), k, uniform || h->precision == MBR_F64 ? -2 : 0, 512, s);
     if (st != MBR_OK && d->k == 0) st = configure(h.get(), k, 1, 512, s);
     if (st != MBR_OK) return st;
     *out = h.release();
