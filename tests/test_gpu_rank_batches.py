@@ -37,3 +37,12 @@ def test_ranks_around_one_vector_per_lane(width, edge, k, kind):
             assert torch.equal(got, member[off:n])
     keep = member >= 0
     assert torch.equal(member[keep & (q == mbr.unrank_batch(sec, idx))], want[keep & (q == mbr.unrank_batch(sec, idx))])
+
+
+def test_calls_go_to_the_current_stream():
+    side = torch.cuda.Stream()
+    assert mbr.binding._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert mbr.binding._stream(None) == side.cuda_stream
+    assert mbr.binding._stream(side) == side.cuda_stream
+    assert mbr.binding._stream(None) == torch.cuda.current_stream().cuda_stream
