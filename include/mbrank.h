@@ -505,13 +505,16 @@ mbr_status mbr_hubbard_destroy(mbr_hubbard *h);
  * k: half-pattern chunk width of the staggered rank; G: -1 selects the flat
  * kernel for every sector (256-lane workgroups, one row per lane at a time,
  * both halves ranked on the fly, no staged x and no barrier between rows);
- * 0 selects the alpha_dn-stationary rows kernel (1024-lane workgroups, one
- * per CU, down-hop lists ranked once per launch shape) for every sector it
- * supports (at most 4095 spin-down configurations and 15 bonds) and the tile
- * kernel with two blocks for the rest; -2 is G = 0 with the sectors of more
- * than 512 spin-down configurations moved to the block kernel (one alpha_up
- * block per 1024-lane workgroup, a workgroup per tile instead of one per CU,
- * up-hop lists of every half state built once per launch shape); G in
+ * 0 selects the panel kernel (512-lane workgroups, each on a run of alpha_up
+ * blocks with the down-hop lists of its spin-down configurations in registers)
+ * for sectors of at most 1024 (fp32) or 512 (fp64) spin-down configurations,
+ * the alpha_dn-stationary rows kernel (1024-lane workgroups that sweep tiles,
+ * down-hop lists ranked once per launch shape) for longer ones (at most 4095
+ * spin-down configurations; both need at most 15 bonds) and the tile
+ * kernel with two blocks for the rest; -2 is G = 0 with the rows kernel's
+ * sectors, and with uniform hopping the fp32 sectors of more than 512, moved
+ * to the block kernel (one alpha_up block per 1024-lane workgroup, a workgroup
+ * per tile, up-hop lists of every half state built once per launch shape); G in
  * {1,2,4} selects the tile kernel for every sector, holding G alpha_up
  * blocks per workgroup (the down-hop ranks of a lane are reused G times);
  * block: threads per workgroup of the tile kernel (256 or 512).  Every shape

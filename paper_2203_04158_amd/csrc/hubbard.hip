@@ -27,6 +27,7 @@
 #include <memory>
 #include <numeric>
 #include <sstream>
+#include <type_traits>
 
 #include "hubbard.hpp"
 #include "rank_device.hpp"
@@ -79,17 +80,20 @@ struct mbr_hubbard {
     uint32_t flat_xoff[kXcd + 1] = {0};
     DevBuf d_rdesc, d_rdesc_slot;       // their descriptors, and descriptors in slot order
     uint32_t rows_xoff[kXcd + 1] = {0};
-    uint32_t rows_xcap = 0, rows_gmax = 1;
+    uint32_t rows_xcap = 0;
     int rows_R = 1, rows_grid = 0;
     bool t_uniform = true;              // all bonds share one amplitude
-    DevBuf d_lists;                     // rows and block kernels: down-hop lists per n_dn
+    DevBuf d_lists;                     // rows, block and panel kernels: down-hop lists per n_dn
     std::vector<uint32_t> lists_ndn;    // n_dn of each list set, in storage order
-    std::vector<uint8_t> lists_blk;     // the set serves block-kernel sectors (their negated-copy offset)
+    std::vector<uint8_t> lists_for;     // the kernel the set serves (how its entries carry the sign)
     std::vector<HvTile> block_tiles;    // block kernel (G = -2) tiles, one alpha_up block each, natural order
     DevBuf d_bdesc;                     // their descriptors
     uint32_t block_xoff[kXcd + 1] = {0};
     uint32_t block_xcap = 0;            // largest C_dn + 1 of the block kernel's sectors
-    DevBuf d_up_tgt, d_up_coef, d_up_n; // block kernel: up-hop lists of every half state
+    std::vector<HvTile> panel_tiles;    // panel kernel tiles, natural order
+    DevBuf d_pdesc;                     // their descriptors
+    uint32_t panel_xoff[kXcd + 1] = {0};
+    DevBuf d_up_tgt, d_up_coef, d_up_n; // block and panel kernels: up-hop lists of every half state
     uint32_t n_slots = 0;
     StagTable tab;
     DevBuf d_hs_states, d_hs_energy, d_tiles, d_secs;
@@ -151,7 +155,6 @@ struct HvArgs {
     uint32_t xcap;     // LDS elements for staged x rows
     uint32_t upcap;    // LDS up-hop list entries (max nblk * nb over tiles)
     uint32_t maxblk;   // LDS per-block entries (max nblk over tiles)
-    uint32_t rgmax;    // alpha_dn-stationary kernel: max alpha_up blocks per tile
     int32_t t_uniform; // every bond has the amplitude bamp[0]
     const void *lists;     // alpha_dn-stationary kernel: down-hop lists (hv_lists_kernel)
     const RowsTileDesc *rdesc;  // and its tiles (n_tiles of them)
@@ -473,11 +476,10 @@ __global__ void __launch_bounds__(512) hv_kernel(HvArgs a) {
 }
 
 // ------------------------------------------------------------------------
-// alpha_dn-stationary kernel.  A workgroup of kRowsBlock lanes sweeps a
-// contiguous run of tiles (alpha_up blocks of one sector, or a few small
-// sectors).  Lane t owns fixed spin-down configurations of the sector: rows
-// t + r kRowsBlock (row slot r < R) of each alpha_up block, or one
-// (block, alpha_dn) pair when C_dn is small.
+// alpha_dn-stationary kernel (launch shape G = 0) for sectors too long for a
+// panel.  A workgroup of kRowsBlock lanes sweeps a contiguous run of tiles, one
+// alpha_up block each.  Lane t owns fixed spin-down configurations of the
+// sector: rows t + r kRowsBlock (row slot r < R) of each alpha_up block.
 //  * down-hops: the targets of an alpha_dn depend on alpha_dn alone.  They are
 //    ranked once per launch shape (staggered lookup, hv_lists_kernel) into a
 //    list per alpha_dn in bond order of 16-bit LDS byte offsets: the tile's x
@@ -501,27 +503,22 @@ __global__ void __launch_bounds__(512) hv_kernel(HvArgs a) {
 constexpr int kRowsBlock = 1024;
 constexpr int kRowsWaves = kRowsBlock / 64;
 constexpr int kRowsNB = 16;           // bonds
-constexpr int kRowsMaxG = 64;         // alpha_up blocks per tile when C_dn is small
 constexpr int kRowsMaxR = 4;          // alpha_dn per lane
 constexpr int kUpMax = 8;             // up-hop gathers in flight per row (more run in a tail loop)
 constexpr int kRowsDownFixed = 12;    // down-hop entries summed without a branch (padding adds zeros)
-constexpr uint32_t kRowsMaxX = 4096;  // staged elements per tile (blocks of C_dn + 1): offsets fit 16 bits
-constexpr uint32_t kRowsSlots = 4;    // fp32: alpha_up blocks per tile when each takes a row slot (512 < C_dn <= 1024)
-constexpr uint32_t kRowsSlotsUT = 3;  // the same with uniform hopping (R = 4 would spill there)
-__host__ __device__ constexpr uint32_t rows_slots(bool ut) { return ut ? kRowsSlotsUT : kRowsSlots; }
+constexpr uint32_t kRowsMaxX = 4096;  // staged elements per tile (C_dn + 1): offsets fit 16 bits
 static_assert(kRowsMaxX <= (uint32_t)(kRowsMaxR * kRowsBlock), "R slots cover a block");
 
 // LDS layout: rank table | bond amplitudes | on-site U | reduction scratch |
 // two buffers.
-// A buffer holds the tile's blocks with stride C_dn + 1 (x rows, then a zero)
-// from byte 0, the negated rows at byte cs, then up-hop targets |
-// coefficients | alpha_up | energies | counts for up to gmax blocks.
+// A buffer holds the tile's block (x rows, then a zero) from byte 0, the
+// negated rows at byte cs, then up-hop targets | coefficients | alpha_up |
+// energy | count.
 struct RowsLds {
     size_t rt, amp, ul, red, buf0, bstride, cs, ut, uc, ua, ue, un, total;
 };
 
-__host__ __device__ inline RowsLds rows_lds_layout(uint32_t rtab_entries, uint32_t xcap, uint32_t gmax,
-                                                   size_t tsz) {
+__host__ __device__ inline RowsLds rows_lds_layout(uint32_t rtab_entries, uint32_t xcap, size_t tsz) {
     auto r16 = [](size_t v) { return (v + 15) & ~(size_t)15; };
     RowsLds L{};
     size_t o = 0;
@@ -537,15 +534,15 @@ __host__ __device__ inline RowsLds rows_lds_layout(uint32_t rtab_entries, uint32
     L.cs = r16((size_t)xcap * tsz);
     size_t b = 2 * L.cs;
     L.ut = b;
-    b += r16((size_t)gmax * kRowsNB * 4);
+    b += r16((size_t)kRowsNB * 4);
     L.uc = b;
-    b += r16((size_t)gmax * kRowsNB * tsz);
+    b += r16((size_t)kRowsNB * tsz);
     L.ua = b;
-    b += r16((size_t)gmax * 4);
+    b += r16(4);
     L.ue = b;
-    b += r16((size_t)gmax * tsz);
+    b += r16(tsz);
     L.un = b;
-    b += r16((size_t)gmax * 4);
+    b += r16(4);
     L.bstride = b;
     L.total = o + 2 * b;
     return L;
@@ -628,63 +625,53 @@ __device__ __forceinline__ T rows_u_energy(uint32_t both, const HvArgs &a, const
     return e;
 }
 
-// Up-hop lists of a tile's blocks into buffer bb: lane t ranks bond t % 16 of
-// block t / 16 (16-lane groups stay inside a wave) and the hops are compacted
-// in bond order with a ballot.  au, eu: the block's alpha_up and its energy,
-// loaded ahead by the caller.
+// Up-hop list of a tile's block into buffer bb: lane b ranks bond b and the
+// hops are compacted in bond order with a ballot.  au, eu: the block's
+// alpha_up and its energy, loaded ahead by the caller.
 template <class T>
-__device__ __forceinline__ void rows_uplists(const HvArgs &a, const uint16_t *rt, uint32_t nblk, uint32_t au,
-                                             T eu, unsigned char *bb, const RowsLds &LL) {
+__device__ __forceinline__ void rows_uplists(const HvArgs &a, const uint16_t *rt, uint32_t au, T eu,
+                                             unsigned char *bb, const RowsLds &LL) {
     uint32_t *ut = reinterpret_cast<uint32_t *>(bb + LL.ut);
     T *uc = reinterpret_cast<T *>(bb + LL.uc);
-    uint32_t *ua = reinterpret_cast<uint32_t *>(bb + LL.ua);
-    T *ue = reinterpret_cast<T *>(bb + LL.ue);
-    uint32_t *un = reinterpret_cast<uint32_t *>(bb + LL.un);
-    const uint32_t t = threadIdx.x;
-    const uint32_t g = t >> 4, b = t & 15;
+    const uint32_t b = threadIdx.x;
     bool hop = false;
     uint32_t tgt = 0;
     T coef = 0;
-    if (g < nblk) {
-        if ((int)b < a.nb) {
-            const uint32_t bi = a.bij[b] & 0xFF, bj = a.bij[b] >> 8;
-            hop = ((au >> bi) ^ (au >> bj)) & 1;
-            if (hop) {
-                tgt = rank_half<0>(au ^ a.bmask[b], rt, a);
-                coef = (__popc(au & a.bbetw[b]) & 1) ? (T)a.bamp[b] : -(T)a.bamp[b];
-            }
-        }
-        if (b == 0) {
-            ua[g] = au;
-            ue[g] = eu;
+    if ((int)b < a.nb) {
+        const uint32_t bi = a.bij[b] & 0xFF, bj = a.bij[b] >> 8;
+        hop = ((au >> bi) ^ (au >> bj)) & 1;
+        if (hop) {
+            tgt = rank_half<0>(au ^ a.bmask[b], rt, a);
+            coef = (__popc(au & a.bbetw[b]) & 1) ? (T)a.bamp[b] : -(T)a.bamp[b];
         }
     }
-    const unsigned long long bal = __ballot(hop);
-    const int lane = threadIdx.x & 63;
-    const unsigned long long grp = 0xFFFFull << (lane & 48);
-    const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const uint32_t nu = (uint32_t)__popcll(bal & grp);
+    const unsigned long long bal = __ballot(hop);  // the first wave's holds the bonds
+    const uint32_t nu = (uint32_t)__popcll(bal);
     if (hop) {
-        const uint32_t pos = (uint32_t)__popcll(bal & grp & below);
-        ut[g * kRowsNB + pos] = tgt;
-        uc[g * kRowsNB + pos] = coef;
+        const uint32_t pos = (uint32_t)__popcll(bal & ((1ull << b) - 1));
+        ut[pos] = tgt;
+        uc[pos] = coef;
     }
-    if (g < nblk && b >= nu) {
+    if (b < (uint32_t)kRowsNB && b >= nu) {
         // entries past the hops (every position b >= nu, written by lane b
         // whether or not it hops itself: a hop lane's own entry lies below nu):
         // block 0 of the sector with coefficient 0, so a fixed number of
         // gathers can be read and summed without a branch
-        ut[g * kRowsNB + b] = 0u;
-        uc[g * kRowsNB + b] = (T)0;
+        ut[b] = 0u;
+        uc[b] = (T)0;
     }
-    if (b == 0 && g < nblk) un[g] = nu;
+    if (b == 0) {
+        *reinterpret_cast<uint32_t *>(bb + LL.ua) = au;
+        *reinterpret_cast<T *>(bb + LL.ue) = eu;
+        *reinterpret_cast<uint32_t *>(bb + LL.un) = nu;
+    }
 }
 
 // Staging of a tile's x rows: each lane loads kRowsPre rows into registers
 // (a fixed number of loads, so the compiler's wait counts stay exact) while
 // the previous tile computes, then stores them at the end of that tile as x
-// at byte g (C_dn + 1) sizeof(T) + i sizeof(T) of the buffer for row
-// g C_dn + i, as -x at cs bytes further, and a zero after every block.
+// from byte 0 of the buffer, as -x at cs bytes further, and a zero after the
+// block.
 constexpr int kRowsPre = (kRowsMaxX + kRowsBlock - 1) / kRowsBlock;
 
 template <class T>
@@ -697,31 +684,18 @@ __device__ __forceinline__ void rows_pre_load(const T *src, uint32_t rows, T (&p
 }
 
 template <class T>
-__device__ __forceinline__ void rows_pre_store(unsigned char *bb, size_t cs, uint32_t nblk, uint32_t cdn,
-                                               const T (&pre)[kRowsPre]) {
+__device__ __forceinline__ void rows_pre_store(unsigned char *bb, size_t cs, uint32_t cdn, const T (&pre)[kRowsPre]) {
     T *xp = reinterpret_cast<T *>(bb);
     T *xm = reinterpret_cast<T *>(bb + cs);
-    const uint32_t rows = nblk * cdn;
-    // block g = e / C_dn of element e = t + j 1024, stepped from j to j + 1
-    // by the quotient and remainder of 1024 / C_dn
-    const uint32_t qs = (uint32_t)kRowsBlock / cdn, rs = (uint32_t)kRowsBlock - qs * cdn;
-    uint32_t g = threadIdx.x / cdn, rem = threadIdx.x - g * cdn;
 #pragma unroll
     for (int j = 0; j < kRowsPre; ++j) {
         const uint32_t e = threadIdx.x + j * kRowsBlock;
-        if (e < rows) {
-            const uint32_t pos = e + g;  // g (C_dn + 1) + (e - g C_dn)
-            xp[pos] = pre[j];
-            xm[pos] = -pre[j];
-        }
-        g += qs;
-        rem += rs;
-        if (rem >= cdn) {
-            rem -= cdn;
-            ++g;
+        if (e < cdn) {
+            xp[e] = pre[j];
+            xm[e] = -pre[j];
         }
     }
-    if (threadIdx.x < nblk) xp[threadIdx.x * (cdn + 1) + cdn] = (T)0;
+    if (threadIdx.x == 0) xp[cdn] = (T)0;
 }
 
 // Sum of the down-hop terms of one row: the list entries (byte offsets from
@@ -811,27 +785,22 @@ __device__ __forceinline__ RowsTile rows_desc_uniform(const uint4 (&q)[2]) {
 // Up-hop terms kUpMax .. of one row past the first batch, in groups of four:
 // a group's gathers are all issued before its sums (entries past the block's
 // hops are block 0 with coefficient 0, so a group needs no branch inside).
-// U: the lists are the same for the whole wave (values taken from lane 0);
-// otherwise a group runs when any lane of the wave needs it.
-template <class T, bool U>
+// The lists are the same for the whole wave (values taken from lane 0).
+template <class T>
 __device__ __forceinline__ T rows_up_tail(const T *xsec, const uint32_t *utb, const T *ucb, uint32_t cdn,
                                           uint32_t rd, uint32_t nu, T v) {
 #pragma unroll
     for (int h0 = kUpMax; h0 < kRowsNB; h0 += 4) {
-        const bool need = U ? nu > (uint32_t)h0 : __ballot(nu > (uint32_t)h0) != 0;
-        if (!need) break;
+        if (nu <= (uint32_t)h0) break;
         T g[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            uint32_t t = utb[h0 + q];
-            if constexpr (U) t = __builtin_amdgcn_readfirstlane(t);
+            const uint32_t t = __builtin_amdgcn_readfirstlane(utb[h0 + q]);
             g[q] = xsec[(uint64_t)t * cdn + rd];
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            T c = ucb[h0 + q];
-            if constexpr (U) c = uniform_val(c);
-            v = fma_t(c, g[q], v);
+            v = fma_t(uniform_val(ucb[h0 + q]), g[q], v);
         }
     }
     return v;
@@ -840,7 +809,7 @@ __device__ __forceinline__ T rows_up_tail(const T *xsec, const uint32_t *utb, co
 template <class T, bool LZ, int R, bool UT>
 __global__ void __launch_bounds__(kRowsBlock) hv_rows_kernel(HvArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const RowsLds LL = rows_lds_layout(a.rtab_entries, a.xcap, a.rgmax, sizeof(T));
+    const RowsLds LL = rows_lds_layout(a.rtab_entries, a.xcap, sizeof(T));
     uint16_t *rt = reinterpret_cast<uint16_t *>(smem + LL.rt);
     T *amp = reinterpret_cast<T *>(smem + LL.amp);
     T *ul = reinterpret_cast<T *>(smem + LL.ul);
@@ -876,7 +845,6 @@ __global__ void __launch_bounds__(kRowsBlock) hv_rows_kernel(HvArgs a) {
     const uint32_t *lists = static_cast<const uint32_t *>(a.lists);
     const RowsTileDesc *desc = a.rdesc;
     const T tu = (T)a.bamp[0];
-    const uint32_t ug = (uint32_t)tid >> 4;  // block of this lane in the up-hop ranking
     const bool has_p = LZ && a.ep.c2;
 
     // Tile descriptors are loaded two tiles ahead and the per-tile scalars
@@ -892,14 +860,14 @@ __global__ void __launch_bounds__(kRowsBlock) hv_rows_kernel(HvArgs a) {
         const RowsTile c = rows_desc_uniform(qc);
         unsigned char *bb = smem + LL.buf0;
         T pre[kRowsPre];
-        rows_pre_load<T>(x + c.base, c.nblk * c.cdn, pre);
-        const uint32_t au = ug < c.nblk ? a.hs_states[c.hs_up0 + ug] : 0u;
-        const T eu = ug < c.nblk ? (T)a.hs_energy[c.hs_up0 + ug] : (T)0;
+        rows_pre_load<T>(x + c.base, c.cdn, pre);
+        const uint32_t au = a.hs_states[c.hs_up0];
+        const T eu = (T)a.hs_energy[c.hs_up0];
         act_c = a.ep.active ? a.ep.active[c.sector] : 1;
         c1_c = LZ ? (T)a.ep.c1[c.sector] : (T)1;
         c2_c = has_p ? (T)a.ep.c2[c.sector] : (T)0;
-        rows_uplists<T>(a, rt, c.nblk, au, eu, bb, LL);
-        rows_pre_store<T>(bb, LL.cs, c.nblk, c.cdn, pre);
+        rows_uplists<T>(a, rt, au, eu, bb, LL);
+        rows_pre_store<T>(bb, LL.cs, c.cdn, pre);
     }
     __syncthreads();
 
@@ -934,11 +902,9 @@ __global__ void __launch_bounds__(kRowsBlock) hv_rows_kernel(HvArgs a) {
         T pre[kRowsPre];
         if (has_next) {
             n = rows_desc_uniform(qn);
-            rows_pre_load<T>(x + n.base, n.nblk * n.cdn, pre);
-            if (ug < n.nblk) {
-                au_n = a.hs_states[n.hs_up0 + ug];
-                eu_n = (T)a.hs_energy[n.hs_up0 + ug];
-            }
+            rows_pre_load<T>(x + n.base, n.cdn, pre);
+            au_n = a.hs_states[n.hs_up0];
+            eu_n = (T)a.hs_energy[n.hs_up0];
             act_c = a.ep.active ? a.ep.active[n.sector] : 1;
             c1_c = LZ ? (T)a.ep.c1[n.sector] : (T)1;
             c2_c = has_p ? (T)a.ep.c2[n.sector] : (T)0;
@@ -956,180 +922,72 @@ __global__ void __launch_bounds__(kRowsBlock) hv_rows_kernel(HvArgs a) {
         const T *xsec = x + c.soff;
         double dot = 0.0;
         if (active) {
-            if (c.gp == 1) {
-                // One alpha_up block per tile: its data is uniform, held in scalars.
-                const uint32_t nu = __builtin_amdgcn_readfirstlane(un[0]);
-                const uint32_t au = __builtin_amdgcn_readfirstlane(ua[0]);
-                const T eu = uniform_val(ue[0]);
-                const T *src[kUpMax];
-                T cf[kUpMax];
-                // entries past nu are block 0 with coefficient 0: read without a branch
+            // One alpha_up block per tile: its data is uniform, held in scalars.
+            const uint32_t nu = __builtin_amdgcn_readfirstlane(un[0]);
+            const uint32_t au = __builtin_amdgcn_readfirstlane(ua[0]);
+            const T eu = uniform_val(ue[0]);
+            const T *src[kUpMax];
+            T cf[kUpMax];
+            // entries past nu are block 0 with coefficient 0: read without a branch
 #pragma unroll
-                for (int h = 0; h < kUpMax; ++h) {
-                    src[h] = xsec + (uint64_t)__builtin_amdgcn_readfirstlane(ut[h]) * cdn;
-                    cf[h] = uniform_val(uc[h]);
-                }
-                T gx[2][kUpMax], gp_[2], ge[2];
-                uint32_t ga[2];
-                uint32_t hl[2][kWords];
-                // a fixed batch of loads per row slot (lanes past C_dn read row 0,
-                // hops past nu read row 0 of the sector with coefficient 0), so
-                // the wait for slot r leaves slot r + 1 in flight
-                const T *pp = has_p ? p : x;
-                if constexpr (kKeepHs) {
-                    if (c.loff != kept_loff || c.hs_dn != kept_hs) {
+            for (int h = 0; h < kUpMax; ++h) {
+                src[h] = xsec + (uint64_t)__builtin_amdgcn_readfirstlane(ut[h]) * cdn;
+                cf[h] = uniform_val(uc[h]);
+            }
+            T gx[2][kUpMax], gp_[2], ge[2];
+            uint32_t ga[2];
+            uint32_t hl[2][kWords];
+            // a fixed batch of loads per row slot (lanes past C_dn read row 0,
+            // hops past nu read row 0 of the sector with coefficient 0), so
+            // the wait for slot r leaves slot r + 1 in flight
+            const T *pp = has_p ? p : x;
+            if constexpr (kKeepHs) {
+                if (c.loff != kept_loff || c.hs_dn != kept_hs) {
 #pragma unroll
-                        for (int r = 0; r < R; ++r) {
-                            const int rd = tid + r * kRowsBlock;
-                            const int rc = rd < (int)cdn ? rd : 0;
-                            if constexpr (kKeepDn) rows_load_list(slists + (size_t)rc * kWords, hlc[r]);
-                            gac[r] = a.hs_states[c.hs_dn + rc];
-                            gec[r] = (T)a.hs_energy[c.hs_dn + rc];
-                        }
-                        kept_loff = c.loff;
-                        kept_hs = c.hs_dn;
+                    for (int r = 0; r < R; ++r) {
+                        const int rd = tid + r * kRowsBlock;
+                        const int rc = rd < (int)cdn ? rd : 0;
+                        if constexpr (kKeepDn) rows_load_list(slists + (size_t)rc * kWords, hlc[r]);
+                        gac[r] = a.hs_states[c.hs_dn + rc];
+                        gec[r] = (T)a.hs_energy[c.hs_dn + rc];
                     }
+                    kept_loff = c.loff;
+                    kept_hs = c.hs_dn;
                 }
-                auto gather = [&](int r, int s) {
-                    const int rd = tid + r * kRowsBlock;
-                    const int rc = rd < (int)cdn ? rd : 0;
+            }
+            auto gather = [&](int r, int s) {
+                const int rd = tid + r * kRowsBlock;
+                const int rc = rd < (int)cdn ? rd : 0;
 #pragma unroll
-                    for (int h = 0; h < kUpMax; ++h) gx[s][h] = src[h][rc];
-                    if constexpr (!kKeepDn) rows_load_list(slists + (size_t)rc * kWords, hl[s]);
-                    if constexpr (!kKeepHs) {
-                        ga[s] = a.hs_states[c.hs_dn + rc];
-                        ge[s] = (T)a.hs_energy[c.hs_dn + rc];
-                    }
-                    if constexpr (LZ) gp_[s] = pp[base + rc];
-                };
-                gather(0, 0);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int s = r & 1;
-                    if (r + 1 < R) gather(r + 1, s ^ 1);
-                    const int rd = tid + r * kRowsBlock;
-                    const uint32_t(&hlr)[kWords] = kKeepDn ? hlc[kKeepDn ? r : 0] : hl[s];
-                    const uint32_t gar = kKeepHs ? gac[kKeepHs ? r : 0] : ga[s];
-                    const T ger = kKeepHs ? gec[kKeepHs ? r : 0] : ge[s];
-                    const T acc = rows_down<T, UT>(hlr, bb, amp, rd < (int)cdn);
-                    if (rd < (int)cdn) {
-                        const T xv = reinterpret_cast<const T *>(bb)[rd];
-                        const T dg = eu + ger + rows_u_energy<T>(au & gar, a, ul);
-                        T v = fma_t(dg, xv, UT ? tu * acc : acc);
-                        // cf = 0 and gx = x[row 0] past nu: those terms add an exact zero
-#pragma unroll
-                        for (int h = 0; h < kUpMax; ++h) v = fma_t(cf[h], gx[s][h], v);
-                        v = rows_up_tail<T, true>(xsec, ut, uc, cdn, (uint32_t)rd, nu, v);
-                        const uint64_t row = base + rd;
-                        if constexpr (LZ) {
-                            const T uu = lz_out(v, c1, c2, gp_[s], has_p);
-                            out[row] = uu;
-                            dot = __builtin_fma((double)xv, (double)uu, dot);
-                        } else {
-                            out[row] = v;
-                        }
-                    }
-                }
-            } else if (sizeof(T) == 4 && R <= (int)rows_slots(UT) && c.gp == 0) {
-                // Several alpha_up blocks per tile (C_dn <= 1024), one per row
-                // slot: lane tid owns alpha_dn = tid in every block, so its
-                // down-hop list, half state and energy serve all of them, and
-                // the up-hop gathers of block r + 1 are in flight while block r
-                // computes.  Same sums as the one-block path.
-                const int rd = tid;
-                const bool valid = rd < (int)cdn;
-                const int rc = valid ? rd : 0;
-                T gx[2][kUpMax], cfs[2][kUpMax], gp_[2];
-                uint32_t hl1[kWords];
-                uint32_t ga1 = 0;
-                T ge1 = 0;
-                const T *pp = has_p ? p : x;
-                if constexpr (kKeepHs) {
-                    // only slot 0's copies: tagged so that the one-block path reloads all
-                    const uint32_t tag = c.loff | 0x80000000u;
-                    if (tag != kept_loff || c.hs_dn != kept_hs) {
-                        if constexpr (kKeepDn) rows_load_list(slists + (size_t)rc * kWords, hlc[0]);
-                        gac[0] = a.hs_states[c.hs_dn + rc];
-                        gec[0] = (T)a.hs_energy[c.hs_dn + rc];
-                        kept_loff = tag;
-                        kept_hs = c.hs_dn;
-                    }
-                }
-                if constexpr (!kKeepDn) rows_load_list(slists + (size_t)rc * kWords, hl1);
+                for (int h = 0; h < kUpMax; ++h) gx[s][h] = src[h][rc];
+                if constexpr (!kKeepDn) rows_load_list(slists + (size_t)rc * kWords, hl[s]);
                 if constexpr (!kKeepHs) {
-                    ga1 = a.hs_states[c.hs_dn + rc];
-                    ge1 = (T)a.hs_energy[c.hs_dn + rc];
+                    ga[s] = a.hs_states[c.hs_dn + rc];
+                    ge[s] = (T)a.hs_energy[c.hs_dn + rc];
                 }
-                const uint32_t(&hld)[kWords] = kKeepDn ? hlc[0] : hl1;
-                const uint32_t gad = kKeepHs ? gac[0] : ga1;
-                const T ged = kKeepHs ? gec[0] : ge1;
-                const int nblk = (int)c.nblk;
-                auto gather = [&](int g, int sl) {
-                    // entries past the block's hops are block 0 with coefficient 0
+                if constexpr (LZ) gp_[s] = pp[base + rc];
+            };
+            gather(0, 0);
 #pragma unroll
-                    for (int h = 0; h < kUpMax; ++h) {
-                        const uint32_t t = __builtin_amdgcn_readfirstlane(ut[g * kRowsNB + h]);
-                        gx[sl][h] = xsec[(uint64_t)t * cdn + rc];
-                        cfs[sl][h] = uniform_val(uc[g * kRowsNB + h]);
-                    }
-                    if constexpr (LZ) gp_[sl] = pp[base + (uint64_t)g * cdn + rc];
-                };
-                gather(0, 0);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    if (r >= nblk) break;
-                    const int sl = r & 1;
-                    if (r + 1 < R && r + 1 < nblk) gather(r + 1, sl ^ 1);
-                    const unsigned char *xb = bb + (size_t)r * (cdn + 1) * sizeof(T);
-                    const T acc = rows_down<T, UT>(hld, xb, amp, valid);
-                    if (valid) {
-                        const uint32_t nu = __builtin_amdgcn_readfirstlane(un[r]);
-                        const uint32_t au = __builtin_amdgcn_readfirstlane(ua[r]);
-                        const T eu = uniform_val(ue[r]);
-                        const T xv = reinterpret_cast<const T *>(xb)[rd];
-                        const T dg = eu + ged + rows_u_energy<T>(au & gad, a, ul);
-                        T v = fma_t(dg, xv, UT ? tu * acc : acc);
-#pragma unroll
-                        for (int h = 0; h < kUpMax; ++h) v = fma_t(cfs[sl][h], gx[sl][h], v);
-                        v = rows_up_tail<T, true>(xsec, ut + r * kRowsNB, uc + r * kRowsNB, cdn, (uint32_t)rd,
-                                                  nu, v);
-                        const uint64_t row = base + (uint64_t)r * cdn + rd;
-                        if constexpr (LZ) {
-                            const T uu = lz_out(v, c1, c2, gp_[sl], has_p);
-                            out[row] = uu;
-                            dot = __builtin_fma((double)xv, (double)uu, dot);
-                        } else {
-                            out[row] = v;
-                        }
-                    }
-                }
-            } else {
-                // several small blocks per tile: block data per lane from LDS; the
-                // first kUpMax up-hop gathers are issued before the LDS work
-                const int g = tid / (int)cdn;
-                if (g < (int)c.nblk && g < (int)c.gp) {
-                    const int rd = tid - g * (int)cdn;
-                    const uint64_t row = base + (uint64_t)g * cdn + rd;
-                    const uint32_t nu = un[g];
-                    // entries past nu are block 0 with coefficient 0: no branch
-                    T gx[kUpMax];
-#pragma unroll
-                    for (int h = 0; h < kUpMax; ++h) gx[h] = xsec[(uint64_t)ut[g * kRowsNB + h] * cdn + rd];
-                    uint32_t hl[kWords];
-                    rows_load_list(slists + (size_t)rd * kWords, hl);
-                    const T pv = has_p ? p[row] : (T)0;
-                    const uint32_t adr = a.hs_states[c.hs_dn + rd];
-                    const T edr = (T)a.hs_energy[c.hs_dn + rd];
-                    const unsigned char *xb = bb + (size_t)g * (cdn + 1) * sizeof(T);
-                    const T acc = rows_down<T, UT>(hl, xb, amp, true);
-                    const T xv = reinterpret_cast<const T *>(xb)[rd];
-                    const T dg = ue[g] + edr + rows_u_energy<T>(ua[g] & adr, a, ul);
+            for (int r = 0; r < R; ++r) {
+                const int s = r & 1;
+                if (r + 1 < R) gather(r + 1, s ^ 1);
+                const int rd = tid + r * kRowsBlock;
+                const uint32_t(&hlr)[kWords] = kKeepDn ? hlc[kKeepDn ? r : 0] : hl[s];
+                const uint32_t gar = kKeepHs ? gac[kKeepHs ? r : 0] : ga[s];
+                const T ger = kKeepHs ? gec[kKeepHs ? r : 0] : ge[s];
+                const T acc = rows_down<T, UT>(hlr, bb, amp, rd < (int)cdn);
+                if (rd < (int)cdn) {
+                    const T xv = reinterpret_cast<const T *>(bb)[rd];
+                    const T dg = eu + ger + rows_u_energy<T>(au & gar, a, ul);
                     T v = fma_t(dg, xv, UT ? tu * acc : acc);
+                    // cf = 0 and gx = x[row 0] past nu: those terms add an exact zero
 #pragma unroll
-                    for (int h = 0; h < kUpMax; ++h) v = fma_t(uc[g * kRowsNB + h], gx[h], v);
-                    v = rows_up_tail<T, false>(xsec, ut + g * kRowsNB, uc + g * kRowsNB, cdn, (uint32_t)rd, nu, v);
+                    for (int h = 0; h < kUpMax; ++h) v = fma_t(cf[h], gx[s][h], v);
+                    v = rows_up_tail<T>(xsec, ut, uc, cdn, (uint32_t)rd, nu, v);
+                    const uint64_t row = base + rd;
                     if constexpr (LZ) {
-                        const T uu = lz_out(v, c1, c2, pv, has_p);
+                        const T uu = lz_out(v, c1, c2, gp_[s], has_p);
                         out[row] = uu;
                         dot = __builtin_fma((double)xv, (double)uu, dot);
                     } else {
@@ -1148,8 +1006,8 @@ __global__ void __launch_bounds__(kRowsBlock) hv_rows_kernel(HvArgs a) {
         }
         // next tile: up-hop targets, negated copy of the staged rows, zeros
         if (has_next) {
-            rows_uplists<T>(a, rt, n.nblk, au_n, eu_n, nb2, LL);
-            rows_pre_store<T>(nb2, LL.cs, n.nblk, n.cdn, pre);
+            rows_uplists<T>(a, rt, au_n, eu_n, nb2, LL);
+            rows_pre_store<T>(nb2, LL.cs, n.cdn, pre);
         }
         __syncthreads();
         if (a.ep.partial && tid < 64) {
@@ -1350,7 +1208,7 @@ __global__ void __launch_bounds__(kBlockLanes) hv_block_kernel(HvArgs a, BlockUp
             for (int h = 0; h < kUpMax; ++h) v = fma_t(cf[h], g[h], v);
             // the rest in groups of four, in the order rows_up_tail sums them
             if (!kEarlyTail) {
-                v = rows_up_tail<T, true>(xsec, lt, lc, cdn, (uint32_t)rd, nu, v);
+                v = rows_up_tail<T>(xsec, lt, lc, cdn, (uint32_t)rd, nu, v);
             } else if (tail) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) v = fma_t(uniform_val(lc[kUpMax + q]), g2[q], v);
@@ -1385,6 +1243,304 @@ __global__ void __launch_bounds__(kBlockLanes) hv_block_kernel(HvArgs a, BlockUp
             double w = tid < kRowsWaves ? red[tid] : 0.0;
             for (int o = kRowsWaves / 2; o > 0; o >>= 1) w += __shfl_down(w, o, 64);
             if (tid == 0) a.ep.partial[c.slot] = active ? w : 0.0;
+        }
+    }
+}
+
+// ------------------------------------------------------------------------
+// Panel kernel (launch shapes G = 0 and -2) for sectors whose block of x fits
+// one panel: C_dn <= 1024 in fp32, <= 512 in fp64.  A 512-lane workgroup takes
+// a run of alpha_up blocks of one sector; each lane keeps its spin-down
+// configurations (two in fp32, one in fp64) over the whole run, so their
+// down-hop lists are decoded once per run into registers, an LDS byte offset
+// and a signed amplitude per hop, and a down-hop costs one LDS read and one
+// fused multiply-add per row.  C_dn of a few hundred leaves room for several
+// groups of whole waves, each on an alpha_up of its own, so alpha_up is the
+// same across a wave: its up-hop targets and amplitudes (hv_uplists_kernel)
+// are scalar loads, a gather is a scalar base plus the lane's offset, and a
+// branch on the number of hops costs no lane anything.  Four rows of x per
+// group are staged at a time in one half of a double buffer, one barrier each,
+// while the next four are on their way to registers; a lane stages just the
+// elements whose rows it sums.
+// The rows kernel that took these sectors before read a list of 32 or 64 bytes
+// and, with bond-dependent hopping, an amplitude from LDS per hop, for every
+// row.  All 169 sectors of the 12-site impurity model in fp32 (16.8 M rows):
+// 172 -> 72 us; 10 sites in fp64 24 -> 14; 14-site chain with (7, 3) 29 -> 19
+// (fp64) and 21 -> 11 (fp32); 8-site chain with (3, 5) 6.8 -> 4.7.
+// What bounds it: at 16 waves a CU (128 registers) the gathers' latency; the
+// vector units are busy 39% of the time, the address units 47%, LDS 21%, and
+// the L2s hand out 10 TB/s.  Gathering one alpha_up ahead (76 -> 80 us), half
+// the hops in registers (72 -> 75), up-hop lists through LDS (75) and 80
+// registers for 24 waves (spills, 194) were all slower.
+// Terms are summed in the order of the rows kernel with the same fused
+// operations, so the products are bitwise equal.
+// ------------------------------------------------------------------------
+constexpr int kPanelLanes = 512;
+constexpr int kPanelWaves = kPanelLanes / 64;
+constexpr int kPanelStage = 4;              // alpha_up per group and stage
+constexpr uint32_t kPanelMaxIts = 16;       // alpha_up per group and workgroup
+constexpr uint32_t kPanelBytes = 4096;      // x elements of a slot: 512 lanes of 8 bytes
+constexpr uint32_t kPanelSlot = kPanelBytes + 16;  // and a zero
+constexpr uint32_t kPanelSign = 0x8000u;    // list offset bit of a negative coefficient
+template <class T>
+__host__ __device__ constexpr int panel_rows() { return 8 / (int)sizeof(T); }  // alpha_dn per lane
+__host__ __device__ inline uint32_t panel_lanes(uint32_t cdn, uint32_t rows) {  // of a group: whole waves
+    return ((cdn + rows - 1) / rows + 63) & ~63u;
+}
+
+inline size_t panel_lds_bytes(size_t tsz) {
+    return 2 * kPanelStage * (size_t)kPanelSlot + kRowsNB * tsz + kPanelWaves * sizeof(double);
+}
+
+// Scalar loads: the lists are not written while a product runs.
+template <class V>
+__device__ __forceinline__ V scalar_at(const V *p, uint32_t i) {
+    return reinterpret_cast<const __attribute__((address_space(4))) V *>(reinterpret_cast<uintptr_t>(p))[i];
+}
+
+template <class T>
+struct PanelUp {  // one alpha_up, in scalar registers
+    uint32_t n, alpha, t[kUpMax];
+    T e, c[kUpMax];
+};
+
+template <class T, bool LZ, bool UT>
+__global__ void __launch_bounds__(kPanelLanes, 4) hv_panel_kernel(HvArgs a, BlockUpLists<T> up) {
+    constexpr int R = panel_rows<T>();
+    constexpr int S = kPanelStage;
+    __shared__ __align__(16) unsigned char xl[2 * S * kPanelSlot];
+    __shared__ T amp[kRowsNB];
+    __shared__ double red[kPanelWaves];
+    uint32_t ti;
+    if (a.binned) {
+        const uint32_t xcd = blockIdx.x % kXcd;
+        ti = a.xoff[xcd] + blockIdx.x / kXcd;
+        if (ti >= a.xoff[xcd + 1]) return;  // whole workgroup: no barrier is skipped by part of it
+    } else {
+        ti = blockIdx.x;
+        if (ti >= a.n_tiles) return;
+    }
+    const uint32_t tid = threadIdx.x;
+    uint4 q[2];
+    rows_desc_load(a.rdesc, ti, q);
+    const RowsTile c = rows_desc_uniform(q);
+    const T *x = static_cast<const T *>(a.x);
+    T *out = static_cast<T *>(a.out);
+    const T *p = static_cast<const T *>(a.ep.p);
+    if (a.ep.basis_j) {
+        const int64_t j = *a.ep.basis_j;
+        x += (uint64_t)j * a.ep.basis_stride;
+        p = j > 0 ? x - a.ep.basis_stride : x;
+    }
+    const bool active = !a.ep.active || __builtin_amdgcn_readfirstlane(a.ep.active[c.sector]) != 0;
+    if (!active) {  // uniform over the workgroup
+        if (a.ep.partial && tid == 0) a.ep.partial[c.slot] = 0.0;
+        return;
+    }
+    const uint32_t cdn = c.cdn;
+    const uint32_t P = panel_lanes(cdn, R);
+    const uint32_t g = __builtin_amdgcn_readfirstlane(tid / P);
+    const uint32_t lane = tid - g * P;
+    const bool in = g < c.gp;                       // the wave has a group (uniform)
+    const uint32_t gbase = g * P * R * (uint32_t)sizeof(T);  // its elements in a slot
+    bool ok[R];
+    uint32_t rc[R], ro[R];  // alpha_dn and its byte offset in a block (a scalar base and this address a row)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t rd = lane + r * P;
+        ok[r] = in && rd < cdn;
+        rc[r] = ok[r] ? rd : cdn - 1;
+        ro[r] = rc[r] * (uint32_t)sizeof(T);
+    }
+    const T *xt = x + c.base, *xsec = x + c.soff;
+    auto at = [](const T *block, uint32_t o) {
+        return *reinterpret_cast<const T *>(reinterpret_cast<const unsigned char *>(block) + o);
+    };
+    // the first stage's rows, the lists and the spin-down half are in flight together
+    const uint32_t nit = (c.nblk + c.gp - 1) / c.gp;
+    T pre[S][R];
+    auto load_rows = [&](uint32_t it0) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            if (it0 + s >= nit) break;
+            uint32_t ru = (it0 + s) * c.gp + g;
+            ru = ru < c.nblk ? ru : c.nblk - 1;
+            const T *src = xt + (uint64_t)ru * cdn;
+#pragma unroll
+            for (int r = 0; r < R; ++r) pre[s][r] = at(src, ro[r]);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int r = 0; r < R; ++r) pre[s][r] = (T)0;
+    if (in) load_rows(0);
+    constexpr int kWords = UT ? kRowsNB / 2 : kRowsNB;
+    const uint32_t *slists = static_cast<const uint32_t *>(a.lists) + (size_t)c.loff * kWords;
+    uint32_t hl[R][kWords], adr[R];
+    T edr[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        rows_load_list(slists + (size_t)rc[r] * kWords, hl[r]);
+        adr[r] = a.hs_states[c.hs_dn + rc[r]];
+        edr[r] = (T)a.hs_energy[c.hs_dn + rc[r]];
+    }
+    if (!UT && tid < kRowsNB) amp[tid] = tid < (uint32_t)a.nb ? (T)a.bamp[tid] : (T)0;
+    if (tid < 2 * S) *reinterpret_cast<T *>(xl + tid * kPanelSlot + kPanelBytes) = (T)0;
+    const bool has_p = LZ && a.ep.c2;
+    const T c1 = LZ ? uniform_val((T)a.ep.c1[c.sector]) : (T)1;
+    const T c2 = has_p ? uniform_val((T)a.ep.c2[c.sector]) : (T)0;
+    const T tu = (T)a.bamp[0];
+    __syncthreads();
+    // hop u of row r: LDS byte offset in a slot and signed amplitude (entries
+    // past the hops: the slot's zero, with amplitude 0)
+    uint32_t off[R][kRowsNB];
+    T cf[R][kRowsNB];
+    uint32_t nw = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t n = ok[r] ? (UT ? hl[r][kWords - 1] >> 16 : hl[r][kWords - 1]) : 0u;
+        nw = nw > n ? nw : n;
+#pragma unroll
+        for (int u = 0; u < kRowsNB - 1; ++u) {
+            const bool live = (uint32_t)u < n;
+            const uint32_t e = UT ? (hl[r][u >> 1] >> ((u & 1) * 16)) & 0xFFFFu : hl[r][u];
+            const T mag = UT ? (T)1 : amp[(e >> 16) & (kRowsNB - 1)];
+            off[r][u] = live ? gbase + (e & (kPanelSign - 1)) : kPanelBytes;
+            cf[r][u] = live ? ((e & kPanelSign) ? -mag : mag) : (T)0;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t m = __shfl_xor(nw, o, 64);
+        nw = nw > m ? nw : m;
+    }
+    nw = __builtin_amdgcn_readfirstlane(nw);
+    auto load_up = [&](uint32_t ru, PanelUp<T> &w) {
+        const uint32_t hsu = __builtin_amdgcn_readfirstlane(c.hs_up0 + (ru < c.nblk ? ru : c.nblk - 1));
+        w.n = scalar_at(up.n, hsu);
+        w.alpha = (scalar_at(reinterpret_cast<const uint32_t *>(a.hs_states), hsu >> 1) >> ((hsu & 1) * 16)) & 0xFFFFu;
+        w.e = (T)scalar_at(a.hs_energy, hsu);
+#pragma unroll
+        for (int h = 0; h < kUpMax; ++h) {
+            w.t[h] = scalar_at(up.tgt, hsu * kRowsNB + h);
+            w.c[h] = scalar_at(up.coef, hsu * kRowsNB + h);
+        }
+    };
+    double dot = 0.0;
+    PanelUp<T> wu;
+    if (in) load_up(g, wu);
+    auto stage = [&](uint32_t it0, auto half) {
+        constexpr uint32_t kHalf = decltype(half)::value * S * kPanelSlot;
+        T xv[S][R];
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                xv[s][r] = pre[s][r];
+                if (ok[r])
+                    *reinterpret_cast<T *>(xl + kHalf + s * kPanelSlot + gbase + (lane + r * P) * (uint32_t)sizeof(T)) =
+                        xv[s][r];
+            }
+        // a wave is past this barrier only when all have read the other half
+        __syncthreads();
+        if (!in) return;
+        if (it0 + S < nit) load_rows(it0 + S);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const uint32_t ru = (it0 + s) * c.gp + g;
+            if (ru >= c.nblk) break;
+            // up-hops in pairs (the odd one out is block 0 with amplitude 0)
+            T gx[kUpMax][R];
+#pragma unroll
+            for (int h = 0; h < kUpMax; h += 2)
+                if ((uint32_t)h < wu.n)
+#pragma unroll
+                    for (int i = h; i < h + 2; ++i) {
+                        const T *src = xsec + (size_t)(wu.t[i] * cdn);
+#pragma unroll
+                        for (int r = 0; r < R; ++r) gx[i][r] = at(src, ro[r]);
+                    }
+            const uint64_t row = c.base + (uint64_t)ru * cdn;
+            T pv[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) pv[r] = has_p ? at(p + row, ro[r]) : (T)0;
+            const PanelUp<T> w = wu;
+            load_up(ru + c.gp, wu);  // the next alpha_up's lists, during this one's sums
+            T acc[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[r] = (T)0;
+#pragma unroll
+            for (int u0 = 0; u0 < kRowsNB; u0 += 4)
+                if (u0 == 0 || (uint32_t)u0 < nw)
+#pragma unroll
+                    for (int u = u0; u < u0 + 4 && u < kRowsNB - 1; ++u)
+#pragma unroll
+                        for (int r = 0; r < R; ++r)
+                            acc[r] = fma_t(cf[r][u],
+                                           *reinterpret_cast<const T *>(xl + kHalf + s * kPanelSlot + off[r][u]), acc[r]);
+            T ue[R];
+            if (a.U_uniform) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) ue[r] = (T)(a.U0 * (double)__popc(w.alpha & adr[r]));
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) ue[r] = (T)0;
+                for (uint32_t m = w.alpha & a.Umask; m; m &= m - 1) {
+                    const int i = __ffs(m) - 1;
+                    const T u = (T)a.U[i];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) ue[r] += ((adr[r] >> i) & 1) ? u : (T)0;
+                }
+            }
+            T v[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const T dg = w.e + edr[r] + ue[r];
+                v[r] = fma_t(dg, xv[s][r], UT ? tu * acc[r] : acc[r]);
+            }
+#pragma unroll
+            for (int h = 0; h < kUpMax; h += 2)
+                if ((uint32_t)h < w.n)
+#pragma unroll
+                    for (int i = h; i < h + 2; ++i)
+#pragma unroll
+                        for (int r = 0; r < R; ++r) v[r] = fma_t(w.c[i], gx[i][r], v[r]);
+            if (w.n > (uint32_t)kUpMax) {
+                const uint32_t hsu = __builtin_amdgcn_readfirstlane(c.hs_up0 + ru);
+                for (uint32_t h = kUpMax; h < w.n; ++h) {
+                    const T *src = xsec + (size_t)(scalar_at(up.tgt, hsu * kRowsNB + h) * cdn);
+                    const T ch = scalar_at(up.coef, hsu * kRowsNB + h);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) v[r] = fma_t(ch, at(src, ro[r]), v[r]);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (ok[r]) {
+                    T *dst = reinterpret_cast<T *>(reinterpret_cast<unsigned char *>(out + row) + ro[r]);
+                    if constexpr (LZ) {
+                        const T uu = lz_out(v[r], c1, c2, pv[r], has_p);
+                        *dst = uu;
+                        dot = __builtin_fma((double)xv[s][r], (double)uu, dot);
+                    } else {
+                        *dst = v[r];
+                    }
+                }
+        }
+    };
+    for (uint32_t it0 = 0; it0 < nit; it0 += 2 * S) {
+        stage(it0, std::integral_constant<uint32_t, 0>{});
+        if (it0 + S < nit) stage(it0 + S, std::integral_constant<uint32_t, 1>{});
+    }
+    // the tile's partial of <x, u>: per wave, then lane 0 adds the eight
+    if (a.ep.partial) {
+        for (int o = 32; o > 0; o >>= 1) dot += __shfl_down(dot, o, 64);
+        if ((tid & 63) == 0) red[tid >> 6] = dot;
+        __syncthreads();
+        if (tid == 0) {
+            double w = 0.0;
+            for (int i = 0; i < kPanelWaves; ++i) w += red[i];
+            a.ep.partial[c.slot] = w;
         }
     }
 }
@@ -1709,7 +1865,6 @@ void fill_args(const mbr_hubbard *h, HvArgs &a, const void *x, void *out, const 
     }
     a.upcap = h->upcap;
     a.lists = h->d_lists.p;
-    a.rgmax = h->rows_gmax;
     a.t_uniform = h->t_uniform ? 1 : 0;
     a.maxblk = h->maxblk;
     a.ep = ep;
@@ -1723,7 +1878,7 @@ void fill_args(const mbr_hubbard *h, HvArgs &a, const void *x, void *out, const 
 template <class T, bool LZ, int R>
 mbr_status launch_rows_r(const mbr_hubbard *h, const HvArgs &a, unsigned cap, hipStream_t s) {
     auto kern = h->t_uniform ? hv_rows_kernel<T, LZ, R, true> : hv_rows_kernel<T, LZ, R, false>;
-    const size_t lds = rows_lds_layout(a.rtab_entries, a.xcap, a.rgmax, sizeof(T)).total;
+    const size_t lds = rows_lds_layout(a.rtab_entries, a.xcap, sizeof(T)).total;
     if (lds > 64 * 1024)
         MBR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -1740,7 +1895,9 @@ mbr_status launch_rows_r(const mbr_hubbard *h, const HvArgs &a, unsigned cap, hi
 template <class T, bool LZ>
 mbr_status launch_rows(const mbr_hubbard *h, const HvArgs &a, unsigned cap, int R, hipStream_t s) {
     switch (R) {
-        case 1: return launch_rows_r<T, LZ, 1>(h, a, cap, s);
+        case 1:  // fp64 only: in fp32 these sectors fit a panel
+            if constexpr (sizeof(T) == 8) return launch_rows_r<T, LZ, 1>(h, a, cap, s);
+            [[fallthrough]];
         case 2: return launch_rows_r<T, LZ, 2>(h, a, cap, s);
         case 3: return launch_rows_r<T, LZ, 3>(h, a, cap, s);
         default: return launch_rows_r<T, LZ, 4>(h, a, cap, s);
@@ -1758,6 +1915,16 @@ mbr_status launch_block(const mbr_hubbard *h, HvArgs a, unsigned grid, hipStream
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     BlockUpLists<T> up{h->d_up_tgt.as<uint32_t>(), h->d_up_coef.as<T>(), h->d_up_n.as<uint32_t>()};
     if (grid) kern<<<grid, kBlockLanes, lds, s>>>(a, up);
+    MBR_HIP(hipGetLastError());
+    return MBR_OK;
+}
+
+// Panel kernel over `grid` workgroups (descriptors and ranges set in a).
+template <class T, bool LZ>
+mbr_status launch_panel(const mbr_hubbard *h, const HvArgs &a, unsigned grid, hipStream_t s) {
+    auto kern = h->t_uniform ? hv_panel_kernel<T, LZ, true> : hv_panel_kernel<T, LZ, false>;
+    BlockUpLists<T> up{h->d_up_tgt.as<uint32_t>(), h->d_up_coef.as<T>(), h->d_up_n.as<uint32_t>()};
+    if (grid) kern<<<grid, kPanelLanes, 0, s>>>(a, up);
     MBR_HIP(hipGetLastError());
     return MBR_OK;
 }
@@ -1780,6 +1947,11 @@ mbr_status launch_t(const mbr_hubbard *h, const void *x, void *out, const HvEpil
         if (!h->flat_tiles.empty()) {
             if (ep.c1) return launch_flat<T, NCH, true>(a, ep.n_tiles, s);
             return launch_flat<T, NCH, false>(a, ep.n_tiles, s);
+        }
+        if (h->hsec[ep.sector].pan) {
+            a.rdesc = h->d_rdesc_slot.as<RowsTileDesc>() + h->hsec[ep.sector].slot0;
+            if (ep.c1) return launch_panel<T, true>(h, a, ep.n_tiles, s);
+            return launch_panel<T, false>(h, a, ep.n_tiles, s);
         }
         if (h->hsec[ep.sector].blk) {
             a.rdesc = h->d_rdesc_slot.as<RowsTileDesc>() + h->hsec[ep.sector].slot0;
@@ -1829,6 +2001,18 @@ mbr_status launch_t(const mbr_hubbard *h, const void *x, void *out, const HvEpil
         if (ep.c1) MBR_TRY((launch_block<T, true>(h, ab, grid, s)));
         else MBR_TRY((launch_block<T, false>(h, ab, grid, s)));
     }
+    if (!h->panel_tiles.empty()) {
+        HvArgs ap = a;
+        ap.rdesc = h->d_pdesc.as<RowsTileDesc>();
+        ap.n_tiles = (uint32_t)h->panel_tiles.size();
+        ap.binned = 1;
+        uint32_t most = 0;
+        for (int i = 0; i <= kXcd; ++i) ap.xoff[i] = h->panel_xoff[i];
+        for (int i = 0; i < kXcd; ++i) most = std::max(most, h->panel_xoff[i + 1] - h->panel_xoff[i]);
+        const unsigned grid = most * kXcd;
+        if (ep.c1) MBR_TRY((launch_panel<T, true>(h, ap, grid, s)));
+        else MBR_TRY((launch_panel<T, false>(h, ap, grid, s)));
+    }
     if (!h->rows_tiles.empty()) {
         HvArgs ar = a;
         ar.rdesc = h->d_rdesc.as<RowsTileDesc>();
@@ -1869,7 +2053,11 @@ std::vector<uint32_t> balanced_ranges(const std::vector<HvTile> &tiles, const st
     std::vector<double> cost(tiles.size());
     double tot = 0;
     for (size_t i = 0; i < tiles.size(); ++i) {
-        cost[i] = (double)tiles[i].nblk * hsec[tiles[i].sector].cdn;
+        const HvSector &sc = hsec[tiles[i].sector];
+        // a panel's workgroup is held for its blocks per group and its start
+        // (12-site impurity model 73.9 us without the start, 72.4 with; 11 sites
+        // 29.9 and 27.5)
+        cost[i] = sc.pan ? (double)((tiles[i].nblk + sc.gp - 1) / sc.gp + 3) : (double)tiles[i].nblk * sc.cdn;
         tot += cost[i];
     }
     std::vector<uint32_t> r(n + 1, 0);
@@ -1884,8 +2072,9 @@ std::vector<uint32_t> balanced_ranges(const std::vector<HvTile> &tiles, const st
     return r;
 }
 
-// Down-hop lists of the rows kernel, one set per n_dn it serves (lrows rows in
-// all), ranked on the device with the launch shape's table.
+// Down-hop lists, one set per n_dn that the rows, block and panel kernels serve
+// (lrows rows in all), ranked on the device with the launch shape's table.
+enum : uint8_t { kListRows, kListBlock, kListPanel };
 mbr_status build_lists(mbr_hubbard *h, uint32_t lrows, hipStream_t s) {
     if (h->lists_ndn.empty()) return MBR_OK;
     const uint32_t tsz = h->precision == MBR_F64 ? 8 : 4;
@@ -1894,12 +2083,12 @@ mbr_status build_lists(mbr_hubbard *h, uint32_t lrows, hipStream_t s) {
     HvArgs a{};
     fill_args(h, a, nullptr, nullptr, HvEpilogue{});
     const uint32_t rcs =
-        (uint32_t)rows_lds_layout(a.rtab_entries, h->rows_xcap, h->rows_gmax, tsz).cs;
+        (uint32_t)rows_lds_layout(a.rtab_entries, h->rows_xcap, tsz).cs;
     const uint32_t bcs = (uint32_t)(((size_t)h->block_xcap * tsz + 15) & ~(size_t)15);
     uint32_t row0 = 0;
     for (size_t li = 0; li < h->lists_ndn.size(); ++li) {
         const uint32_t nd = h->lists_ndn[li];
-        const uint32_t cs = h->lists_blk[li] ? bcs : rcs;
+        const uint32_t cs = h->lists_for[li] == kListPanel ? kPanelSign : h->lists_for[li] == kListBlock ? bcs : rcs;
         const uint32_t cdn = (uint32_t)binom(h->L, (int)nd);
         uint32_t *lists = h->d_lists.as<uint32_t>() + (size_t)row0 * words;
         const unsigned grid = (cdn + 255) / 256;
@@ -1913,7 +2102,7 @@ mbr_status build_lists(mbr_hubbard *h, uint32_t lrows, hipStream_t s) {
     return MBR_OK;
 }
 
-// Up-hop lists of every half state for the block kernel.
+// Up-hop lists of every half state for the block and panel kernels.
 mbr_status build_uplists(mbr_hubbard *h, hipStream_t s) {
     const uint32_t n_hs = h->hs_off[h->L + 1];
     const size_t tsz = h->precision == MBR_F64 ? 8 : 4;
@@ -1934,8 +2123,9 @@ mbr_status build_uplists(mbr_hubbard *h, hipStream_t s) {
 }
 
 // Rebuild the rank table, tiles, work ranges and LDS budgets for (k, G, block).
-// G = 0 selects the alpha_dn-stationary kernel for every sector it supports;
-// G = -2 the same, but sectors with C_dn > 512 go to the block kernel.
+// G = 0 selects the panel kernel for sectors that fit it and the
+// alpha_dn-stationary kernel for longer ones; G = -2 the block kernel instead of
+// the latter.
 mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     const int L = h->L;
     if (k < 1 || k > L || k > 16) MBR_FAIL(MBR_EINVAL, "k=%d outside 1..L", k);
@@ -1952,15 +2142,43 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     const int Gt = rows_shape ? 2 : G;  // tile-kernel blocks for sectors the rows kernel does not take
     const size_t xbudget = (Gt == 4 ? 112 : 56) * 1024;
     std::vector<HvSector> hsec;
-    std::vector<HvTile> tiles, rows_tiles, other_tiles, flat_tiles, block_tiles;
+    std::vector<HvTile> tiles, rows_tiles, other_tiles, flat_tiles, block_tiles, panel_tiles;
     uint64_t off = 0;
-    uint32_t slot = 0, xcap = 0, upcap = 0, maxblk = 0, rows_xcap = 0, rows_gmax = 1, lrows = 0, block_xcap = 0;
+    uint32_t slot = 0, xcap = 0, upcap = 0, maxblk = 0, rows_xcap = 0, lrows = 0, block_xcap = 0;
     std::vector<uint32_t> lists_ndn, lists_rows;
-    std::vector<uint8_t> lists_blk;
+    std::vector<uint8_t> lists_for;
     int rows_R = 1;
     bool t_uniform = true;  // every bond has one amplitude (the rows kernel's uniform-hopping instances)
     for (auto &b : h->bonds) t_uniform = t_uniform && b.t == h->bonds[0].t;
     const uint32_t nbm = (uint32_t)std::max(1, h->nb);
+    const uint32_t panel_r = (uint32_t)(8 / tsz);
+    auto takes_block = [&](uint64_t cup, uint32_t cdn) {
+        // (the block kernel addresses a sector with 32-bit byte offsets)
+        return G == -2 && cdn > kBlockMin && cdn + 1 <= kRowsMaxX && cup * cdn * tsz <= 0xFFFFFFFFull;
+    };
+    const bool lists_ok = rows_shape && h->nb <= kRowsNB - 1;
+    // With uniform hopping in fp32 the block kernel takes its sectors of 513 to
+    // 1024 as well: its down-hop is an LDS read and an add there, and one
+    // alpha_up a workgroup fills the chip sooner (12-site chain, 924 x 924, block
+    // 7.9 us, panel 8.8; with 3432 alpha_up the panel leads, 21 against 24).
+    auto takes_panel = [&](uint64_t cup, uint32_t cdn) {
+        return lists_ok && cdn <= kPanelBytes / tsz && !(t_uniform && takes_block(cup, cdn));
+    };
+    // Blocks per group of a panel: as many as leave a workgroup to every CU.
+    // A run's start costs about three blocks' time, so long runs are better
+    // where there are enough of them (12-site impurity model: 16 blocks 72 us,
+    // 8 78, 4 95, 1 252; 10-site half-filled chain: 1 block 4.6 us, 4 6.4,
+    // 16 15.0); past 16 the last round of workgroups costs what the starts save.
+    uint32_t panel_its = kPanelMaxIts;
+    for (; panel_its > 1; panel_its /= 2) {
+        uint64_t n = 0;
+        for (const mbr_spin_sector &sp : h->secs) {
+            const uint32_t cup = (uint32_t)binom(L, sp.n_up), cdn = (uint32_t)binom(L, sp.n_dn);
+            const uint32_t nblk = panel_its * ((uint32_t)kPanelLanes / panel_lanes(cdn, panel_r));
+            if (takes_panel(cup, cdn)) n += (cup + nblk - 1) / nblk;
+        }
+        if (n >= (uint64_t)device_cu_count()) break;
+    }
     for (size_t si = 0; si < h->secs.size(); ++si) {
         HvSector sc{};
         sc.off = off;
@@ -1969,12 +2187,18 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
         sc.hs_up = h->hs_off[h->secs[si].n_up];
         sc.hs_dn = h->hs_off[h->secs[si].n_dn];
         sc.rows = (rows_shape && sc.cdn + 1 <= kRowsMaxX && h->nb <= kRowsNB - 1) ? 1 : 0;
-        // (the block kernel addresses a sector with 32-bit byte offsets)
-        sc.blk = (G == -2 && sc.rows && sc.cdn > kBlockMin && (uint64_t)sc.cup * sc.cdn * tsz <= 0xFFFFFFFFull) ? 1 : 0;
-        if (sc.blk) sc.rows = 0;
+        sc.pan = takes_panel(sc.cup, sc.cdn) ? 1 : 0;
+        sc.blk = !sc.pan && lists_ok && takes_block(sc.cup, sc.cdn) ? 1 : 0;
+        if (sc.blk || sc.pan) sc.rows = 0;
         sc.magic = sc.cdn == 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / sc.cdn);
         uint32_t nblk;
-        if (sc.blk) {
+        if (sc.pan) {
+            sc.wide = 1;
+            sc.x_lds = 1;
+            sc.gp = (uint32_t)kPanelLanes / panel_lanes(sc.cdn, panel_r);
+            sc.R = panel_r;
+            nblk = sc.gp * panel_its;
+        } else if (sc.blk) {
             sc.wide = 1;
             sc.x_lds = 1;
             sc.gp = 1;
@@ -1987,25 +2211,11 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
         } else if (sc.rows) {
             sc.wide = 1;
             sc.x_lds = 1;
-            if (sc.cdn <= (uint32_t)kRowsBlock / 2) {
-                // blocks across lanes
-                sc.gp = std::min<uint32_t>(kRowsMaxG, kRowsBlock / sc.cdn);
-                sc.R = 1;
-                nblk = sc.gp;
-            } else if (sc.cdn <= (uint32_t)kRowsBlock && tsz == 4) {
-                // one block per row slot (gp = 0): rows_slots() blocks a tile
-                // (fp32; in fp64 the extra slots would not fit the registers)
-                sc.gp = 0;
-                nblk = std::min<uint32_t>(rows_slots(t_uniform), kRowsMaxX / (sc.cdn + 1));
-                sc.R = nblk;
-            } else {
-                // one block per tile, spread over ceil(C_dn / 1024) row slots
-                sc.gp = 1;
-                sc.R = (sc.cdn + kRowsBlock - 1) / kRowsBlock;
-                nblk = 1;
-            }
+            // one block per tile, spread over ceil(C_dn / 1024) row slots
+            sc.gp = 1;
+            sc.R = (sc.cdn + kRowsBlock - 1) / kRowsBlock;
+            nblk = 1;
             rows_R = std::max(rows_R, (int)sc.R);
-            rows_gmax = std::max(rows_gmax, std::max<uint32_t>(sc.gp, nblk));
         } else {
             sc.wide = sc.cdn >= kWideMin;
             if (sc.wide) {
@@ -2027,13 +2237,15 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
             t.rup0 = r;
             t.nblk = std::min(nblk, sc.cup - r);
             t.slot = slot++;
-            if (sc.blk) {
+            if (sc.pan) {
+                panel_tiles.push_back(t);
+            } else if (sc.blk) {
                 block_xcap = std::max(block_xcap, sc.cdn + 1);
                 block_tiles.push_back(t);
             } else if (flat) {
                 flat_tiles.push_back(t);
             } else if (sc.rows) {
-                rows_xcap = std::max(rows_xcap, t.nblk * (sc.cdn + 1));
+                rows_xcap = std::max(rows_xcap, sc.cdn + 1);
                 rows_tiles.push_back(t);
             } else {
                 if (sc.x_lds) xcap = std::max(xcap, t.nblk * sc.cdn);
@@ -2044,7 +2256,7 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
             tiles.push_back(t);
         }
         sc.nslots = slot - sc.slot0;
-        if (sc.rows || sc.blk) {  // down-hop lists are shared by the sectors of one n_dn
+        if (sc.rows || sc.blk || sc.pan) {  // down-hop lists are shared by the sectors of one n_dn
             const uint32_t nd = (uint32_t)h->secs[si].n_dn;
             auto it = std::find(lists_ndn.begin(), lists_ndn.end(), nd);
             const size_t li = (size_t)(it - lists_ndn.begin());
@@ -2052,7 +2264,7 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
                 // one n_dn is one C_dn, so its sectors all take the same kernel
                 lists_ndn.push_back(nd);
                 lists_rows.push_back(lrows);
-                lists_blk.push_back(sc.blk ? 1 : 0);
+                lists_for.push_back(sc.pan ? kListPanel : sc.blk ? kListBlock : kListRows);
                 lrows += sc.cdn;
             }
             sc.loff = lists_rows[li];
@@ -2069,9 +2281,10 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     const std::vector<uint32_t> rr = balanced_ranges(rows_tiles, hsec, kXcd);
     const std::vector<uint32_t> fr = balanced_ranges(flat_tiles, hsec, kXcd);
     const std::vector<uint32_t> br = balanced_ranges(block_tiles, hsec, kXcd);
+    const std::vector<uint32_t> pr = balanced_ranges(panel_tiles, hsec, kXcd);
     if (!block_tiles.empty() && block_lds_bytes(block_xcap, tsz) > kLdsMax)
         MBR_FAIL(MBR_EUNSUPPORTED, "block kernel needs %zu bytes of LDS", block_lds_bytes(block_xcap, tsz));
-    const size_t rows_lds = rows_lds_layout((uint32_t)((uint64_t)tab.nrows << k), rows_xcap, rows_gmax, tsz).total;
+    const size_t rows_lds = rows_lds_layout((uint32_t)((uint64_t)tab.nrows << k), rows_xcap, tsz).total;
     if (!rows_tiles.empty() && rows_lds > kLdsMax) MBR_FAIL(MBR_EUNSUPPORTED, "rows kernel needs %zu bytes of LDS", rows_lds);
     // commit
     h->tab = std::move(tab);
@@ -2094,11 +2307,12 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     h->rows_xcap = rows_xcap;
     h->rows_R = rows_R;
     h->lists_ndn = lists_ndn;
-    h->lists_blk = lists_blk;
+    h->lists_for = lists_for;
     h->block_tiles = block_tiles;
     h->block_xcap = block_xcap;
+    h->panel_tiles = panel_tiles;
+    for (int b = 0; b <= kXcd; ++b) h->panel_xoff[b] = pr[b];
     for (int b = 0; b <= kXcd; ++b) h->block_xoff[b] = br[b];
-    h->rows_gmax = rows_gmax;
     h->rows_grid = rows_grid;
     h->t_uniform = t_uniform;
     MBR_TRY(upload(h->d_tiles, other_tiles.data(), other_tiles.size() * sizeof(HvTile), s));
@@ -2114,24 +2328,27 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
             d.slot = t.slot;
             return d;
         };
-        for (const auto *tl : {&rows_tiles, &block_tiles})
+        for (const auto *tl : {&rows_tiles, &block_tiles, &panel_tiles})
             for (auto &t : *tl) {  // field widths of the packed descriptor
                 const HvSector &sc = hsec[t.sector];
                 if (sc.cdn > 0xFFF || sc.gp > 0xFF || t.nblk > 0xFFF || sc.hs_up + t.rup0 > 0xFFFF ||
                     sc.hs_dn > 0xFFFF || sc.loff > 0xFFFF || t.sector > 0xFFFF)
                     MBR_FAIL(MBR_EUNSUPPORTED, "rows-kernel tile descriptor out of range");
             }
-        std::vector<RowsTileDesc> rd, rs, bd;
+        std::vector<RowsTileDesc> rd, rs, bd, pd;
         for (auto &t : rows_tiles) rd.push_back(mk(t));
         for (auto &t : block_tiles) bd.push_back(mk(t));
+        for (auto &t : panel_tiles) pd.push_back(mk(t));
         for (auto &t : tiles) rs.push_back(mk(t));
         MBR_TRY(upload(h->d_rdesc, rd.data(), rd.size() * sizeof(RowsTileDesc), s));
         MBR_TRY(upload(h->d_bdesc, bd.data(), bd.size() * sizeof(RowsTileDesc), s));
+        MBR_TRY(upload(h->d_pdesc, pd.data(), pd.size() * sizeof(RowsTileDesc), s));
         MBR_TRY(upload(h->d_rdesc_slot, rs.data(), rs.size() * sizeof(RowsTileDesc), s));
     }
     for (int b = 0; b <= kXcd; ++b) h->rows_xoff[b] = rr[b];
     MBR_TRY(upload(h->d_secs, h->hsec.data(), h->hsec.size() * sizeof(HvSector), s));
     h->lds_bytes = std::max(other_tiles.empty() ? 0 : lds_bytes_for(h, tsz), rows_tiles.empty() ? 0 : rows_lds);
+    if (!panel_tiles.empty()) h->lds_bytes = std::max(h->lds_bytes, panel_lds_bytes(tsz));
     if (!block_tiles.empty()) h->lds_bytes = std::max(h->lds_bytes, block_lds_bytes(block_xcap, tsz));
     if (!flat_tiles.empty())
         h->lds_bytes = std::max<size_t>(h->lds_bytes, ((((size_t)h->tab.nrows << h->tab.k) * 2 + 15) & ~(size_t)15) +
@@ -2146,7 +2363,7 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     h->grid -= h->grid % kXcd;
     if (h->grid < kXcd) h->grid = kXcd;
     MBR_TRY(build_lists(h, lrows, s));
-    if (!block_tiles.empty()) MBR_TRY(build_uplists(h, s));
+    if (!block_tiles.empty() || !panel_tiles.empty()) MBR_TRY(build_uplists(h, s));
     h->generation++;
     return MBR_OK;
 }
@@ -2365,17 +2582,14 @@ mbr_status mbr_hubbard_create(const mbr_hubbard_desc *d, mbr_hubbard **out, void
         *out = h.release();
         return MBR_OK;
     }
-    // default launch shape: two lookups per half rank; the block kernel for
-    // sectors of more than 512 spin-down configurations, except in fp32 with
-    // bond-dependent hopping, where the rows kernel packs several of their
-    // blocks into a tile.  us per product, block / rows kernel: 12-site chain
-    // half filled 13.9 / 16.4 (fp64) and 8.1 / 24.7 (fp32), 14 sites with (4,7)
-    // 31.9 / 38.0; impurity model, 12 sites, all sectors 264 / 293 (fp64) and
-    // 184 / 168 (fp32).
+    // default launch shape: two lookups per half rank, and for the sectors too
+    // long for a panel the block kernel.  us per product, block / rows kernel:
+    // half filled chains of 12 and 14 sites 13.9 / 16.4 and 110 / 127 (fp64), of
+    // 14 sites 61 / 64 (fp32); impurity model, 14 sites half filled 113 / 167
+    // (fp64) and 77 / 110 (fp32), 13 sites with 4 to 8 down 767 / 1115 and
+    // 433 / 465.
     const int k = d->k > 0 ? std::min(d->k, L) : (L + 1) / 2;
-    bool uniform = true;
-    for (const mbr_bond &b : h->bonds) uniform = uniform && b.t == h->bonds[0].t;
-    mbr_status st = configure(h.get(), k, uniform || h->precision == MBR_F64 ? -2 : 0, 512, s);
+    mbr_status st = configure(h.get(), k, -2, 512, s);
     if (st != MBR_OK && d->k == 0) st = configure(h.get(), k, 1, 512, s);
     if (st != MBR_OK) return st;
     *out = h.release();

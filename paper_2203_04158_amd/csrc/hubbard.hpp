@@ -25,11 +25,12 @@ struct HvSector {
     uint32_t wide;    // lanes over alpha_dn with blocks in registers (1) or flattened rows (0)
     uint32_t x_lds;   // x blocks staged in LDS (1) or gathered from memory (0)
     uint32_t rows;    // handled by the alpha_dn-stationary kernel (1) or the tile kernel (0)
-    uint32_t gp;      // rows kernel: alpha_up blocks per tile (lanes over (block, alpha_dn))
-    uint32_t R;       // rows kernel: alpha_dn values per lane
-    uint32_t loff;    // rows kernel: first down-hop list row of the sector's n_dn
+    uint32_t gp;      // panel kernel: groups of a workgroup (1 in the rows and block kernels)
+    uint32_t R;       // rows, block and panel kernels: alpha_dn values per lane
+    uint32_t loff;    // rows, block and panel kernels: first down-hop list row of the sector's n_dn
     uint32_t magic;   // flat kernel: floor(2^32 / C_dn), to split a row index into (alpha_up, alpha_dn)
     uint32_t blk;     // handled by the block kernel (launch shape G = -2): one alpha_up block per workgroup
+    uint32_t pan;     // handled by the panel kernel (launch shapes G = 0, -2)
 };
 
 // Epilogue: y = H x (plain), or u = c1[s] (H x)_i - c2[s] p_i written to `out`
