@@ -469,13 +469,15 @@ __global__ void __launch_bounds__(kBlock) lz_next(const HvTile *tiles, uint32_t 
 constexpr int kKc = 8;
 constexpr uint32_t kFoldGroups = 64;   // groups per sector up to which lz_subtract sums the coefficients itself
 
-// Rows per merged group of the batched Gram-Schmidt kernels: 4096, so that one
-// block reduction serves many rows, but fewer where that would leave the chip
-// short of workgroups (eight per CU wanted).  Ten sites, 1,048,576 rows, 40
-// steps: 4.91 ms with 4,096 rows a group, 4.35 with 2,048, 4.31 with 512.
+// Rows per group of the Gram-Schmidt kernels: 4096 in batched steps, so that
+// one block reduction serves many rows, but fewer where that would leave the
+// chip short of workgroups (eight per CU wanted); a lone sector's steps take the
+// least.  Ten sites, 1,048,576 rows, 40 steps: 4.91 ms with 4,096 rows a group,
+// 4.35 with 2,048, 3.93 with 1,024, 4.28 with 512 (too many to sum in place).
+constexpr uint64_t kGroupMin = 1024;
 inline uint64_t group_rows(uint64_t total) {
     const uint64_t g = total / ((uint64_t)device_cu_count() * 8);
-    return g < 512 ? 512 : g > 4096 ? 4096 : g;
+    return g < kGroupMin ? kGroupMin : g > 4096 ? 4096 : g;
 }
 
 // Sums of eight values over the wave: three exchanges that halve the values a
@@ -814,9 +816,9 @@ struct mbr_lanczos {
     uint32_t n_slots = 0;
     std::vector<HvSector> secs;
     DevBuf d_tiles_slot, d_secs;
-    // reorthogonalising path: consecutive tiles of a sector merged into groups
-    // of at least kGroupRows rows, with their own slot numbering (rsecs holds
-    // the sectors with slot0/nslots over those slots); rt0/rnt per sector
+    // reorthogonalising path: groups of alpha_up blocks of a sector
+    // (group_rows), with their own slot numbering (rsecs holds the sectors with
+    // slot0/nslots over those slots); rt0/rnt per sector
     DevBuf d_rtiles, d_rsecs;
     std::vector<uint32_t> rt0, rnt;
     uint32_t n_rtiles = 0;
@@ -1011,12 +1013,8 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
     MBR_TRY(upload(lz->d_tiles_slot, tiles.data(), tiles.size() * sizeof(HvTile), s));
     MBR_TRY(upload(lz->d_secs, lz->secs.data(), lz->secs.size() * sizeof(HvSector), s));
     if (o->reorth) {
-        // batched steps: merge a sector's tiles (contiguous rows, slot order)
-        // into groups of at least kGroupRows rows, so there is one block
-        // reduction per group and basis vector instead of one per tile.
-        // Per-sector launches keep the tiles (a lone sector needs them all to
-        // fill the GPU).
-        const uint64_t grow = o->batched ? group_rows(lz->total) : 0;
+        // groups of whole alpha_up blocks of a sector, whatever the product's tiles
+        const uint64_t grow = o->batched ? group_rows(lz->total) : kGroupMin;
         std::vector<HvTile> groups;
         std::vector<HvSector> rsecs = lz->secs;
         lz->rt0.assign(lz->ns, 0);
@@ -1025,16 +1023,9 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
             const HvSector &sc = lz->secs[si];
             lz->rt0[si] = (uint32_t)groups.size();
             rsecs[si].slot0 = (uint32_t)groups.size();
-            for (uint32_t t = sc.slot0; t < sc.slot0 + sc.nslots;) {
-                HvTile g = tiles[t];
-                g.slot = (uint32_t)groups.size();
-                uint64_t rows = (uint64_t)g.nblk * sc.cdn;
-                for (++t; t < sc.slot0 + sc.nslots && rows < grow; ++t) {
-                    g.nblk += tiles[t].nblk;  // tiles[t] starts where the group ends
-                    rows += (uint64_t)tiles[t].nblk * sc.cdn;
-                }
-                groups.push_back(g);
-            }
+            const uint32_t nblk = (uint32_t)std::max<uint64_t>(1, grow / sc.cdn);
+            for (uint32_t r = 0; r < sc.cup; r += nblk)
+                groups.push_back({(uint32_t)si, r, std::min(nblk, sc.cup - r), (uint32_t)groups.size()});
             lz->rnt[si] = (uint32_t)groups.size() - lz->rt0[si];
             rsecs[si].nslots = lz->rnt[si];
         }
@@ -1045,7 +1036,7 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
         MBR_TRY(upload(lz->d_rtiles, groups.data(), groups.size() * sizeof(HvTile), s));
         MBR_TRY(upload(lz->d_rsecs, rsecs.data(), rsecs.size() * sizeof(HvSector), s));
     }
-    const size_t ns = lz->ns, m = lz->m, nsl = lz->n_slots;
+    const size_t ns = lz->ns, m = lz->m, nsl = std::max(lz->n_slots, lz->n_rtiles);
     if (o->reorth) {
         const double bytes = (double)lz->ld * lz->tsz * (m + 2);
         if (bytes > 250e9) MBR_FAIL(MBR_ENOMEM, "basis of %.1f GB", bytes / 1e9);
