@@ -266,8 +266,8 @@ __global__ void __launch_bounds__(kBlock) lz_update(const HvTile *tiles, uint32_
 // launch; here it adds 2.4 us to the update's 8.5.
 template <class T>
 __global__ void __launch_bounds__(kBlock) lz_alpha_update(const HvTile *tiles, uint32_t n_tiles,
-                                                          const HvSector *secs, T *__restrict__ u,
-                                                          const T *__restrict__ q, LzDev d, int m,
+                                                          const HvSector *secs, const HvSector *hsecs,
+                                                          T *__restrict__ u, const T *__restrict__ q, LzDev d, int m,
                                                           double tol, uint32_t s) {
     __shared__ double red[kRedWaves];
     __shared__ double c3s, sum_s;
@@ -276,7 +276,7 @@ __global__ void __launch_bounds__(kBlock) lz_alpha_update(const HvTile *tiles, u
             if (threadIdx.x == 0) d.pn[tiles[ti].slot] = 0.0;
         return;
     }
-    const double sum = sector_sum(d.pd + secs[s].slot0, secs[s].nslots, red);
+    const double sum = sector_sum(d.pd + hsecs[s].slot0, hsecs[s].nslots, red);
     if (threadIdx.x == 0) {
         const double a = d.c1[s] * sum;
         c3s = a * d.c1[s];
@@ -469,7 +469,7 @@ __global__ void __launch_bounds__(kBlock) lz_next(const HvTile *tiles, uint32_t 
 constexpr int kKc = 8;
 constexpr uint32_t kFoldGroups = 64;   // groups per sector up to which lz_subtract sums the coefficients itself
 
-// Rows per group of the Gram-Schmidt kernels: 4096 in batched steps, so that
+// Rows per group of the vector kernels: 4096 in batched steps, so that
 // one block reduction serves many rows, but fewer where that would leave the
 // chip short of workgroups (eight per CU wanted); a lone sector's steps take the
 // least.  Ten sites, 1,048,576 rows, 40 steps: 4.91 ms with 4,096 rows a group,
@@ -816,8 +816,8 @@ struct mbr_lanczos {
     uint32_t n_slots = 0;
     std::vector<HvSector> secs;
     DevBuf d_tiles_slot, d_secs;
-    // reorthogonalising path: groups of alpha_up blocks of a sector
-    // (group_rows), with their own slot numbering (rsecs holds the sectors with
+    // the vector kernels' groups of alpha_up blocks of a sector (group_rows),
+    // with their own slot numbering (rsecs holds the sectors with
     // slot0/nslots over those slots); rt0/rnt per sector
     DevBuf d_rtiles, d_rsecs;
     std::vector<uint32_t> rt0, rnt;
@@ -862,6 +862,9 @@ mbr_status enqueue_plain(mbr_lanczos *lz, int par, uint32_t s0, uint32_t nsec, u
     T *P = par ? lz->bufA.as<T>() : lz->bufB.as<T>();
     const HvSector *secs = lz->d_secs.as<HvSector>();
     const HvTile *tiles = lz->d_tiles_slot.as<HvTile>() + t0;
+    const uint32_t g0 = all ? 0 : lz->rt0[s0], gn = all ? lz->n_rtiles : lz->rnt[s0];
+    const HvTile *groups = lz->d_rtiles.as<HvTile>() + g0;
+    const HvSector *rsecs = lz->d_rsecs.as<HvSector>();
     HvEpilogue ep{};
     ep.c1 = lz->dev.c1;
     ep.c2 = lz->dev.c2;
@@ -874,13 +877,13 @@ mbr_status enqueue_plain(mbr_lanczos *lz, int par, uint32_t s0, uint32_t nsec, u
         ep.sector = s0;
     }
     MBR_TRY(hubbard_launch(lz->h, X, P, ep, s));
-    const unsigned g = std::min<unsigned>(lz->grid, nt);
+    const unsigned g = std::min<unsigned>(lz->grid, gn);
     if (nsec == 1) {
-        lz_alpha_update<T><<<g, kBlock, 0, s>>>(tiles, nt, secs, P, X, lz->dev, lz->m, default_tol(lz), s0);
+        lz_alpha_update<T><<<g, kBlock, 0, s>>>(groups, gn, rsecs, secs, P, X, lz->dev, lz->m, default_tol(lz), s0);
     } else {
         lz_alpha<<<nsec, kBlock, 0, s>>>(secs, lz->dev, lz->m, s0);
-        lz_update<T><<<g, kBlock, 0, s>>>(tiles, nt, secs, P, X, lz->dev);
-        lz_beta<<<nsec, kBlock, 0, s>>>(secs, lz->dev, lz->m, default_tol(lz), s0);
+        lz_update<T><<<g, kBlock, 0, s>>>(groups, gn, rsecs, P, X, lz->dev);
+        lz_beta<<<nsec, kBlock, 0, s>>>(rsecs, lz->dev, lz->m, default_tol(lz), s0);
     }
     MBR_HIP(hipGetLastError());
     return MBR_OK;
@@ -974,14 +977,14 @@ mbr_status capture(mbr_lanczos *lz, int par, int steps, hipGraphExec_t *out) {
 
 template <class T>
 mbr_status lz_start_t(mbr_lanczos *lz, const double *v0, hipStream_t s) {
-    const HvSector *secs = lz->d_secs.as<HvSector>();
-    const HvTile *tiles = lz->d_tiles_slot.as<HvTile>();
+    const HvSector *secs = lz->d_rsecs.as<HvSector>();
+    const HvTile *groups = lz->d_rtiles.as<HvTile>();
     const bool reorth = lz->o.reorth != 0;
     T *X = reorth ? lz->work.as<T>() : lz->bufA.as<T>();
-    lz_start_vectors<T><<<lz->grid, kBlock, 0, s>>>(tiles, lz->n_slots, secs, v0, X, reorth ? nullptr : lz->bufB.as<T>(), lz->dev.pn);
+    lz_start_vectors<T><<<lz->grid, kBlock, 0, s>>>(groups, lz->n_rtiles, secs, v0, X, reorth ? nullptr : lz->bufB.as<T>(), lz->dev.pn);
     lz_start_scalars<<<lz->ns, kBlock, 0, s>>>(secs, lz->dev, reorth ? 1 : 0);
     if (reorth)
-        lz_first<T><<<lz->grid, kBlock, 0, s>>>(tiles, lz->n_slots, secs, X, lz->basis.as<T>(), lz->dev);
+        lz_first<T><<<lz->grid, kBlock, 0, s>>>(groups, lz->n_rtiles, secs, X, lz->basis.as<T>(), lz->dev);
     MBR_HIP(hipGetLastError());
     return MBR_OK;
 }
@@ -1012,9 +1015,11 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
     hipStream_t s = nullptr;
     MBR_TRY(upload(lz->d_tiles_slot, tiles.data(), tiles.size() * sizeof(HvTile), s));
     MBR_TRY(upload(lz->d_secs, lz->secs.data(), lz->secs.size() * sizeof(HvSector), s));
-    if (o->reorth) {
-        // groups of whole alpha_up blocks of a sector, whatever the product's tiles
-        const uint64_t grow = o->batched ? group_rows(lz->total) : kGroupMin;
+    {
+        // groups of whole alpha_up blocks of a sector, whatever the product's
+        // tiles (without reorthogonalisation the same for batched and per-sector
+        // steps, whose sums are then the same)
+        const uint64_t grow = o->batched || !o->reorth ? group_rows(lz->total) : kGroupMin;
         std::vector<HvTile> groups;
         std::vector<HvSector> rsecs = lz->secs;
         lz->rt0.assign(lz->ns, 0);
@@ -1082,7 +1087,7 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
     d.steps = lz->steps.as<int32_t>();
     d.j = lz->jcount.as<int32_t>();
     d.done = lz->done.as<uint32_t>();
-    lz->grid = (unsigned)std::min<uint64_t>(lz->n_slots, (uint64_t)device_cu_count() * 8);
+    lz->grid = (unsigned)std::min<uint64_t>(lz->n_rtiles, (uint64_t)device_cu_count() * 8);
     *out = lz.release();
     return MBR_OK;
 }
