@@ -507,7 +507,8 @@ mbr_status mbr_hubbard_destroy(mbr_hubbard *h);
  * both halves ranked on the fly, no staged x and no barrier between rows);
  * 0 selects the panel kernel (512-lane workgroups, each on a run of alpha_up
  * blocks with the down-hop lists of its spin-down configurations in registers)
- * for sectors of at most 1024 (fp32) or 512 (fp64) spin-down configurations,
+ * for sectors of at most 1024 (fp32, and fp64 with bond-dependent hopping, where
+ * above 512 it has 1024 lanes) or 512 (fp64) spin-down configurations,
  * the alpha_dn-stationary rows kernel (1024-lane workgroups that sweep tiles,
  * down-hop lists ranked once per launch shape) for longer ones (at most 4095
  * spin-down configurations; both need at most 15 bonds) and the tile

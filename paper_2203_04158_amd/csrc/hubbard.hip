@@ -49,6 +49,13 @@ struct HvTrieDesc {
     uint64_t off[9];
 };
 
+struct PanelTiles {
+    std::vector<HvTile> tiles;  // natural order
+    DevBuf d_desc;              // their descriptors
+    uint32_t xoff[kXcd + 1] = {0};
+};
+enum : uint32_t { kPanNone, kPanShort, kPanLong };  // HvSector::pan
+
 struct mbr_hubbard {
     int32_t L = 0, nb = 0, precision = MBR_F64;
     int32_t rank_kind = MBR_HV_RANK_HALVES;
@@ -90,9 +97,7 @@ struct mbr_hubbard {
     DevBuf d_bdesc;                     // their descriptors
     uint32_t block_xoff[kXcd + 1] = {0};
     uint32_t block_xcap = 0;            // largest C_dn + 1 of the block kernel's sectors
-    std::vector<HvTile> panel_tiles;    // panel kernel tiles, natural order
-    DevBuf d_pdesc;                     // their descriptors
-    uint32_t panel_xoff[kXcd + 1] = {0};
+    PanelTiles panel, lpanel;           // panel kernel: sectors of 512 and of 1024 lanes
     DevBuf d_up_tgt, d_up_coef, d_up_n; // block and panel kernels: up-hop lists of every half state
     uint32_t n_slots = 0;
     StagTable tab;
@@ -1249,8 +1254,9 @@ __global__ void __launch_bounds__(kBlockLanes) hv_block_kernel(HvArgs a, BlockUp
 
 // ------------------------------------------------------------------------
 // Panel kernel (launch shapes G = 0 and -2) for sectors whose block of x fits
-// one panel: C_dn <= 1024 in fp32, <= 512 in fp64.  A 512-lane workgroup takes
-// a run of alpha_up blocks of one sector; each lane keeps its spin-down
+// one panel: C_dn <= 1024 in fp32, <= 512 in fp64, and <= 1024 there with
+// bond-dependent hopping (a long panel).  A 512-lane workgroup (1024 for a long
+// panel) takes a run of alpha_up blocks of one sector; each lane keeps its spin-down
 // configurations (two in fp32, one in fp64) over the whole run, so their
 // down-hop lists are decoded once per run into registers, an LDS byte offset
 // and a signed amplitude per hop, and a down-hop costs one LDS read and one
@@ -1259,8 +1265,8 @@ __global__ void __launch_bounds__(kBlockLanes) hv_block_kernel(HvArgs a, BlockUp
 // same across a wave: its up-hop targets and amplitudes (hv_uplists_kernel)
 // are scalar loads, a gather is a scalar base plus the lane's offset, and a
 // branch on the number of hops costs no lane anything.  Four rows of x per
-// group are staged at a time in one half of a double buffer, one barrier each,
-// while the next four are on their way to registers; a lane stages just the
+// group (two in a long panel) are staged at a time in one half of a double buffer, one barrier each,
+// while the next are on their way to registers; a lane stages just the
 // elements whose rows it sums.
 // The rows kernel that took these sectors before read a list of 32 or 64 bytes
 // and, with bond-dependent hopping, an amplitude from LDS per hop, for every
@@ -1276,11 +1282,10 @@ __global__ void __launch_bounds__(kBlockLanes) hv_block_kernel(HvArgs a, BlockUp
 // operations, so the products are bitwise equal.
 // ------------------------------------------------------------------------
 constexpr int kPanelLanes = 512;
-constexpr int kPanelWaves = kPanelLanes / 64;
-constexpr int kPanelStage = 4;              // alpha_up per group and stage
+constexpr int kPanelLong = 1024;            // lanes of a long panel
+__host__ __device__ constexpr int panel_stage(int nl) { return 2048 / nl; }  // alpha_up per group and stage
 constexpr uint32_t kPanelMaxIts = 16;       // alpha_up per group and workgroup
-constexpr uint32_t kPanelBytes = 4096;      // x elements of a slot: 512 lanes of 8 bytes
-constexpr uint32_t kPanelSlot = kPanelBytes + 16;  // and a zero
+__host__ __device__ constexpr uint32_t panel_bytes(int nl) { return 8u * nl; }  // x elements of a slot: 8 bytes a lane
 constexpr uint32_t kPanelSign = 0x8000u;    // list offset bit of a negative coefficient
 template <class T>
 __host__ __device__ constexpr int panel_rows() { return 8 / (int)sizeof(T); }  // alpha_dn per lane
@@ -1288,8 +1293,8 @@ __host__ __device__ inline uint32_t panel_lanes(uint32_t cdn, uint32_t rows) {  
     return ((cdn + rows - 1) / rows + 63) & ~63u;
 }
 
-inline size_t panel_lds_bytes(size_t tsz) {
-    return 2 * kPanelStage * (size_t)kPanelSlot + kRowsNB * tsz + kPanelWaves * sizeof(double);
+inline size_t panel_lds_bytes(int nl, size_t tsz) {
+    return 2 * panel_stage(nl) * ((size_t)panel_bytes(nl) + 16) + kRowsNB * tsz + (size_t)nl / 64 * sizeof(double);
 }
 
 // Scalar loads: the lists are not written while a product runs.
@@ -1304,10 +1309,13 @@ struct PanelUp {  // one alpha_up, in scalar registers
     T e, c[kUpMax];
 };
 
-template <class T, bool LZ, bool UT>
-__global__ void __launch_bounds__(kPanelLanes, 4) hv_panel_kernel(HvArgs a, BlockUpLists<T> up) {
+template <class T, bool LZ, bool UT, int NL>
+__global__ void __launch_bounds__(NL, 4) hv_panel_kernel(HvArgs a, BlockUpLists<T> up) {
     constexpr int R = panel_rows<T>();
-    constexpr int S = kPanelStage;
+    constexpr int S = panel_stage(NL);
+    constexpr uint32_t kPanelBytes = panel_bytes(NL);
+    constexpr uint32_t kPanelSlot = kPanelBytes + 16;  // and a zero
+    constexpr int kPanelWaves = NL / 64;
     __shared__ __align__(16) unsigned char xl[2 * S * kPanelSlot];
     __shared__ T amp[kRowsNB];
     __shared__ double red[kPanelWaves];
@@ -1532,7 +1540,7 @@ __global__ void __launch_bounds__(kPanelLanes, 4) hv_panel_kernel(HvArgs a, Bloc
         stage(it0, std::integral_constant<uint32_t, 0>{});
         if (it0 + S < nit) stage(it0 + S, std::integral_constant<uint32_t, 1>{});
     }
-    // the tile's partial of <x, u>: per wave, then lane 0 adds the eight
+    // the tile's partial of <x, u>: per wave, then lane 0 adds them
     if (a.ep.partial) {
         for (int o = 32; o > 0; o >>= 1) dot += __shfl_down(dot, o, 64);
         if ((tid & 63) == 0) red[tid >> 6] = dot;
@@ -1877,7 +1885,8 @@ void fill_args(const mbr_hubbard *h, HvArgs &a, const void *x, void *out, const 
 // tiles of a per-sector launch, 0 for a whole product.
 template <class T, bool LZ, int R>
 mbr_status launch_rows_r(const mbr_hubbard *h, const HvArgs &a, unsigned cap, hipStream_t s) {
-    auto kern = h->t_uniform ? hv_rows_kernel<T, LZ, R, true> : hv_rows_kernel<T, LZ, R, false>;
+    // one row slot is left for uniform hopping only (long panels take the rest)
+    auto kern = R == 1 || h->t_uniform ? hv_rows_kernel<T, LZ, R, true> : hv_rows_kernel<T, LZ, R == 1 ? 2 : R, false>;
     const size_t lds = rows_lds_layout(a.rtab_entries, a.xcap, sizeof(T)).total;
     if (lds > 64 * 1024)
         MBR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -1921,10 +1930,12 @@ mbr_status launch_block(const mbr_hubbard *h, HvArgs a, unsigned grid, hipStream
 
 // Panel kernel over `grid` workgroups (descriptors and ranges set in a).
 template <class T, bool LZ>
-mbr_status launch_panel(const mbr_hubbard *h, const HvArgs &a, unsigned grid, hipStream_t s) {
-    auto kern = h->t_uniform ? hv_panel_kernel<T, LZ, true> : hv_panel_kernel<T, LZ, false>;
+mbr_status launch_panel(const mbr_hubbard *h, bool longp, const HvArgs &a, unsigned grid, hipStream_t s) {
+    auto kern = h->t_uniform ? hv_panel_kernel<T, LZ, true, kPanelLanes> : hv_panel_kernel<T, LZ, false, kPanelLanes>;
+    if constexpr (sizeof(T) == 8)
+        if (longp) kern = hv_panel_kernel<T, LZ, false, kPanelLong>;
     BlockUpLists<T> up{h->d_up_tgt.as<uint32_t>(), h->d_up_coef.as<T>(), h->d_up_n.as<uint32_t>()};
-    if (grid) kern<<<grid, kPanelLanes, 0, s>>>(a, up);
+    if (grid) kern<<<grid, longp ? kPanelLong : kPanelLanes, 0, s>>>(a, up);
     MBR_HIP(hipGetLastError());
     return MBR_OK;
 }
@@ -1950,8 +1961,9 @@ mbr_status launch_t(const mbr_hubbard *h, const void *x, void *out, const HvEpil
         }
         if (h->hsec[ep.sector].pan) {
             a.rdesc = h->d_rdesc_slot.as<RowsTileDesc>() + h->hsec[ep.sector].slot0;
-            if (ep.c1) return launch_panel<T, true>(h, a, ep.n_tiles, s);
-            return launch_panel<T, false>(h, a, ep.n_tiles, s);
+            const bool longp = h->hsec[ep.sector].pan == kPanLong;
+            if (ep.c1) return launch_panel<T, true>(h, longp, a, ep.n_tiles, s);
+            return launch_panel<T, false>(h, longp, a, ep.n_tiles, s);
         }
         if (h->hsec[ep.sector].blk) {
             a.rdesc = h->d_rdesc_slot.as<RowsTileDesc>() + h->hsec[ep.sector].slot0;
@@ -2001,17 +2013,19 @@ mbr_status launch_t(const mbr_hubbard *h, const void *x, void *out, const HvEpil
         if (ep.c1) MBR_TRY((launch_block<T, true>(h, ab, grid, s)));
         else MBR_TRY((launch_block<T, false>(h, ab, grid, s)));
     }
-    if (!h->panel_tiles.empty()) {
+    for (const PanelTiles *pt : {&h->panel, &h->lpanel}) {
+        if (pt->tiles.empty()) continue;
         HvArgs ap = a;
-        ap.rdesc = h->d_pdesc.as<RowsTileDesc>();
-        ap.n_tiles = (uint32_t)h->panel_tiles.size();
+        ap.rdesc = pt->d_desc.as<RowsTileDesc>();
+        ap.n_tiles = (uint32_t)pt->tiles.size();
         ap.binned = 1;
         uint32_t most = 0;
-        for (int i = 0; i <= kXcd; ++i) ap.xoff[i] = h->panel_xoff[i];
-        for (int i = 0; i < kXcd; ++i) most = std::max(most, h->panel_xoff[i + 1] - h->panel_xoff[i]);
+        for (int i = 0; i <= kXcd; ++i) ap.xoff[i] = pt->xoff[i];
+        for (int i = 0; i < kXcd; ++i) most = std::max(most, pt->xoff[i + 1] - pt->xoff[i]);
         const unsigned grid = most * kXcd;
-        if (ep.c1) MBR_TRY((launch_panel<T, true>(h, ap, grid, s)));
-        else MBR_TRY((launch_panel<T, false>(h, ap, grid, s)));
+        const bool longp = pt == &h->lpanel;
+        if (ep.c1) MBR_TRY((launch_panel<T, true>(h, longp, ap, grid, s)));
+        else MBR_TRY((launch_panel<T, false>(h, longp, ap, grid, s)));
     }
     if (!h->rows_tiles.empty()) {
         HvArgs ar = a;
@@ -2142,7 +2156,7 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     const int Gt = rows_shape ? 2 : G;  // tile-kernel blocks for sectors the rows kernel does not take
     const size_t xbudget = (Gt == 4 ? 112 : 56) * 1024;
     std::vector<HvSector> hsec;
-    std::vector<HvTile> tiles, rows_tiles, other_tiles, flat_tiles, block_tiles, panel_tiles;
+    std::vector<HvTile> tiles, rows_tiles, other_tiles, flat_tiles, block_tiles, panel_tiles, lpanel_tiles;
     uint64_t off = 0;
     uint32_t slot = 0, xcap = 0, upcap = 0, maxblk = 0, rows_xcap = 0, lrows = 0, block_xcap = 0;
     std::vector<uint32_t> lists_ndn, lists_rows;
@@ -2161,24 +2175,32 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     // 1024 as well: its down-hop is an LDS read and an add there, and one
     // alpha_up a workgroup fills the chip sooner (12-site chain, 924 x 924, block
     // 7.9 us, panel 8.8; with 3432 alpha_up the panel leads, 21 against 24).
-    auto takes_panel = [&](uint64_t cup, uint32_t cdn) {
-        return lists_ok && cdn <= kPanelBytes / tsz && !(t_uniform && takes_block(cup, cdn));
+    // In fp64 sectors of that length need the long panel, one 1024-lane
+    // workgroup a CU, which pays with bond-dependent hopping (12-site impurity
+    // model, all sectors, 211 us with the block kernel, 151 with the panel).
+    auto takes_panel = [&](uint64_t cup, uint32_t cdn) -> uint32_t {
+        if (!lists_ok) return kPanNone;
+        if (cdn <= panel_bytes(kPanelLanes) / tsz) return t_uniform && takes_block(cup, cdn) ? kPanNone : kPanShort;
+        return tsz == 8 && !t_uniform && cdn <= panel_bytes(kPanelLong) / tsz ? kPanLong : kPanNone;
     };
     // Blocks per group of a panel: as many as leave a workgroup to every CU.
     // A run's start costs about three blocks' time, so long runs are better
     // where there are enough of them (12-site impurity model: 16 blocks 72 us,
     // 8 78, 4 95, 1 252; 10-site half-filled chain: 1 block 4.6 us, 4 6.4,
     // 16 15.0); past 16 the last round of workgroups costs what the starts save.
-    uint32_t panel_its = kPanelMaxIts;
-    for (; panel_its > 1; panel_its /= 2) {
-        uint64_t n = 0;
-        for (const mbr_spin_sector &sp : h->secs) {
-            const uint32_t cup = (uint32_t)binom(L, sp.n_up), cdn = (uint32_t)binom(L, sp.n_dn);
-            const uint32_t nblk = panel_its * ((uint32_t)kPanelLanes / panel_lanes(cdn, panel_r));
-            if (takes_panel(cup, cdn)) n += (cup + nblk - 1) / nblk;
+    uint32_t panel_its[3] = {0, kPanelMaxIts, kPanelMaxIts};
+    for (uint32_t kind : {kPanShort, kPanLong})
+        for (uint32_t &its = panel_its[kind]; its > 1; its /= 2) {
+            uint64_t n = 0;
+            for (const mbr_spin_sector &sp : h->secs) {
+                const uint32_t cup = (uint32_t)binom(L, sp.n_up), cdn = (uint32_t)binom(L, sp.n_dn);
+                if (takes_panel(cup, cdn) != kind) continue;
+                const uint32_t nl = kind == kPanLong ? kPanelLong : kPanelLanes;
+                const uint32_t nblk = its * (nl / panel_lanes(cdn, panel_r));
+                n += (cup + nblk - 1) / nblk;
+            }
+            if (n >= (uint64_t)device_cu_count()) break;
         }
-        if (n >= (uint64_t)device_cu_count()) break;
-    }
     for (size_t si = 0; si < h->secs.size(); ++si) {
         HvSector sc{};
         sc.off = off;
@@ -2187,7 +2209,7 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
         sc.hs_up = h->hs_off[h->secs[si].n_up];
         sc.hs_dn = h->hs_off[h->secs[si].n_dn];
         sc.rows = (rows_shape && sc.cdn + 1 <= kRowsMaxX && h->nb <= kRowsNB - 1) ? 1 : 0;
-        sc.pan = takes_panel(sc.cup, sc.cdn) ? 1 : 0;
+        sc.pan = takes_panel(sc.cup, sc.cdn);
         sc.blk = !sc.pan && lists_ok && takes_block(sc.cup, sc.cdn) ? 1 : 0;
         if (sc.blk || sc.pan) sc.rows = 0;
         sc.magic = sc.cdn == 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / sc.cdn);
@@ -2195,9 +2217,9 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
         if (sc.pan) {
             sc.wide = 1;
             sc.x_lds = 1;
-            sc.gp = (uint32_t)kPanelLanes / panel_lanes(sc.cdn, panel_r);
+            sc.gp = (uint32_t)(sc.pan == kPanLong ? kPanelLong : kPanelLanes) / panel_lanes(sc.cdn, panel_r);
             sc.R = panel_r;
-            nblk = sc.gp * panel_its;
+            nblk = sc.gp * panel_its[sc.pan];
         } else if (sc.blk) {
             sc.wide = 1;
             sc.x_lds = 1;
@@ -2238,7 +2260,7 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
             t.nblk = std::min(nblk, sc.cup - r);
             t.slot = slot++;
             if (sc.pan) {
-                panel_tiles.push_back(t);
+                (sc.pan == kPanLong ? lpanel_tiles : panel_tiles).push_back(t);
             } else if (sc.blk) {
                 block_xcap = std::max(block_xcap, sc.cdn + 1);
                 block_tiles.push_back(t);
@@ -2281,7 +2303,6 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     const std::vector<uint32_t> rr = balanced_ranges(rows_tiles, hsec, kXcd);
     const std::vector<uint32_t> fr = balanced_ranges(flat_tiles, hsec, kXcd);
     const std::vector<uint32_t> br = balanced_ranges(block_tiles, hsec, kXcd);
-    const std::vector<uint32_t> pr = balanced_ranges(panel_tiles, hsec, kXcd);
     if (!block_tiles.empty() && block_lds_bytes(block_xcap, tsz) > kLdsMax)
         MBR_FAIL(MBR_EUNSUPPORTED, "block kernel needs %zu bytes of LDS", block_lds_bytes(block_xcap, tsz));
     const size_t rows_lds = rows_lds_layout((uint32_t)((uint64_t)tab.nrows << k), rows_xcap, tsz).total;
@@ -2310,8 +2331,8 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     h->lists_for = lists_for;
     h->block_tiles = block_tiles;
     h->block_xcap = block_xcap;
-    h->panel_tiles = panel_tiles;
-    for (int b = 0; b <= kXcd; ++b) h->panel_xoff[b] = pr[b];
+    h->panel.tiles = panel_tiles;
+    h->lpanel.tiles = lpanel_tiles;
     for (int b = 0; b <= kXcd; ++b) h->block_xoff[b] = br[b];
     h->rows_grid = rows_grid;
     h->t_uniform = t_uniform;
@@ -2328,27 +2349,33 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
             d.slot = t.slot;
             return d;
         };
-        for (const auto *tl : {&rows_tiles, &block_tiles, &panel_tiles})
+        for (const auto *tl : {&rows_tiles, &block_tiles, &panel_tiles, &lpanel_tiles})
             for (auto &t : *tl) {  // field widths of the packed descriptor
                 const HvSector &sc = hsec[t.sector];
                 if (sc.cdn > 0xFFF || sc.gp > 0xFF || t.nblk > 0xFFF || sc.hs_up + t.rup0 > 0xFFFF ||
                     sc.hs_dn > 0xFFFF || sc.loff > 0xFFFF || t.sector > 0xFFFF)
                     MBR_FAIL(MBR_EUNSUPPORTED, "rows-kernel tile descriptor out of range");
             }
-        std::vector<RowsTileDesc> rd, rs, bd, pd;
+        std::vector<RowsTileDesc> rd, rs, bd;
         for (auto &t : rows_tiles) rd.push_back(mk(t));
         for (auto &t : block_tiles) bd.push_back(mk(t));
-        for (auto &t : panel_tiles) pd.push_back(mk(t));
+        for (PanelTiles *pt : {&h->panel, &h->lpanel}) {
+            const std::vector<uint32_t> pr = balanced_ranges(pt->tiles, hsec, kXcd);
+            for (int b = 0; b <= kXcd; ++b) pt->xoff[b] = pr[b];
+            std::vector<RowsTileDesc> pd;
+            for (auto &t : pt->tiles) pd.push_back(mk(t));
+            MBR_TRY(upload(pt->d_desc, pd.data(), pd.size() * sizeof(RowsTileDesc), s));
+        }
         for (auto &t : tiles) rs.push_back(mk(t));
         MBR_TRY(upload(h->d_rdesc, rd.data(), rd.size() * sizeof(RowsTileDesc), s));
         MBR_TRY(upload(h->d_bdesc, bd.data(), bd.size() * sizeof(RowsTileDesc), s));
-        MBR_TRY(upload(h->d_pdesc, pd.data(), pd.size() * sizeof(RowsTileDesc), s));
         MBR_TRY(upload(h->d_rdesc_slot, rs.data(), rs.size() * sizeof(RowsTileDesc), s));
     }
     for (int b = 0; b <= kXcd; ++b) h->rows_xoff[b] = rr[b];
     MBR_TRY(upload(h->d_secs, h->hsec.data(), h->hsec.size() * sizeof(HvSector), s));
     h->lds_bytes = std::max(other_tiles.empty() ? 0 : lds_bytes_for(h, tsz), rows_tiles.empty() ? 0 : rows_lds);
-    if (!panel_tiles.empty()) h->lds_bytes = std::max(h->lds_bytes, panel_lds_bytes(tsz));
+    if (!panel_tiles.empty()) h->lds_bytes = std::max(h->lds_bytes, panel_lds_bytes(kPanelLanes, tsz));
+    if (!lpanel_tiles.empty()) h->lds_bytes = std::max(h->lds_bytes, panel_lds_bytes(kPanelLong, tsz));
     if (!block_tiles.empty()) h->lds_bytes = std::max(h->lds_bytes, block_lds_bytes(block_xcap, tsz));
     if (!flat_tiles.empty())
         h->lds_bytes = std::max<size_t>(h->lds_bytes, ((((size_t)h->tab.nrows << h->tab.k) * 2 + 15) & ~(size_t)15) +
@@ -2363,7 +2390,7 @@ mbr_status configure(mbr_hubbard *h, int k, int G, int block, hipStream_t s) {
     h->grid -= h->grid % kXcd;
     if (h->grid < kXcd) h->grid = kXcd;
     MBR_TRY(build_lists(h, lrows, s));
-    if (!block_tiles.empty() || !panel_tiles.empty()) MBR_TRY(build_uplists(h, s));
+    if (!block_tiles.empty() || !panel_tiles.empty() || !lpanel_tiles.empty()) MBR_TRY(build_uplists(h, s));
     h->generation++;
     return MBR_OK;
 }

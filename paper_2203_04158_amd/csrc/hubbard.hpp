@@ -30,7 +30,7 @@ struct HvSector {
     uint32_t loff;    // rows, block and panel kernels: first down-hop list row of the sector's n_dn
     uint32_t magic;   // flat kernel: floor(2^32 / C_dn), to split a row index into (alpha_up, alpha_dn)
     uint32_t blk;     // handled by the block kernel (launch shape G = -2): one alpha_up block per workgroup
-    uint32_t pan;     // handled by the panel kernel (launch shapes G = 0, -2)
+    uint32_t pan;     // handled by the panel kernel (launch shapes G = 0, -2): 1 in 512 lanes, 2 in 1024
 };
 
 // Epilogue: y = H x (plain), or u = c1[s] (H x)_i - c2[s] p_i written to `out`

@@ -1,4 +1,5 @@
-"""The panel kernel of H·x (C_dn <= 1024 in fp32, <= 512 in fp64) where its
+"""The panel kernel of H·x (C_dn <= 1024 in fp32, <= 512 in fp64, <= 1024
+there with bond-dependent hopping) where its
 split can go wrong: groups of one to eight waves, blocks that do not fill the
 last wave, fewer alpha_up blocks than groups, a last run of fewer blocks, up to
 fifteen hops a half, uniform and bond-dependent hopping, uniform and
@@ -29,6 +30,7 @@ CASES = [
     (12, "ring", [(6, 4), (5, 3), (2, 6), (0, 4), (12, 5), (4, 12), (1, 2)]),
     (11, "star", [(5, 5), (4, 4), (2, 8), (11, 3)]),
     (13, "ring", [(3, 2), (2, 3), (1, 11)]),
+    (12, "star", [(2, 6), (3, 5), (0, 7), (1, 4)]),
     (4, "ring", [(2, 2), (1, 2), (2, 1), (4, 0)]),
     (1, "none", [(0, 0), (1, 0), (0, 1), (1, 1)]),
 ]
