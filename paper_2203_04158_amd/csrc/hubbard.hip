@@ -1274,7 +1274,7 @@ __global__ void __launch_bounds__(kBlockLanes) hv_block_kernel(HvArgs a, BlockUp
 // 172 -> 72 us; 10 sites in fp64 24 -> 14; 14-site chain with (7, 3) 29 -> 19
 // (fp64) and 21 -> 11 (fp32); 8-site chain with (3, 5) 6.8 -> 4.7.
 // What bounds it: at 16 waves a CU (128 registers) the gathers' latency; the
-// vector units are busy 39% of the time, the address units 47%, LDS 21%, and
+// vector units are busy 37% of the time, the address units 47%, LDS 21%, and
 // the L2s hand out 10 TB/s.  Gathering one alpha_up ahead (76 -> 80 us), half
 // the hops in registers (72 -> 75), up-hop lists through LDS (75) and 80
 // registers for 24 waves (spills, 194) were all slower.
