@@ -327,9 +327,14 @@ __global__ void __launch_bounds__(kBlock) lz_start_vectors(const HvTile *tiles, 
     }
 }
 
+// First scalars of every sector.  The counters of finished workgroups are cleared
+// too, on the caller's stream: a run cut off within a kernel may have left them
+// anywhere, and every later kernel would then miss its last workgroup.
 __global__ void lz_start_scalars(const HvSector *secs, LzDev d, int reorth) {
     __shared__ double red[kRedWaves];
     const uint32_t s = blockIdx.x;
+    if (s == 0)
+        for (uint32_t i = threadIdx.x; i < kDoneBytes / 4; i += blockDim.x) d.done[i] = 0;
     double sum = sector_sum(d.pn + secs[s].slot0, secs[s].nslots, red);
     if (threadIdx.x == 0) {
         double nrm = sqrt(sum);
@@ -1072,6 +1077,8 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
     MBR_HIP(hipMemset(lz->steps.p, 0, ns * 4));
     MBR_HIP(hipMemset(lz->jcount.p, 0, 8));
     MBR_HIP(hipMemset(lz->done.p, 0, kDoneBytes));
+    // the clears run on the null stream, which a caller's non-blocking stream does not wait for
+    MBR_HIP(hipStreamSynchronize(s));
     LzDev &d = lz->dev;
     d.alpha = lz->alpha.as<double>();
     d.beta = lz->beta.as<double>();
