@@ -712,29 +712,40 @@ __device__ __forceinline__ double recip(double q) {
 }
 
 // Number of eigenvalues below x: negative pivots of the LDL^T factorisation of
-// T - x I (Sturm sequence), b2 the squared off-diagonal.  Pivots smaller than
-// 1e-290 count as that, with their sign (a zero as negative), so that their
-// reciprocals stay finite.
+// T - x I (Sturm sequence), b2 the squared off-diagonal, all of a matrix scaled
+// to norms below 1.  A pivot smaller than kPivotMin counts as that, with its
+// sign (a zero as negative), so that the next one, at most b2 / kPivotMin, and
+// its reciprocal stay finite: an infinite pivot would make recip's Newton steps
+// NaN and every later pivot count as not negative.
+constexpr double kPivotMin = 1e-290;
+
+__device__ __forceinline__ double pivot(double q) {
+    return fabs(q) < kPivotMin ? (q > 0 ? kPivotMin : -kPivotMin) : q;
+}
+
 __device__ __forceinline__ int sturm_count(const double *a, const double *b2, int n, double x) {
-    int c = 0;
-    double q = a[0] - x;
-    if (q < 0) ++c;
+    double q = pivot(a[0] - x);
+    int c = q < 0 ? 1 : 0;
     for (int i = 1; i < n; ++i) {
-        const double qq = fabs(q) < 1e-290 ? (q > 0 ? 1e-290 : -1e-290) : q;
-        q = __builtin_fma(-b2[i - 1], recip(qq), a[i] - x);
+        q = pivot(__builtin_fma(-b2[i - 1], recip(q), a[i] - x));
         if (q < 0) ++c;
     }
     return c;
 }
 
-// The same count with the off-diagonal squared on the way.
-__device__ __forceinline__ int sturm_count_far(const double *a, const double *b, int n, double x) {
-    int c = 0;
-    double q = a[0] - x;
-    if (q < 0) ++c;
+// The same count of a matrix in memory, scaled (a power of two) and squared on
+// the way; the next entries are loaded during a step.
+__device__ __forceinline__ int sturm_count_far(const double *a, const double *b, double scale, int n, double x) {
+    double q = pivot(__builtin_fma(a[0], scale, -x));
+    int c = q < 0 ? 1 : 0;
+    double an = a[1], bn = b[0];  // n > kTriLds
     for (int i = 1; i < n; ++i) {
-        const double qq = fabs(q) < 1e-290 ? (q > 0 ? 1e-290 : -1e-290) : q;
-        q = __builtin_fma(-(b[i - 1] * b[i - 1]), recip(qq), a[i] - x);
+        const double as = __builtin_fma(an, scale, -x), bs = bn * scale;
+        if (i + 1 < n) {
+            an = a[i + 1];
+            bn = b[i];
+        }
+        q = pivot(__builtin_fma(-bs * bs, recip(q), as));
         if (q < 0) ++c;
     }
     return c;
@@ -742,7 +753,9 @@ __device__ __forceinline__ int sturm_count_far(const double *a, const double *b,
 
 // One workgroup per matrix: multisection of the Gershgorin interval, a lane a
 // point, keeping the sub-interval where the Sturm count first reaches one.  The
-// matrix is staged in LDS as far as it fits.  Bound by the serial chain of the
+// matrix is scaled by the power of two that brings its Gershgorin bound below 1
+// (exact, so the bits do not depend on its units) and staged in LDS as far as it
+// fits.  Bound by the serial chain of the
 // counts: 40 steps, 37 us with a wave and divisions, 23 us so.
 constexpr int kTriBlock = 256;
 constexpr int kTriLds = 2048;
@@ -770,7 +783,7 @@ __global__ void __launch_bounds__(kTriBlock) tridiag_lowest_kernel(const double 
         hi = fmax(hi, d + (bl + br));
         if (staged) {
             sa[i] = d;
-            sb2[i] = i + 1 < n ? b[i] * b[i] : 0.0;
+            sb2[i] = br;
         }
     }
     for (int o = 32; o > 0; o >>= 1) {
@@ -786,14 +799,28 @@ __global__ void __launch_bounds__(kTriBlock) tridiag_lowest_kernel(const double 
         lo = fmin(lo, lo_w[k]);
         hi = fmax(hi, hi_w[k]);
     }
-    const double pad = 1e-12 * fmax(1.0, fmax(fabs(lo), fabs(hi)));
+    int e = 0;
+    const double bound = fmax(fabs(lo), fabs(hi));
+    if (bound < INFINITY) (void)frexp(bound, &e);
+    e = e < -1000 ? -1000 : e;  // 2^-e has to be finite
+    const double scale = ldexp(1.0, -e);
+    lo *= scale;
+    hi *= scale;
+    if (staged)
+        for (int i = threadIdx.x; i < n; i += kTriBlock) {  // the lane's own entries
+            const double bs = sb2[i] * scale;
+            sa[i] *= scale;
+            sb2[i] = bs * bs;
+        }
+    __syncthreads();
+    const double pad = 1e-12 * fmax(fabs(lo), fabs(hi));
     lo -= pad;
     hi += pad;
     for (int it = 0; it < 40; ++it) {
         if (!(hi - lo > 4.5e-16 * fmax(fabs(lo), fabs(hi)) + 1e-300)) break;
         const double h = (hi - lo) / (kTriBlock + 1.0);
         const double x = lo + h * (double)(threadIdx.x + 1);
-        const int c = staged ? sturm_count(sa, sb2, n, x) : sturm_count_far(a, b, n, x);
+        const int c = staged ? sturm_count(sa, sb2, n, x) : sturm_count_far(a, b, scale, n, x);
         const unsigned long long ball = __ballot(c >= 1);
         __syncthreads();  // first_w's readers of the iteration before are done
         if (lane == 0) first_w[w] = ball ? 64 * w + (__ffsll((long long)ball) - 1) : kTriBlock;
@@ -805,7 +832,7 @@ __global__ void __launch_bounds__(kTriBlock) tridiag_lowest_kernel(const double 
         lo = nlo;
         hi = nhi;
     }
-    if (threadIdx.x == 0) e0[bi] = 0.5 * (lo + hi);
+    if (threadIdx.x == 0) e0[bi] = ldexp(0.5 * (lo + hi), e);
 }
 
 }  // namespace
