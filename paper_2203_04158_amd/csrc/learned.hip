@@ -39,6 +39,7 @@
 #include <cmath>
 #include <memory>
 #include <mutex>
+#include <type_traits>
 
 #include "rank_device.hpp"
 
@@ -452,6 +453,12 @@ constexpr int kTileNT = 2;               // 16-sample groups of a tile
 // fp32 product reaches (12.7 ms before).  Against 64 bits the gradient is off
 // by 5e-8 to 8e-8 (8e-8 to 1.7e-7 before) at 64 to 8,192 samples.  Tiles of 16
 // samples gain nothing: 37.1 against 35.0 us a call at 4,096.
+//
+// A set input bit adds its weight and a clear one adds nothing, whatever the
+// weight is, but a product with the clear bit makes NaN of an infinite one, and
+// likewise of an infinite gradient.  A workgroup with such weights, or whose
+// bias gradients show that there were such gradients, goes through its tiles
+// once more, and non-finite values then pass the matrix cores by (CAREFUL).
 template <int NT>
 __global__ void __launch_bounds__(kGradBlock) mlp_grad_kernel(const float *__restrict__ w, int B,
                                                               const uint32_t *__restrict__ q,
@@ -482,111 +489,143 @@ __global__ void __launch_bounds__(kGradBlock) mlp_grad_kernel(const float *__res
     }
     const float b3 = rounded(w[P_B3]);
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    f32x4 gw2[4] = {zero, zero, zero, zero}, gw1[2] = {zero, zero}, gb1 = zero, gb2 = zero, gw3 = zero;
-    float gb3 = 0.f, sq = 0.f;
-    for (int tile = blockIdx.x; tile < B / S; tile += gridDim.x) {
-        __syncthreads();  // the tile before is done with LDS
-        if (threadIdx.x < S) {
-            const int s = tile * S + threadIdx.x;
-            if (q) {
-                xs[threadIdx.x] = q[s];
-                ts[threadIdx.x] = tgt[s];
-            } else {
-                const uint64_t idx = splitmix64_at(seed, step * (uint64_t)B + (uint64_t)s) % n;
-                xs[threadIdx.x] = states[idx];
-                ts[threadIdx.x] = (float)((double)idx / (double)n);
+    f32x4 gw2[4], gw1[2], gb1, gb2, gw3;
+    float gb3, sq;
+    auto pass = [&](auto careful) {
+        constexpr bool CAREFUL = decltype(careful)::value;
+        gw2[0] = gw2[1] = gw2[2] = gw2[3] = gw1[0] = gw1[1] = gb1 = gb2 = gw3 = zero;
+        gb3 = sq = 0.f;
+        for (int tile = blockIdx.x; tile < B / S; tile += gridDim.x) {
+            __syncthreads();  // the tile before is done with LDS
+            if (threadIdx.x < S) {
+                const int s = tile * S + threadIdx.x;
+                if (q) {
+                    xs[threadIdx.x] = q[s];
+                    ts[threadIdx.x] = tgt[s];
+                } else {
+                    const uint64_t idx = splitmix64_at(seed, step * (uint64_t)B + (uint64_t)s) % n;
+                    xs[threadIdx.x] = states[idx];
+                    ts[threadIdx.x] = (float)((double)idx / (double)n);
+                }
             }
+            __syncthreads();
+            // layer 1: K is the input bits
+            f32x4 h[NT];
+            uint32_t x[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                x[t] = xs[16 * t + c];
+                h[t] = b1;
+            }
+#pragma unroll
+            for (int k = 0; k < kIn / 4; ++k)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) h[t] = mfma_f32(CAREFUL && !isfinite(a1[k]) ? 0.f : a1[k], (x[t] >> (4 * k + g)) & 1u ? 1.f : 0.f, h[t]);
+            if constexpr (CAREFUL)
+                for (int k = 0; k < kIn; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float v = rounded(w[P_W1 + (row + r) * kIn + k]);
+                        if (!isfinite(v))
+#pragma unroll
+                            for (int t = 0; t < NT; ++t) h[t][r] += (x[t] >> k) & 1u ? v : 0.f;
+                    }
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    h[t][r] = h[t][r] > 0.f ? h[t][r] : 0.f;
+                    h1[(row + r) * LD + 16 * t + c] = h[t][r];
+                }
+            __syncthreads();
+            // layer 2, and the output's share of these rows
+            f32x4 z[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) z[t] = b2;
+#pragma unroll
+            for (int k = 0; k < kH / 4; ++k)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) z[t] = mfma_f32(a2[k], h1[(4 * k + g) * LD + 16 * t + c], z[t]);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                float y = 0.f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    z[t][r] = z[t][r] > 0.f ? z[t][r] : 0.f;
+                    y += w3[r] * z[t][r];
+                }
+                y += __shfl_xor(y, 16, 64);
+                y += __shfl_xor(y, 32, 64);
+                if (g == 0) ysum[wv][16 * t + c] = y;
+            }
+            __syncthreads();
+            // output, its error, and back to layer 2
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int s = 16 * t + c;
+                const float y = b3 + ((ysum[0][s] + ysum[1][s]) + (ysum[2][s] + ysum[3][s]));
+                const float e = y - ts[s], d = 2.f * e / (float)B;
+                if (wv == 0 && g == 0) {
+                    sq += e * e;
+                    gb3 += d;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    // carefully, a non-finite error reaches the units at rest too
+                    const float dz = CAREFUL ? (z[t][r] > 0.f ? 1.f : 0.f) * d * w3[r] : z[t][r] > 0.f ? d * w3[r] : 0.f;
+                    gw3[r] += d * z[t][r];
+                    gb2[r] += dz;
+                    d2[(row + r) * LD + s] = dz;
+                }
+            }
+            __syncthreads();
+            // back to layer 1
+            f32x4 u[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) u[t] = zero;
+#pragma unroll
+            for (int k = 0; k < kH / 4; ++k)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) u[t] = mfma_f32(a2t[k], d2[(4 * k + g) * LD + 16 * t + c], u[t]);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float dz = h[t][r] > 0.f ? u[t][r] : 0.f;
+                    gb1[r] += dz;
+                    d1[(row + r) * LD + 16 * t + c] = dz;
+                }
+            wave_lds_fence();  // a wave reads only its own rows of d1
+            // weight gradients: K is the samples
+#pragma unroll
+            for (int k = 0; k < S / 4; ++k) {
+                const float a = d2[(16 * wv + c) * LD + 4 * k + g];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) gw2[j] = mfma_f32(a, h1[(16 * j + c) * LD + 4 * k + g], gw2[j]);
+                float e = d1[(16 * wv + c) * LD + 4 * k + g];
+                if constexpr (CAREFUL) e = isfinite(e) ? e : 0.f;
+                const uint32_t xk = xs[4 * k + g];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) gw1[j] = mfma_f32(e, (xk >> (16 * j + c)) & 1u ? 1.f : 0.f, gw1[j]);
+            }
+            if constexpr (CAREFUL)
+                for (int s = 0; s < S; ++s)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float v = d1[(row + r) * LD + s];
+                        if (!isfinite(v))
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) gw1[j][r] += (xs[s] >> (16 * j + c)) & 1u ? v : 0.f;
+                    }
         }
-        __syncthreads();
-        // layer 1: K is the input bits
-        f32x4 h[NT];
-        uint32_t x[NT];
+    };
+    pass(std::false_type{});
+    bool odd = !isfinite(gb3);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            x[t] = xs[16 * t + c];
-            h[t] = b1;
-        }
+    for (int k = 0; k < kIn / 4; ++k) odd = odd || !isfinite(a1[k]);
 #pragma unroll
-        for (int k = 0; k < kIn / 4; ++k)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) h[t] = mfma_f32(a1[k], (x[t] >> (4 * k + g)) & 1u ? 1.f : 0.f, h[t]);
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                h[t][r] = h[t][r] > 0.f ? h[t][r] : 0.f;
-                h1[(row + r) * LD + 16 * t + c] = h[t][r];
-            }
-        __syncthreads();
-        // layer 2, and the output's share of these rows
-        f32x4 z[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) z[t] = b2;
-#pragma unroll
-        for (int k = 0; k < kH / 4; ++k)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) z[t] = mfma_f32(a2[k], h1[(4 * k + g) * LD + 16 * t + c], z[t]);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            float y = 0.f;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                z[t][r] = z[t][r] > 0.f ? z[t][r] : 0.f;
-                y += w3[r] * z[t][r];
-            }
-            y += __shfl_xor(y, 16, 64);
-            y += __shfl_xor(y, 32, 64);
-            if (g == 0) ysum[wv][16 * t + c] = y;
-        }
-        __syncthreads();
-        // output, its error, and back to layer 2
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int s = 16 * t + c;
-            const float y = b3 + ((ysum[0][s] + ysum[1][s]) + (ysum[2][s] + ysum[3][s]));
-            const float e = y - ts[s], d = 2.f * e / (float)B;
-            if (wv == 0 && g == 0) {
-                sq += e * e;
-                gb3 += d;
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float dz = z[t][r] > 0.f ? d * w3[r] : 0.f;
-                gw3[r] += d * z[t][r];
-                gb2[r] += dz;
-                d2[(row + r) * LD + s] = dz;
-            }
-        }
-        __syncthreads();
-        // back to layer 1
-        f32x4 u[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) u[t] = zero;
-#pragma unroll
-        for (int k = 0; k < kH / 4; ++k)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) u[t] = mfma_f32(a2t[k], d2[(4 * k + g) * LD + 16 * t + c], u[t]);
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float dz = h[t][r] > 0.f ? u[t][r] : 0.f;
-                gb1[r] += dz;
-                d1[(row + r) * LD + 16 * t + c] = dz;
-            }
-        wave_lds_fence();  // a wave reads only its own rows of d1
-        // weight gradients: K is the samples
-#pragma unroll
-        for (int k = 0; k < S / 4; ++k) {
-            const float a = d2[(16 * wv + c) * LD + 4 * k + g];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) gw2[j] = mfma_f32(a, h1[(16 * j + c) * LD + 4 * k + g], gw2[j]);
-            const float e = d1[(16 * wv + c) * LD + 4 * k + g];
-            const uint32_t xk = xs[4 * k + g];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) gw1[j] = mfma_f32(e, (xk >> (16 * j + c)) & 1u ? 1.f : 0.f, gw1[j]);
-        }
-    }
+    for (int r = 0; r < 4; ++r) odd = odd || !isfinite(w3[r]) || !isfinite(gb1[r]) || !isfinite(gb2[r]);
+    if (__syncthreads_or(odd)) pass(std::true_type{});
     float *out = part + (size_t)blockIdx.x * kPart;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
