@@ -541,7 +541,9 @@ mbr_status mbr_hubbard_set_config(mbr_hubbard *h, int32_t k, int32_t G, int32_t 
  * scratch vectors and keep the fastest (for a trie-ranked product: the trie's
  * chunk width, rebuilding the tries; get_config then reports it as k).  If the environment variable
  * MBR_AUTOTUNE_CACHE names a file, a matching entry (device, L, bonds,
- * sectors, precision) is used without timing, and new results are appended;
+ * sectors, precision; for launch shapes also whether the bonds share one
+ * amplitude and the sites one U, and the library's version of the shapes) is
+ * used without timing, and new results are appended;
  * unreadable or malformed entries are ignored.  Synchronises `stream`. */
 mbr_status mbr_hubbard_autotune(mbr_hubbard *h, int32_t reps, void *stream);
 

@@ -2470,6 +2470,18 @@ std::string tune_key(const mbr_hubbard *h) {
     return key;
 }
 
+// Key of a tuned launch shape.  Which kernel a shape means depends on whether the
+// bonds share one amplitude, and its cost on whether the sites share one U.  The
+// number changes when a shape comes to mean another kernel, so that older lines,
+// tuned when G = 0 meant the rows kernel for short sectors, match no longer.
+constexpr int kShapeVersion = 2;
+
+std::string shape_key(const mbr_hubbard *h) {
+    bool u_uniform = true;
+    for (double u : h->U) u_uniform = u_uniform && u == h->U[0];
+    return tune_key(h) + ";t" + (h->t_uniform ? "1" : "0") + ";u" + (u_uniform ? "1" : "0") + ";v" + std::to_string(kShapeVersion);
+}
+
 // Trie-ranked product: time the chunk widths that give two, three and four
 // levels over the 2L-bit patterns (at least 4 bits, at most 16) and keep the
 // fastest; same cache file and format as the launch-shape tuner, under the
@@ -2675,7 +2687,7 @@ mbr_status mbr_hubbard_autotune(mbr_hubbard *h, int32_t reps, void *stream) {
     if (reps < 1 || reps > 1000) MBR_FAIL(MBR_EINVAL, "reps=%d", reps);
     if (h->rank_kind == MBR_HV_RANK_TRIE) return autotune_trie_k(h, reps, stream);
     hipStream_t s = as_stream(stream);
-    const std::string key = tune_key(h);
+    const std::string key = shape_key(h);
     const char *path = std::getenv("MBR_AUTOTUNE_CACHE");
     if (path && *path) {
         std::ifstream in(path);
