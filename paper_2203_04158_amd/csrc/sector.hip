@@ -3,15 +3,15 @@
 // A sector is every M-bit pattern passing a set of popcount windows, in
 // ascending numeric order (Sec. III ordering).
 //
-// Up to 32 orbitals a wave takes all patterns of one high part (the low
-// `low_bits` <= 14 bits run through, 64 at a time) and drops the high part at
-// once when it already breaks a window; see sector_block_kernel.
+// High part by high part (up to 32 orbitals): a wave takes all patterns of one
+// high part (the low `low_bits` <= 14 bits run through, 64 at a time), and a high
+// part that already breaks a window is dropped at once; see sector_block_kernel.
 //
-// Beyond, the particle number N has to be fixed and the enumeration walks the
-// C(M,N) patterns of that number: each thread owns a run of consecutive
-// combination indices, positions itself with a greedy combinadics unrank
-// (inverse of Eq. cns) and steps to the next larger pattern of equal popcount
-// with Gosper's rule.
+// Run by run (a fixed particle number N): the enumeration walks the C(M,N)
+// patterns of that number, where each thread owns a run of consecutive combination
+// indices, positions itself with a greedy combinadics unrank (inverse of Eq.
+// cns) and steps to the next larger pattern of equal popcount with Gosper's rule.
+// Beyond 32 orbitals this is the only way; below, runs_are_faster decides.
 //
 // High parts and runs are visited in increasing order, so a count pass, an
 // exclusive scan of the counts and a write pass give the sorted list without
@@ -87,8 +87,9 @@ __global__ void sector_count_kernel(uint64_t S, uint64_t run, int N, int M, Cons
     counts[t] = cnt;
 }
 
+template <class P>
 __global__ void sector_fill_kernel(uint64_t S, uint64_t run, int N, int M, ConsSet cs,
-                                   const uint64_t *bt, const uint64_t *offsets, uint64_t *out,
+                                   const uint64_t *bt, const uint64_t *offsets, P *out,
                                    uint64_t nruns) {
     uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     if (t >= nruns) return;
@@ -97,7 +98,7 @@ __global__ void sector_fill_kernel(uint64_t S, uint64_t run, int N, int M, ConsS
     uint64_t a = combo_at(u0, N, M, bt);
     uint64_t o = offsets[t];
     for (uint64_t j = 0; j < len; ++j) {
-        if (in_sector(a, cs)) out[o++] = a;
+        if (in_sector(a, cs)) out[o++] = static_cast<P>(a);
         if (j + 1 < len) a = next_combo(a);
     }
 }
@@ -117,7 +118,8 @@ struct ConsSet32 {
 
 constexpr int kMaxLow = 14;                   // low bits a wave runs through
 constexpr int kMaxHigh = 32 - kMaxLow;
-constexpr unsigned kSecBlock = 256, kSecWaves = kSecBlock / 64;
+constexpr unsigned kSecBlock = 512;
+constexpr uint32_t kSecQueue = 512;            // high parts a workgroup looks over together
 constexpr uint32_t kStepUnroll = 4;            // steps in flight (the table of step weights has room for them)
 constexpr uint32_t kScanChunk = 1024;         // counts per scan workgroup
 constexpr uint32_t kMaxChunks = (1u << kMaxHigh) / kScanChunk;
@@ -134,60 +136,85 @@ __device__ __forceinline__ uint32_t weight_of(uint32_t bits, int shift, const ui
     return w;
 }
 
-// One wave per high part h: the patterns (h << low_bits) | p, p ascending, 64 at
-// a time, tested against every window (three instructions each) and against
-// the modular weight, which is split into a part per lane (bits 0-5), one per
-// step (a table in LDS) and one per high part.  Without FILL the members are
-// counted, with it they are written from offsets[h] on.
+// A permutation of [0, 2^bits): which high parts a workgroup takes.  Open ones are
+// alike (few bits set, when there are few particles), and any regular stride
+// hands them to a few workgroups.
+__device__ __forceinline__ uint32_t spread(uint32_t i, int bits) {
+    const uint32_t mask = (uint32_t)((1ull << bits) - 1);
+    uint32_t x = (i * 0x9E3779B1u) & mask;
+    x ^= x >> ((bits + 1) / 2);
+    return (x * 0x9E3779B1u) & mask;
+}
+
+// A workgroup looks over `together` (up to kSecQueue) high parts and queues the
+// open ones in LDS, for its waves to take in turn.  One wave per high part h: the
+// patterns (h << low_bits) | p, p ascending, 64 at a time, tested against every
+// window (three instructions each) and against the modular weight, which is
+// split into a part per lane (bits 0-5), one per step (a table in LDS) and one
+// per high part.  Without FILL the members are counted, with it they are written
+// from offsets[h] on.
 //
 // Bound by the issue of these tests and the chain of a wave's few open high
-// parts.  Testing every pattern of the high parts that the windows leave open
-// costs less than enumerating the C(M,N) patterns of the right particle number
-// one by one, which took an unrank per 64 patterns and, per pattern, 64-bit
-// windows, a loop over the set bits for the weight and a 64-bit remainder:
-// total momentum 3 of the 14-site ring (841,332 states), both passes:
-// 524 -> 83 us, and the counts no longer go through host memory.
+// parts, hence the queue: with high parts dealt out to the waves at a fixed
+// stride, one wave had up to all of its 32 open (32 orbitals, 4 particles: 1,382
+// us, with the queue 147).  Enumerating the C(M,N) patterns of the right
+// particle number one by one costs an unrank per 64 patterns and, per pattern,
+// 64-bit windows, a loop over the set bits for the weight and a 64-bit
+// remainder: total momentum 3 of the 14-site ring (841,332 states), both
+// passes: 524 -> 83 us, and the counts no longer go through host memory.
 template <class P, bool FILL, int NW>
-__global__ void __launch_bounds__(kSecBlock) sector_block_kernel(int low_bits, uint32_t n_high, ConsSet32 cs,
+__global__ void __launch_bounds__(kSecBlock) sector_block_kernel(int low_bits, uint32_t n_high, uint32_t together, ConsSet32 cs,
                                                                  uint32_t *__restrict__ counts,
                                                                  const uint64_t *__restrict__ chunk0, P *__restrict__ out) {
     __shared__ uint32_t weight[32];
     __shared__ __align__(16) uint32_t step_weight[1 << (kMaxLow - 6)];
+    __shared__ uint2 queue[kSecQueue];
+    __shared__ uint32_t queued;
     const uint32_t steps = low_bits > 6 ? 1u << (low_bits - 6) : 1u;
     const uint32_t lane = threadIdx.x & 63;
     const bool on = low_bits >= 6 || lane < (1u << low_bits);
     const uint32_t modulus = cs.modulus;  // 1 and all weights 0 without a modular weight
+    if (threadIdx.x == 0) queued = 0;
     if (threadIdx.x < 32) weight[threadIdx.x] = cs.weight[threadIdx.x];
     __syncthreads();
-    for (uint32_t s = threadIdx.x; s < std::max(steps, kStepUnroll); s += kSecBlock) step_weight[s] = weight_of(s, 6, weight, modulus);
+    for (uint32_t s = threadIdx.x; s < std::max(steps, kStepUnroll); s += blockDim.x) step_weight[s] = weight_of(s, 6, weight, modulus);
     const uint32_t lane_weight = weight_of(lane, 0, weight, modulus);
     __syncthreads();
     const uint32_t low_mask = (1u << low_bits) - 1;
-    // a wave's high parts lie waves apart, so that no wave gets a stretch of open ones; a lane looks at one each
-    const uint32_t waves = gridDim.x * kSecWaves, wave = blockIdx.x * kSecWaves + (threadIdx.x >> 6);
-    for (uint64_t h0 = wave; h0 < n_high; h0 += 64ull * waves) {
-        const uint64_t mine = h0 + (uint64_t)lane * waves;
-        const uint32_t mh = (uint32_t)mine;
-        bool open = mine < n_high;
-        uint32_t mine_need = 0;  // weight the low bits have to bring
-        if (open) {
-            const uint32_t high = mh << low_bits;
-            for (int j = 0; j < cs.n; ++j) {
-                const int c = __popc(high & cs.mask[j]), more = __popc(cs.mask[j] & low_mask);
-                open = open && c <= cs.lo[j] + (int)cs.width[j] && c + more >= cs.lo[j];
-            }
+    const int high_bits = 31 - __builtin_clz(n_high);
+    const uint32_t wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    for (uint64_t i0 = blockIdx.x; i0 < n_high; i0 += (uint64_t)together * gridDim.x) {
+        for (uint32_t k = threadIdx.x; k < together; k += blockDim.x) {
+            const uint64_t i = i0 + (uint64_t)k * gridDim.x;
+            bool open = i < n_high;
+            const uint32_t mh = open ? spread((uint32_t)i, high_bits) : 0u;
+            uint32_t need = 0;  // weight the low bits have to bring
             if (open) {
-                mine_need = cs.residue + modulus - weight_of(mh, low_bits, weight, modulus);
-                mine_need = mine_need >= modulus ? mine_need - modulus : mine_need;
+                const uint32_t high = mh << low_bits;
+                for (int j = 0; j < cs.n; ++j) {
+                    const int c = __popc(high & cs.mask[j]), more = __popc(cs.mask[j] & low_mask);
+                    open = open && c <= cs.lo[j] + (int)cs.width[j] && c + more >= cs.lo[j];
+                }
+                if (open) {
+                    need = cs.residue + modulus - weight_of(mh, low_bits, weight, modulus);
+                    need = need >= modulus ? need - modulus : need;
+                }
+                if constexpr (!FILL) {
+                    if (!open) counts[mh] = 0;
+                }
             }
-            if constexpr (!FILL) {
-                if (!open) counts[mh] = 0;
+            const uint64_t live = __ballot(open);
+            if (live) {
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&queued, (uint32_t)__popcll(live));
+                at = __builtin_amdgcn_readfirstlane(at);
+                if (open) queue[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0))] = make_uint2(mh, need);
             }
         }
-        for (uint64_t live = __ballot(open); live; live &= live - 1) {
-            const int i = __builtin_ctzll(live);
-            const uint32_t h = (uint32_t)h0 + (uint32_t)i * waves, high = h << low_bits;
-            const uint32_t need = (uint32_t)__builtin_amdgcn_readlane((int)mine_need, i);
+        __syncthreads();
+        for (uint32_t q = wave; q < queued; q += waves) {
+            const uint32_t h = __builtin_amdgcn_readfirstlane(queue[q].x), high = h << low_bits;
+            const uint32_t need = __builtin_amdgcn_readfirstlane(queue[q].y);
             uint32_t n = 0;
             uint64_t o = 0;
             if constexpr (FILL) o = chunk0[h / kScanChunk] + counts[h];
@@ -216,6 +243,11 @@ __global__ void __launch_bounds__(kSecBlock) sector_block_kernel(int low_bits, u
             if constexpr (!FILL) {
                 if (lane == 0) counts[h] = n;
             }
+        }
+        if (i0 + (uint64_t)together * gridDim.x < n_high) {  // the queue fills again
+            __syncthreads();
+            if (threadIdx.x == 0) queued = 0;
+            __syncthreads();
         }
     }
 }
@@ -309,7 +341,58 @@ int implied_n(int M, const std::vector<mbr_popc_cons> &cons) {
     return covered == full ? n : -1;
 }
 
-// The list of a sector of more than 32 orbitals and N particles, run by run.
+// Low bits of list_blocks: 2^10 to 2^14 patterns per high part, about 2^16 high
+// parts from 26 orbitals on.
+int low_bits_of(int M) { return std::min(M, std::max(10, std::min(kMaxLow, M - 16))); }
+
+// Windows that hold one of the low bits.
+int low_windows(const std::vector<mbr_popc_cons> &cons, int low) {
+    return (int)std::count_if(cons.begin(), cons.end(), [&](const mbr_popc_cons &c) { return (c.mask & ((1ull << low) - 1)) != 0; });
+}
+
+// Share of the high parts that the windows leave open: exact for windows that
+// share no bits (which are then independent), else by a set of such windows, the
+// narrowest first.
+double open_share(int M, int low, const std::vector<mbr_popc_cons> &cons) {
+    std::vector<std::pair<double, uint64_t>> each;
+    for (const mbr_popc_cons &c : cons) {
+        const int below = __builtin_popcountll(c.mask & ((1ull << low) - 1)), above = __builtin_popcountll(c.mask) - below;
+        double some = 0;
+        for (int k = 0; k <= above; ++k)
+            if (k <= c.hi && k + below >= c.lo) some += (double)mbr::binom(above, k);
+        each.push_back({some / (double)(1ull << above), c.mask});
+    }
+    std::sort(each.begin(), each.end());
+    double share = 1;
+    uint64_t seen = 0;
+    for (const auto &[part, mask] : each)
+        if (!(mask & seen)) {
+            share *= part;
+            seen |= mask;
+        }
+    return share;
+}
+
+// Whether a sector of up to 32 orbitals with N particles, S = C(M,N), is listed
+// sooner by its runs.  In units of one pattern tested against one window (about
+// 1 us per million), high parts cost their open patterns and the chain of one
+// of them, times 1.3 with two or three windows in the low bits and 5 with more
+// (the kernel's instances); runs cost 23.5 per pattern, 47 with a modular weight,
+// and a start that grows with the windows.  Beyond 2^28 patterns the counts
+// that the runs carry through host memory double their cost.  us by runs / by
+// high parts, M orbitals and N particles, one window: M = 32, N = 4 100 / 147, N = 8
+// 355 / 1,497, N = 10 1,800 / 2,676, N = 16 30,600 / 3,877; M = 28, N = 6 105 / 111,
+// N = 8 167 / 205, N = 10 446 / 261; M = 26, N = 8 131 / 100; 16 sites with (3, 5)
+// particles 291 / 381, (3, 6) 592 / 535; nine windows, M = 26, N = 10 334 / 391.
+bool runs_are_faster(int M, int N, uint64_t S, const std::vector<mbr_popc_cons> &cons, bool weighted) {
+    if (N < 0 || S > (1ull << 28)) return false;
+    const int low = low_bits_of(M), n_low = low_windows(cons, low);
+    const double each = n_low <= 1 ? 1.0 : n_low <= 3 ? 1.3 : 5.0, chain = 2e3 * (double)(1 << low), all = (double)(1ull << M);
+    const double by_runs = (weighted ? 47.0 : 23.5) * ((double)S + 1.6e6 + 0.6e6 * (double)cons.size());
+    return each * (all + chain) > by_runs && each * (open_share(M, low, cons) * all + chain) > by_runs;
+}
+
+// The list of a sector of N particles, run by run.
 mbr_status list_runs(mbr_sector &sec, int N, uint64_t S, hipStream_t s) {
     using namespace mbr;
     const int M = sec.M;
@@ -346,10 +429,13 @@ mbr_status list_runs(mbr_sector &sec, int N, uint64_t S, hipStream_t s) {
     }
     if (total >= 0xFFFFFFFFull) MBR_FAIL(MBR_ERANGE, "sector of %llu states", (unsigned long long)total);
     sec.n = total;
-    MBR_TRY(sec.states.alloc(total * 8));
+    MBR_TRY(sec.states.alloc(total * (sec.width_bits / 8)));
     MBR_TRY(upload(d_off, off.data(), nruns * sizeof(uint64_t), s));
     if (total > 0) {
-        sector_fill_kernel<<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_off.as<uint64_t>(), sec.states.as<uint64_t>(), nruns);
+        if (sec.width_bits == 32)
+            sector_fill_kernel<<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_off.as<uint64_t>(), sec.states.as<uint32_t>(), nruns);
+        else
+            sector_fill_kernel<<<grid, blk, 0, s>>>(S, run, N, M, cs, bt, d_off.as<uint64_t>(), sec.states.as<uint64_t>(), nruns);
         MBR_HIP(hipGetLastError());
         MBR_HIP(hipStreamSynchronize(s));
     }
@@ -360,11 +446,10 @@ mbr_status list_runs(mbr_sector &sec, int N, uint64_t S, hipStream_t s) {
 mbr_status list_blocks(mbr_sector &sec, hipStream_t s) {
     using namespace mbr;
     const int M = sec.M;
-    // 2^10 to 2^14 patterns per wave, about 2^16 waves from 26 orbitals on
-    const int low = std::min(M, std::max(10, std::min(kMaxLow, M - 16)));
+    const int low = low_bits_of(M);
     const uint32_t n_high = 1u << (M - low), chunks = (n_high + kScanChunk - 1) / kScanChunk;
     ConsSet32 cs{};
-    int n_low = 0;  // windows with low bits; the others hold or fail with the high part
+    const int n_low = low_windows(sec.cons, low);  // the other windows hold or fail with the high part
     for (const bool with_low : {true, false}) {
         for (const mbr_popc_cons &c : sec.cons) {
             if (((c.mask & ((1ull << low) - 1)) != 0) != with_low) continue;
@@ -372,7 +457,6 @@ mbr_status list_blocks(mbr_sector &sec, hipStream_t s) {
             cs.lo[cs.n] = c.lo;
             cs.width[cs.n++] = (uint32_t)(c.hi - c.lo);
         }
-        if (with_low) n_low = cs.n;
     }
     cs.modulus = sec.modulus > 0 ? (uint32_t)sec.modulus : 1u;
     cs.residue = (uint32_t)sec.residue;
@@ -381,12 +465,16 @@ mbr_status list_blocks(mbr_sector &sec, hipStream_t s) {
     MBR_TRY(scratch.alloc((size_t)(chunks + 1) * 8 + (size_t)n_high * 4));
     uint64_t *sums = scratch.as<uint64_t>();
     uint32_t *counts = reinterpret_cast<uint32_t *>(sums + chunks + 1);
-    const unsigned grid = grid_for(n_high, kSecWaves, device_cu_count() * 8);
+    // a wave for every high part while that leaves CUs idle, then up to 32 waves a CU
+    const uint32_t cus = (uint32_t)device_cu_count();
+    const unsigned block = 64 * std::clamp(n_high / cus, 1u, kSecBlock / 64);
+    const unsigned grid = grid_for(n_high, block / 64, cus * (2048 / kSecBlock));
+    const uint32_t together = std::min((n_high + grid - 1) / grid, kSecQueue);
     // windows tested per pattern
     const int nw = n_low <= 1 ? 1 : n_low <= 3 ? 3 : kMaxCons;
     const auto count = nw == 1 ? sector_block_kernel<uint32_t, false, 1> : nw == 3 ? sector_block_kernel<uint32_t, false, 3>
                                                                                     : sector_block_kernel<uint32_t, false, kMaxCons>;
-    count<<<grid, kSecBlock, 0, s>>>(low, n_high, cs, counts, nullptr, nullptr);
+    count<<<grid, block, 0, s>>>(low, n_high, together, cs, counts, nullptr, nullptr);
     sector_scan_kernel<<<chunks, kScanChunk, 0, s>>>(counts, n_high, sums);
     sector_chunks_kernel<<<1, 64, 0, s>>>(sums, chunks);
     MBR_HIP(hipGetLastError());
@@ -400,11 +488,11 @@ mbr_status list_blocks(mbr_sector &sec, hipStream_t s) {
         if (sec.width_bits == 32) {
             const auto fill = nw == 1 ? sector_block_kernel<uint32_t, true, 1> : nw == 3 ? sector_block_kernel<uint32_t, true, 3>
                                                                                            : sector_block_kernel<uint32_t, true, kMaxCons>;
-            fill<<<grid, kSecBlock, 0, s>>>(low, n_high, cs, counts, sums, sec.states.as<uint32_t>());
+            fill<<<grid, block, 0, s>>>(low, n_high, together, cs, counts, sums, sec.states.as<uint32_t>());
         } else {
             const auto fill = nw == 1 ? sector_block_kernel<uint64_t, true, 1> : nw == 3 ? sector_block_kernel<uint64_t, true, 3>
                                                                                            : sector_block_kernel<uint64_t, true, kMaxCons>;
-            fill<<<grid, kSecBlock, 0, s>>>(low, n_high, cs, counts, sums, sec.states.as<uint64_t>());
+            fill<<<grid, block, 0, s>>>(low, n_high, together, cs, counts, sums, sec.states.as<uint64_t>());
         }
         MBR_HIP(hipGetLastError());
         MBR_HIP(hipStreamSynchronize(s));
@@ -449,8 +537,8 @@ mbr_status sector_build_impl(int32_t M, int32_t width_bits, int32_t n_cons, cons
     sec->residue = residue;
     for (int i = 0; i < M && modulus > 0; ++i) sec->weights.push_back(weights[i] % modulus);
     MBR_HIP(hipGetDevice(&sec->device));
-    if (M <= 32) MBR_TRY(list_blocks(*sec, s));
-    else MBR_TRY(list_runs(*sec, N, S, s));
+    if (M > 32 || runs_are_faster(M, N, S, cv, modulus > 0)) MBR_TRY(list_runs(*sec, N, S, s));
+    else MBR_TRY(list_blocks(*sec, s));
     *out = sec.release();
     return MBR_OK;
 }
