@@ -479,10 +479,27 @@ constexpr uint32_t kFoldGroups = 64;   // groups per sector up to which lz_subtr
 // chip short of workgroups (eight per CU wanted); a lone sector's steps take the
 // least.  Ten sites, 1,048,576 rows, 40 steps: 4.91 ms with 4,096 rows a group,
 // 4.35 with 2,048, 3.93 with 1,024, 4.28 with 512 (too many to sum in place).
-constexpr uint64_t kGroupMin = 1024;
+constexpr uint64_t kGroupMin = 1024, kGroupMax = 4096;
 inline uint64_t group_rows(uint64_t total) {
     const uint64_t g = total / ((uint64_t)device_cu_count() * 8);
-    return g < kGroupMin ? kGroupMin : g > 4096 ? 4096 : g;
+    return g < kGroupMin ? kGroupMin : g > kGroupMax ? kGroupMax : g;
+}
+
+// Least alpha_up blocks in a group of the Gram-Schmidt steps when a sector has the
+// chip to itself.  Every group is one more partial of every sum and one more block
+// reduction per eight basis vectors, and beyond two a CU nothing is gained for
+// them; in fp64 two blocks in turn on one CU are also better as one group.  Sectors
+// long enough to give every CU several groups of kGroupMax rows have those
+// (rounded up: one block of 3,432 rows was 3% slower than two).  us a step, one
+// block a group / this rule: 12 sites, 924 x 924, 60 steps 119 / 112 (fp64), 74 / 69
+// (fp32); 13 sites, 1716 x 1716 385 / 364, 213 / 194; 14 sites, 2002 x 1001 287 / 258,
+// 171 / 141; 364 x 3003, 200 steps 411 / 380 (fp64; in fp32 219, 244 with two);
+// 3432 x 3432 3,813 / 3,748, 2,004 / 1,896.
+inline uint32_t alone_blocks(const HvSector &sc, size_t tsz) {
+    const uint32_t cus = (uint32_t)device_cu_count();
+    if ((uint64_t)sc.cup * sc.cdn >= kGroupMax * 8 * cus) return (uint32_t)((kGroupMax + sc.cdn - 1) / sc.cdn);
+    const uint32_t n = (sc.cup + 2 * cus - 1) / (2 * cus);
+    return n == 1 && tsz == 8 && sc.cup > cus ? 2 : n;
 }
 
 // Sums of eight values over the wave: three exchanges that halve the values a
@@ -1050,7 +1067,9 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
     {
         // groups of whole alpha_up blocks of a sector, whatever the product's
         // tiles (without reorthogonalisation the same for batched and per-sector
-        // steps, whose sums are then the same)
+        // steps, whose sums are then the same); with it, a sector that has the
+        // chip to itself takes fewer
+        const bool alone = lz->ns == 1 || !o->batched;
         const uint64_t grow = o->batched || !o->reorth ? group_rows(lz->total) : kGroupMin;
         std::vector<HvTile> groups;
         std::vector<HvSector> rsecs = lz->secs;
@@ -1060,7 +1079,8 @@ mbr_status mbr_lanczos_create(const mbr_hubbard *h, const mbr_lanczos_opts *o, m
             const HvSector &sc = lz->secs[si];
             lz->rt0[si] = (uint32_t)groups.size();
             rsecs[si].slot0 = (uint32_t)groups.size();
-            const uint32_t nblk = (uint32_t)std::max<uint64_t>(1, grow / sc.cdn);
+            uint32_t nblk = (uint32_t)std::max<uint64_t>(1, grow / sc.cdn);
+            if (o->reorth && alone) nblk = std::max(nblk, alone_blocks(sc, lz->tsz));
             for (uint32_t r = 0; r < sc.cup; r += nblk)
                 groups.push_back({(uint32_t)si, r, std::min(nblk, sc.cup - r), (uint32_t)groups.size()});
             lz->rnt[si] = (uint32_t)groups.size() - lz->rt0[si];
