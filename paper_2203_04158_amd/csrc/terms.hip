@@ -9,10 +9,11 @@
 // The product is taken in gather form from the bra side (Eq. Talpha2), each
 // output row summed by one wave or workgroup, so no atomics are needed:
 //   y_alpha = sum_T v [alpha AND m == l] (-1)^popcount(alpha AND s) x[rank(alpha XOR x_T)]
-// with alpha = states[row].  Ranks come from two small tables where the sector
-// allows it (op_sum_tables), else from the operator's ranker: a staggered
-// table (sector C^M_N; table staged in LDS when it fits) or a packed trie (any
-// sector; walk plus membership check).
+// with alpha = states[row].  Ranks of 32-bit patterns come from two small tables
+// where the sector allows it (op_sum_tables; C^M_N always does), else from the
+// packed trie (any sector; walk plus membership check).  64-bit patterns are
+// ranked by the operator's ranker: a staggered table (sector C^M_N; staged in
+// LDS when it fits) or a trie.
 #include <algorithm>
 #include <memory>
 #include <tuple>
@@ -766,15 +767,18 @@ mbr_status with_kernel(const mbr_operator *op, F f) {
             if (nb + no <= kOpTables) return f(op_apply_kernel<P, uint16_t, kSumLds>, nb + no);
             return f(op_apply_kernel<P, uint16_t, kSumGlobal>, no);
         }
-    }
-    if (r->kind == MBR_RANKER_TRIE) return f(op_apply_kernel<P, uint32_t, kTrie>, (size_t)0);
-    const StagTable &tb = r->stag;
-    const size_t lds = ((size_t)tb.nrows << tb.k) * tb.entry_bytes;
-    const bool in_lds = lds <= kLdsTable;
-    switch (tb.entry_bytes) {
-        case 2: return in_lds ? f(op_apply_kernel<P, uint16_t, kStagLds>, lds) : f(op_apply_kernel<P, uint16_t, kStagGlobal>, (size_t)0);
-        case 4: return in_lds ? f(op_apply_kernel<P, uint32_t, kStagLds>, lds) : f(op_apply_kernel<P, uint32_t, kStagGlobal>, (size_t)0);
-        default: return in_lds ? f(op_apply_kernel<P, uint64_t, kStagLds>, lds) : f(op_apply_kernel<P, uint64_t, kStagGlobal>, (size_t)0);
+        if (r->kind == MBR_RANKER_TRIE) return f(op_apply_kernel<P, uint32_t, kTrie>, (size_t)0);
+        MBR_FAIL(MBR_EUNSUPPORTED, "a staggered sector of %d orbitals without sum tables", op->M);
+    } else {
+        if (r->kind == MBR_RANKER_TRIE) return f(op_apply_kernel<P, uint32_t, kTrie>, (size_t)0);
+        const StagTable &tb = r->stag;
+        const size_t lds = ((size_t)tb.nrows << tb.k) * tb.entry_bytes;
+        const bool in_lds = lds <= kLdsTable;
+        switch (tb.entry_bytes) {
+            case 2: return in_lds ? f(op_apply_kernel<P, uint16_t, kStagLds>, lds) : f(op_apply_kernel<P, uint16_t, kStagGlobal>, (size_t)0);
+            case 4: return in_lds ? f(op_apply_kernel<P, uint32_t, kStagLds>, lds) : f(op_apply_kernel<P, uint32_t, kStagGlobal>, (size_t)0);
+            default: return in_lds ? f(op_apply_kernel<P, uint64_t, kStagLds>, lds) : f(op_apply_kernel<P, uint64_t, kStagGlobal>, (size_t)0);
+        }
     }
 }
 
@@ -830,10 +834,12 @@ mbr_status op_sum_tables(mbr_operator *op, int low, hipStream_t st) {
 }
 
 // Tiles and launch shape of op_low_kernel: the rows of every high part in
-// pieces of 64.  op->n_tiles stays 0 where op_apply_kernel is the faster one:
-// where the work is too small to repay the longer chain of a wave (fewer than
-// 2^14 rows or 2^24 pairs of row and tuple), or where the high parts leave
-// more than half of the lanes without a row.  us per product, op_apply / op_low:
+// pieces of 64.  op->n_tiles stays 0, and op_apply_kernel runs, where the work is
+// too small to repay the longer chain of a wave (fewer than 2^14 rows or 2^24
+// pairs of row and tuple), or where the high parts leave more than half of the
+// lanes without a row.  The first two lines are a compromise: neither rows nor
+// pairs alone part the kernels, and the rings of up to 10 sites give away less
+// than 2 us for what 16 orbitals keep.  us per product, op_apply / op_low:
 //   ring,    10 sites,   6,352 rows,  1,020 tuples: 10.7 / 9.0
 //   general, 16 orbitals, 12,870 rows, 14,656 tuples: 104 / 122
 //   ring,    11 sites,  19,404 rows,  1,353 tuples: 24.0 / 21.0
