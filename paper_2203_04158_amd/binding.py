@@ -24,6 +24,7 @@ RANK_HALVES, RANK_TRIE = 0, 1
 
 _lib = None
 _T = None  # torch, once the library is loaded
+_raw_stream = None  # torch's own (current stream of a device as an integer, current device), where it has them
 
 
 class MbrError(RuntimeError):
@@ -174,7 +175,7 @@ _SIGS = {
 
 def lib() -> C.CDLL:
     """Load libmbrank.so; raises if it has not been built."""
-    global _lib, _T
+    global _lib, _T, _raw_stream
     if _lib is None:
         # torch ships its own HIP runtime with the same soname as the system one;
         # loading torch first makes libmbrank bind to that runtime, so the process
@@ -196,8 +197,16 @@ def lib() -> C.CDLL:
             # a library older than this binding: calling these raises
             for name in missing:
                 setattr(L, name, _missing_symbol(name))
-        _lib, _T = L, torch
+        _lib, _T, _raw_stream = L, torch, _find_raw_stream(torch)
     return _lib
+
+
+def _find_raw_stream(torch):
+    """The two functions that current_stream() is made of, or None: they are not
+    part of torch's public interface, and a torch without them is asked through
+    current_stream()."""
+    found = [getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice")]
+    return tuple(found) if all(callable(f) for f in found) else None
 
 
 def _missing_symbol(name: str):
@@ -221,8 +230,9 @@ def _check(fn: str, st: int) -> None:
 def _stream(stream):
     if stream is None:
         torch = _T or _torch()
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream and torch.cuda.is_initialized():
+            current, device = _raw_stream
+            return current(device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
