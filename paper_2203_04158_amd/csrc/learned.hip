@@ -469,7 +469,7 @@ __global__ void __launch_bounds__(kGradBlock) mlp_grad_kernel(const float *__res
     constexpr int S = 16 * NT, LD = S + 1;
     __shared__ float h1[kH * LD], d1[kH * LD], d2[kH * LD];  // [feature][sample]
     __shared__ float ysum[kGradBlock / 64][S], ts[S];
-    __shared__ uint32_t xs[S];
+    __shared__ uint32_t xs[S], again;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
     const int row = 16 * wv + 4 * g;  // this lane's rows of a C fragment: row .. row + 3
     float a1[kIn / 4], a2[kH / 4], a2t[kH / 4];
@@ -619,13 +619,16 @@ __global__ void __launch_bounds__(kGradBlock) mlp_grad_kernel(const float *__res
                     }
         }
     };
-    pass(std::false_type{});
-    bool odd = !isfinite(gb3);
+    if (threadIdx.x == 0) again = 0;
+    pass(std::false_type{});  // with barriers behind the line above
+    float probe = gb3;        // not finite if any of these is not
 #pragma unroll
-    for (int k = 0; k < kIn / 4; ++k) odd = odd || !isfinite(a1[k]);
+    for (int k = 0; k < kIn / 4; ++k) probe += 0.f * a1[k];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) odd = odd || !isfinite(w3[r]) || !isfinite(gb1[r]) || !isfinite(gb2[r]);
-    if (__syncthreads_or(odd)) pass(std::true_type{});
+    for (int r = 0; r < 4; ++r) probe += 0.f * w3[r] + (gb1[r] + gb2[r]);
+    if (!isfinite(probe)) again = 1;
+    __syncthreads();
+    if (again) pass(std::true_type{});
     float *out = part + (size_t)blockIdx.x * kPart;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
