@@ -2720,7 +2720,7 @@ mbr_status mbr_hubbard_autotune(mbr_hubbard *h, int32_t reps, void *stream) {
     for (int k : ks)
         for (int G : {-2, -1, 0, 1, 2, 4})
             for (int block : {256, 512}) {
-                if (G <= 0 && block != 512) continue;  // the rows, block and flat kernels have one block size each
+                if (G <= 0 && block != 512) continue;  // the other kernels have one block size each
                 if (configure(h, k, G, block, s) != MBR_OK) continue;
                 HvEpilogue ep{};
                 if (hubbard_launch(h, bx.p, by.p, ep, s) != MBR_OK) continue;

@@ -348,7 +348,7 @@ __global__ void lz_start_scalars(const HvSector *secs, LzDev d, int reorth) {
     }
 }
 
-// The reorthogonalising kernels move the rows of a tile (or merged group) as
+// The reorthogonalising kernels move the rows of a group of alpha_up blocks as
 // 16-byte packs: the vectors share one stride that is a multiple of 64 rows,
 // so a row index decides the alignment of every vector alike.  A span is the
 // unaligned head, the run of whole packs and the tail; its leftover rows (at
@@ -959,12 +959,12 @@ mbr_status enqueue_reorth(mbr_lanczos *lz, uint32_t s0, uint32_t nsec, uint32_t 
         ep.sector = s0;
     }
     MBR_TRY(hubbard_launch(lz->h, V, W, ep, s));
-    // the Gram-Schmidt kernels run over the merged groups of these sectors
+    // the Gram-Schmidt kernels run over the groups of these sectors
     const uint32_t g0 = all ? 0 : lz->rt0[s0], gn = all ? lz->n_rtiles : lz->rnt[s0];
     const HvTile *groups = lz->d_rtiles.as<HvTile>() + g0;
     const HvSector *rsecs = lz->d_rsecs.as<HvSector>();
     // batched: one workgroup per group, so the dispatcher balances groups of
-    // unequal size; per sector: the tile grid of the other kernels
+    // unequal size; per sector: the grid of the other kernels
     const unsigned g = all ? std::max<unsigned>(1, std::min<unsigned>(gn, 1u << 20))
                            : std::min<unsigned>(lz->grid, gn);
     lz_update_dots<T><<<g, kBlock, 0, s>>>(groups, gn, rsecs, secs, W, V, lz->ld, lz->m, lz->dev);
