@@ -21,10 +21,13 @@
 // prefix bytes and the map apart took two loads a step, and the walks are bound
 // by the rate of their scattered loads: 8,000,003 lookups of 64-bit patterns
 // among 7.1 M states, k = 8, 143 -> 115 us; 2^24 in 32-bit patterns of a sector
-// with 242,250 leaf records 258 -> 215 us.)
+// with 242,250 leaf records 258 -> 215 us.)  Queries in ascending order find their
+// records in the nearest cache, and a lookup is then bound by the issue of its vector
+// instructions, 18 a step: 2^24 of them among the C(28, N) states for N = 6 to 14 take
+// 53 us, with 25 a step 63 us, with base, prefix bytes and map apart 56 us.
 // The top levels that fit 48 KB are staged in LDS; large batches on a trie whose
-// next level fits 144 KB run with one workgroup of 1024 lanes per CU that stages
-// that level too.  With k = 8 the sector
+// next level fits 144 KB run with one or two workgroups of 1024 lanes per CU that
+// stage that level too.  With k = 8 the sector
 // M = 32, N = 16 with >= 6 of orbitals 0-7 occupied needs about 4 M leaf
 // records (its packed trie holds 332 M entries).
 #include <algorithm>
@@ -39,20 +42,26 @@ constexpr unsigned kBlock = 256;
 constexpr int kQ = 4;                      // independent walks in flight per lane
 constexpr size_t kLdsBudget = 48 * 1024;   // bytes of top levels staged per workgroup
 constexpr unsigned kWideBlock = 1024;
-constexpr size_t kWideBudget = 144 * 1024; // the same for a workgroup that has a CU to itself
+constexpr size_t kWideBudget = 144 * 1024; // the same for a workgroup of kWideBlock lanes, which has a CU to itself
+constexpr size_t kHalfCu = 80 * 1024;      // or shares it with one more up to here: 51 KB, 2^24 queries in order 62 -> 54 us
 // Batch from which the wider staging is taken: 8,000,003 lookups (36 orbitals,
 // k = 8, three levels in memory against two) 165 -> 143 us, 1,000,003 25.0 -> 24.1,
-// 300,003 13.0 either way.
+// 300,003 13.0 either way.  Queries in order gain nothing from it (98,280 states,
+// k = 8: 2^24 in 53 -> 58 us, 2^22 in 17 -> 18; scattered 106 -> 83 and 30 -> 25).
 constexpr uint64_t kWideMin = 1 << 19;
 constexpr int kMaxH = 32;
+
+// A level: its first word, the bit offset of its chunk, and the chunk's bits: all of
+// them (8-byte records) or those above the lowest five (others).
+struct alignas(16) BtLevel {
+    uint32_t off, shift, wid, none;
+};
 
 struct BtArgs {
     const uint32_t *rec;      // all levels' records, level after level
     int32_t M, H, lds_levels;
     uint32_t lds_words;       // words of the staged levels
-    uint32_t off[kMaxH];      // first word of each level
-    uint32_t shift[kMaxH];    // bit offset of each level's chunk
-    uint32_t cmask[kMaxH];    // chunk mask
+    BtLevel level[kMaxH];
 };
 
 constexpr uint32_t kPartBits = 96;  // chunk values per 16-byte part (records of 4 words and more)
@@ -68,37 +77,42 @@ __host__ __device__ constexpr uint32_t map_word(uint32_t rw, uint32_t c) {
 __host__ __device__ constexpr uint32_t map_bit(uint32_t c) { return c % 32; }  // 96 is a multiple of 32
 
 // What a step reads of a record: {base, map} or the 16-byte part of chunk value
-// c; and its answer: whether c occurs, and the child or rank, base + set bits
-// below c.  The words are combined with masks, not chosen by branches, which
-// would put the loads of the walks that advance together one after another.
+// c; and its answer: whether c occurs, and the child or rank counted from one,
+// base + set bits up to c.  The words are combined with masks, not chosen by
+// branches, which would put the loads of the walks that advance together one after
+// another; which words of the part lie below c's follows from a table with a bit per
+// word of the map, its place from one with a byte per word.
 template <int RW>
 struct BtPart {
     uint4 v;
-    __device__ __forceinline__ void load(const uint32_t *rec, uint32_t c) {
+    uint32_t w;  // word of the map that holds c's bit
+    // the record starts at rec[at]
+    __device__ __forceinline__ void load(const uint32_t *rec, uint32_t at, uint32_t c, uint32_t wid) {
         if constexpr (RW == 2) {
-            const uint2 h = *reinterpret_cast<const uint2 *>(rec);
+            const uint2 h = *reinterpret_cast<const uint2 *>(rec + at);
             v = make_uint4(h.x, h.y, 0, 0);
         } else {
-            v = *reinterpret_cast<const uint4 *>(rec + (RW == 4 ? 0u : 4 * part_of(c)));
+            w = __builtin_amdgcn_ubfe(c, 5, wid);
+            if constexpr (RW > 4) at += __builtin_amdgcn_perm(0x08080404u, 0x04000000u, w);
+            v = *reinterpret_cast<const uint4 *>(rec + at);
         }
     }
     __device__ __forceinline__ bool step(uint32_t c, uint32_t &next) const {
-        const uint32_t bit = 1u << map_bit(c), below = bit - 1u;
-        if constexpr (RW == 2) {
-            next = v.x + __popc(v.y & below);
-            return (v.y & bit) != 0;
-        } else {
-            const uint32_t word = RW == 4 ? c >> 5 : (c >> 5) - 3 * part_of(c);
-            const uint32_t past0 = word > 0 ? ~0u : 0u, past1 = RW > 4 && word > 1 ? ~0u : 0u;  // whole words below c's
-            uint32_t own = (v.y & ~past0) | (v.z & past0);
-            next = v.x + __popc(v.y & past0);
+        uint32_t own = v.y;
+        next = v.x;
+        if constexpr (RW > 2) {
+            const uint32_t past0 = (uint32_t)__builtin_amdgcn_sbfe(0xB6, w, 1);  // word 0 of the part is below c's
+            own = (v.y & ~past0) | (v.z & past0);
+            next += __popc(v.y & past0);
             if constexpr (RW > 4) {
+                const uint32_t past1 = (uint32_t)__builtin_amdgcn_sbfe(0x24, w, 1);  // and word 1
                 own = (own & ~past1) | (v.w & past1);
                 next += __popc(v.z & past1);
             }
-            next += __popc(own & below);
-            return (own & bit) != 0;
         }
+        const uint32_t upto = own << (~c & 31u);  // c's bit on top, those below it
+        next += __popc(upto);
+        return (int32_t)upto < 0;
     }
 };
 
@@ -109,46 +123,48 @@ __global__ void __launch_bounds__(BLOCK) bt_rank_kernel(const P *__restrict__ q,
     stage_to_lds(top, a.rec, (uint64_t)a.lds_words * 4);
     __syncthreads();
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    const P beyond = a.M >= (int)(8 * sizeof(P)) ? (P)0 : (P)(~(P)0 << a.M);
     for (uint64_t base = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; base < n; base += stride * kQ) {
         P x[kQ];
-        uint32_t node[kQ];
+        uint32_t node[kQ];  // counted from one
         bool ok[kQ];
 #pragma unroll
         for (int u = 0; u < kQ; ++u) {
             const uint64_t j = base + u * stride;
-            x[u] = j < n ? q[j] : (P)0;
-            ok[u] = j < n && (a.M >= (int)(8 * sizeof(P)) || (x[u] >> a.M) == 0);
-            node[u] = 0;
+            x[u] = q[j < n ? j : n - 1];  // a branch would have each load wait for the one before
+        }
+#pragma unroll
+        for (int u = 0; u < kQ; ++u) {
+            ok[u] = (x[u] & beyond) == 0;
+            node[u] = 1;
         }
         // staged levels from LDS, the rest through the caches; a walk that
-        // leaves the sector stays on record 0 of each further level
-        auto advance = [&](const uint32_t *lv, int l) {
+        // leaves the sector stays on the first record of each further level
+        auto advance = [&](const uint32_t *rec, const BtLevel &v) {
+            const uint32_t first = v.off - RW;
             uint32_t c[kQ];
             BtPart<RW> part[kQ];
 #pragma unroll
             for (int u = 0; u < kQ; ++u) {
-                c[u] = (uint32_t)(x[u] >> a.shift[l]) & a.cmask[l];
-                part[u].load(lv + node[u] * RW, c[u]);  // words < 2^32
+                // the chunk; from k = 6 on with what lies above it, which the step leaves out
+                c[u] = RW == 2 ? (uint32_t)(x[u] >> v.shift) & ((1u << v.wid) - 1u) : (uint32_t)(x[u] >> v.shift);
+                part[u].load(rec, node[u] * RW + first, c[u], v.wid);  // words < 2^32
             }
 #pragma unroll
             for (int u = 0; u < kQ; ++u) {
                 uint32_t nx;
                 const bool occurs = part[u].step(c[u], nx);
                 ok[u] = ok[u] && occurs;
-                node[u] = ok[u] ? nx : 0u;
+                node[u] = ok[u] ? nx : 1u;
             }
         };
         int l = 0;
-        for (; l < a.lds_levels; ++l) {
-            advance(top + a.off[l], l);
-        }
-        for (; l < a.H; ++l) {
-            advance(a.rec + a.off[l], l);
-        }
+        for (; l < a.lds_levels; ++l) advance(top, a.level[l]);
+        for (; l < a.H; ++l) advance(a.rec, a.level[l]);
 #pragma unroll
         for (int u = 0; u < kQ; ++u) {
             const uint64_t j = base + u * stride;
-            if (j < n) out[j] = ok[u] ? node[u] : MBR_NOT_FOUND;
+            if (j < n) out[j] = ok[u] ? node[u] - 1 : MBR_NOT_FOUND;
         }
     }
 }
@@ -318,7 +334,7 @@ mbr_status run_bt(const P *q, uint64_t n, uint32_t *out, const BtArgs &a, hipStr
     const size_t lds = (size_t)a.lds_words * 4;
     if (lds > 64 * 1024)
         MBR_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWideBudget));
-    const unsigned grid = mbr::grid_for(n, BLOCK * kQ, mbr::device_cu_count() * (BLOCK == kWideBlock ? 1 : 8));
+    const unsigned grid = mbr::grid_for(n, BLOCK * kQ, mbr::device_cu_count() * (BLOCK == kWideBlock ? (lds > kHalfCu ? 1 : 2) : 8));
     kern<<<grid, BLOCK, lds, s>>>(q, n, out, a);
     MBR_HIP(hipGetLastError());
     return MBR_OK;
@@ -334,9 +350,7 @@ mbr_status launch_bt(const mbr_ranker *r, const void *q, uint64_t n, uint32_t *o
     a.lds_levels = t.lds_levels;
     a.lds_words = (uint32_t)t.lds_words;
     for (int l = 0; l < t.H; ++l) {
-        a.off[l] = (uint32_t)t.off[l];
-        a.shift[l] = (uint32_t)t.shift[l];
-        a.cmask[l] = (1u << t.w[l]) - 1u;
+        a.level[l] = {(uint32_t)t.off[l], (uint32_t)t.shift[l], (uint32_t)(t.rw[0] == 2 ? t.w[l] : std::max(t.w[l] - 5, 0)), 0};
     }
     const bool wide = t.wide_levels > t.lds_levels && n >= kWideMin;
     if (wide) {
