@@ -216,7 +216,7 @@ def row_staggered(torch, mbr, reps):
     ms = time_launches(torch, lambda: mbr.rank_batch(r, q, out=out), reps)
     exact = bool(torch.equal(out, idx))
     roof = hbm_roofline(8.0 * nq, ms, "rank_staggered_kernel (4 B in, 4 B out per query)")
-    roof["traffic"] = traffic_for("rank_staggered_kernel<unsignedint,unsignedint,true,4,unsignedint>")
+    roof["traffic"] = traffic_for("rank_staggered_kernel<unsignedint,unsignedint,true,4,1,unsignedint>")
     # cold: each launch follows a 1 GB copy that evicts the L2s and the
     # last-level cache, so queries and table come from HBM (median of 10)
     scrub = torch.empty(1 << 28, dtype=torch.float32, device="cuda")
